@@ -12,9 +12,8 @@
 // and the two trace columns the next strip needs.  When only a few columns are requested
 // (the reduced form), phase C computes just those from compact copies of the spike rows.
 //
-// The chains of phases A and B read the next factor block from global memory into
-// registers while the current block (in LDS) is applied, then store it to the other LDS
-// buffer: the latency of the block loads stays off the dependency chain.
+// The chains of phases A and B read the factor blocks of the next steps from global memory
+// into rings of registers: the latency of the block loads stays off the dependency chain.
 //
 // Arithmetic is in T (float or double complex); gathered and scattered fields are FP64.
 #include "helm_internal.hpp"
@@ -165,22 +164,6 @@ __device__ inline void scatter(const SolveArgs<T>& a, int r, int l, int i, cplx<
     if (i == io.qo1 && io.tro1) io.tro1[(size_t)r * a.Ny + l] = xv;
 }
 
-// A factor block staged through registers into LDS.  Thread t owns elements
-// t + NT*j, j < BLK/NT, of the column-major block.
-template <typename T>
-struct BlockPipe {
-    static constexpr int PER = BLK / NT;
-    cplx<T> reg[PER];
-    __device__ void load(const cplx<T>* __restrict__ g) {
-#pragma unroll
-        for (int j = 0; j < PER; ++j) reg[j] = g[threadIdx.x + NT * j];
-    }
-    __device__ void store(cplx<T>* s) const {
-#pragma unroll
-        for (int j = 0; j < PER; ++j) s[threadIdx.x + NT * j] = reg[j];
-    }
-};
-
 // acc[u] += sum_{k<W} M(i,k) vin[k][g + G*u]   (M column-major WP x WP)
 template <typename T, int R, int G>
 __device__ inline void matvec(cplx<T> (&acc)[R / G], const cplx<T>* M, const cplx<T> (*vin)[R],
@@ -194,98 +177,96 @@ __device__ inline void matvec(cplx<T> (&acc)[R / G], const cplx<T>* M, const cpl
     }
 }
 
-// ---------------------------------------------------------------- phase A
-// R right-hand sides per workgroup; thread (i = t % 64, g = t / 64) owns row i of the
-// block and right-hand sides g, g+4, ...
+// ---------------------------------------------------------------- phase A, few right-hand sides
+// Panels of at most 4 right-hand sides (R = 1, 2 or 4 per workgroup): a chain of matrix-vector
+// products, bound by the latency of a step and by the 64 x 64 block each step reads (64 KB in
+// complex128, about 0.43 us through one CU's load path).  Thread (i, w) multiplies row i of the
+// block with the 16 columns 16 w .. 16 w + 15 straight from registers (a ring of D blocks, D
+// steps ahead); the four waves' partial sums meet in LDS behind the step's only barrier.  Wave w
+// then needs the result only at its own 16 columns: lane (row 16 w + lane % 16, right-hand side
+// lane / 16) adds the four partial sums, forms the next step's operand there and keeps it in a
+// part of LDS that only its wave reads.
 template <typename T, int R>
-__global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1, 1))) k_phase_a(SolveArgs<T> a) {
+__global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1, 1))) k_phase_a_few(SolveArgs<T> a) {
     using V = cplx<T>;
-    constexpr int G = 4, U = R / G;
-    __shared__ V Gs[2][BLK];
-    __shared__ V vin[WP][R];
-    const int t = threadIdx.x, i = t & (WP - 1), g = t >> 6;
-    const int c = blockIdx.x, rbase = blockIdx.y * R;
+    constexpr int D = std::is_same<T, double>::value && R > 1 ? 3 : 4;   // 3: no spills
+    __shared__ V vecw[4][R][16];
+    __shared__ V part[2][4][R][WP];
+    const int t = threadIdx.x, i = t & (WP - 1), w = t >> 6, k0 = 16 * w;
+    const int c = blockIdx.x;
     const int r0 = c * a.m;
     const int r1 = (c < a.P - 1) ? c * a.m + a.m - 1 : a.Ny;
     const int n = r1 - r0;
     const int steps = 2 * n - 1;                 // forward r0..r1-1, backward r1-2..r0
-    auto row_of = [&](int k) { return k < n ? r0 + k : r1 - 2 - (k - n); };
-    const V zero = cmk<V>(0, 0);
-    V z[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) z[u] = zero;
-
-    // the next step's block, staged through registers as separate real and imaginary parts
-    // (an array of complex128 values was kept in scratch memory)
-    constexpr int PER = BLK / NT;
-    T prx[PER], pry[PER];
-    auto pload = [&](const V* __restrict__ gsrc) {
-#pragma unroll
-        for (int j = 0; j < PER; ++j) {
-            const V v = gsrc[t + NT * j];
-            prx[j] = v.x;
-            pry[j] = v.y;
-        }
+    auto row_of = [&](int k) {
+        k = k < steps ? k : steps - 1;
+        return k < n ? r0 + k : r1 - 2 - (k - n);
     };
-    auto pstore = [&](V* dst) {
+    // this lane's element of the vectors
+    const int q = k0 + (i & 15), bl = i >> 4, b = bl < R ? bl : R - 1;
+    const int r = blockIdx.y * R + b;
+    const bool own = bl < R && r < a.nrhs;
+    V* Yr = a.Yw + (size_t)(own ? r : 0) * a.Ny * WP + q;
+    V breg[D][16];
+    auto load_blk = [&](int k, V (&g)[16]) {
+        const V* G = fslot(a, row_of(k), 0) + (size_t)k0 * WP + i;
 #pragma unroll
-        for (int j = 0; j < PER; ++j) dst[t + NT * j] = cmk<V>(prx[j], pry[j]);
+        for (int kk = 0; kk < 16; ++kk) g[kk] = G[kk * WP];
     };
-    pload(fslot(a, row_of(0), 0));
-    pstore(Gs[0]);
-    int cur = 0;
-    for (int k = 0; k < steps; ++k) {
+#pragma unroll
+    for (int d = 0; d < D; ++d) load_blk(d, breg[d]);
+    V z = cmk<V>(0, 0);
+    // loads of the next row, issued a step ahead: its right-hand side and coupling (forward),
+    // z_l and coupling (backward)
+    RawRhs raw = load_raw(a.io, own ? r : a.nrhs, r0, q, a.Ny, a.nrhs, a.W);
+    double2 cn = a.cy[r0];
+    V zn = z;
+    // v: the step's operand (this lane's element); returns (G v) there
+    auto product = [&](int k, V (&g)[16], V v) {
+        const int buf = k & 1;
+        if (bl < R) vecw[w][bl][i & 15] = v;
+        __builtin_amdgcn_wave_barrier();         // only this wave's lanes read the entries
+        V acc[R];
+#pragma unroll
+        for (int u = 0; u < R; ++u) acc[u] = cmk<V>(0, 0);
+#pragma unroll
+        for (int kk = 0; kk < 16; ++kk)
+#pragma unroll
+            for (int u = 0; u < R; ++u) cfma(acc[u], g[kk], vecw[w][u][kk]);
+        load_blk(k + D, g);
+#pragma unroll
+        for (int u = 0; u < R; ++u) part[buf][w][u][i] = acc[u];
+        __syncthreads();
+        return cadd(cadd(part[buf][0][b][q], part[buf][1][b][q]), cadd(part[buf][2][b][q], part[buf][3][b][q]));
+    };
+    auto step = [&](int k, int j) {
         const int l = row_of(k);
-        const bool fwd = k < n;
-        // unconditional (the last step reloads its own block)
-        pload(fslot(a, row_of(k + 1 < steps ? k + 1 : k), 0));
-        if (fwd) {
-            const V cl = ccast<V>(a.cy[l]);
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int r = rbase + g + G * u;
-                V v = zero;
-                if (r < a.nrhs && i < a.W) {
-                    v = gather<T>(a.io, r, l, i, a.Ny);
-                    if (l > r0) v = csub(v, cmul(cl, z[u]));
-                }
-                vin[i][g + G * u] = v;
-            }
+        if (k < n) {
+            V v = combine<T>(a.io, raw);
+            if (k > 0) v = csub(v, cmul(ccast<V>(cn), z));
+            const int ln = l + 1 < r1 ? l + 1 : l;
+            raw = load_raw(a.io, own ? r : a.nrhs, ln, q, a.Ny, a.nrhs, a.W);
+            cn = a.cy[ln];
+            z = product(k, breg[j], v);
+            if (own) Yr[(size_t)l * WP] = z;
+            if (k == n - 1 && n > 1) { cn = a.by[r1 - 2]; zn = Yr[(size_t)(r1 - 2) * WP]; }
         } else {
-#pragma unroll
-            for (int u = 0; u < U; ++u) vin[i][g + G * u] = z[u];
+            const V zl = zn, bk = ccast<V>(cn);
+            const int lb = l - 1 >= r0 ? l - 1 : l;
+            cn = a.by[lb];
+            zn = Yr[(size_t)lb * WP];
+            z = csub(zl, cmul(bk, product(k, breg[j], z)));
+            if (own) Yr[(size_t)l * WP] = z;
         }
-        __syncthreads();
-        V acc[U];
+    };
+    int k = 0;
+    for (; k + D <= steps; k += D) {
 #pragma unroll
-        for (int u = 0; u < U; ++u) acc[u] = zero;
-        matvec<T, R, G>(acc, Gs[cur], vin, a.W, i, g);
-        if (fwd) {
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int r = rbase + g + G * u;
-                z[u] = acc[u];
-                if (r < a.nrhs) a.Yw[((size_t)r * a.Ny + l) * WP + i] = acc[u];
-            }
-        } else {
-            const V bl = ccast<V>(a.by[l]);
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int r = rbase + g + G * u;
-                if (r < a.nrhs) {
-                    V* p = a.Yw + ((size_t)r * a.Ny + l) * WP + i;
-                    const V y = csub(*p, cmul(bl, acc[u]));
-                    *p = y;
-                    z[u] = y;
-                } else {
-                    z[u] = zero;
-                }
-            }
-        }
-        pstore(Gs[cur ^ 1]);
-        __syncthreads();
-        cur ^= 1;
+        for (int j = 0; j < D; ++j) step(k + j, j);
     }
+#pragma unroll
+    for (int j = 0; j < D; ++j)
+        if (k + j < steps) step(k + j, j);
 }
 
 // ---------------------------------------------------------------- phase A, MFMA
@@ -491,6 +472,158 @@ __global__ void __launch_bounds__(NT) k_phase_a_mfma_multi(MultiArgs<float> m) {
     Blk b;
     if (multi_blk(m, k, b)) phase_a_mfma<D>(m.a[k], b);
 }
+
+// ---------------------------------------------------------------- phase A, FP64 MFMA
+// complex128, 16 right-hand sides per workgroup: the block product of a step (64 x 64 times
+// 64 x 16, complex) as four real products on v_mfma_f64_16x16x4f64, wave w owning output rows
+// 16 w .. 16 w + 15.  The FP64 matrix and vector peaks are equal on MI355X; what the VALU form
+// lost was everything else: every block went through registers into LDS and back (64 KB each
+// way per step) behind two barriers.  Here each lane loads its 16 A operands of a block
+// straight into a ring of two register blocks and refills them between the products, as in
+// the complex64 form, and a step has one barrier.  Bound by its 64 MFMAs per wave and step
+// (64 cycles each, 1.7 us a step at 2.4 GHz).
+// FP64 lane layout: A[l % 16][l / 16], B[l / 16][l % 16], C[l / 16 + 4 j][l % 16].
+typedef double md4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ void phase_a_mfma64(const SolveArgs<double>& a, const Blk& B) {
+    using V = double2;
+    constexpr int R = 16;
+    __shared__ V Vs[2][WP][R];
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+    const int n = lane & 15, q4 = lane >> 4;
+    const int c = B.x, rbase = B.y * R;
+    const int r0 = c * a.m;
+    const int r1 = (c < a.P - 1) ? c * a.m + a.m - 1 : a.Ny;
+    const int nr = r1 - r0;
+    const int nsteps = 2 * nr - 1;
+    const int rn = rbase + n;
+    const bool rn_ok = rn < a.nrhs;
+    const int qrow = 16 * w + q4;                        // this lane's output rows: qrow + 4 j
+    const size_t ybase = (size_t)(rn_ok ? rn : 0) * a.Ny * WP + qrow;
+    bool tm[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        bool on = false;
+        for (int k = 0; k < 8; ++k) on = on || (a.tcol[k] == qrow + 4 * j);
+        tm[j] = on;
+    }
+    auto row_of = [&](int k) {
+        k = k < nsteps ? k : nsteps - 1;
+        return k < nr ? r0 + k : r1 - 2 - (k - nr);
+    };
+    auto g_ptr = [&](int k) { return fslot(a, row_of(k), 0) + (size_t)q4 * WP + 16 * w + n; };
+    V greg[2][16];
+#pragma unroll
+    for (int d = 0; d < 2; ++d) {
+        const V* G = g_ptr(d);
+#pragma unroll
+        for (int s = 0; s < 16; ++s) greg[d][s] = G[4 * s * WP];
+    }
+    // right-hand-side values of the lane's four rows (clamped, branch-free loads)
+    V rv[4], ta, tb;
+    auto load_rhs = [&](int l) {
+        const bool tr = rn_ok && a.io.q_t >= 0;
+        const size_t pt = tr ? (size_t)rn * a.Ny + l : 0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int q = qrow + 4 * j;
+            const bool in = rn_ok && q < a.W && q >= a.io.src_lo && q < a.io.src_hi;
+            const size_t ps = in ? (size_t)rn * a.io.src_rs + (size_t)l * a.io.src_ls + (q + a.io.src_off) : 0;
+            const V v = a.io.src[ps];
+            rv[j] = cmk<V>(in ? v.x : 0.0, in ? v.y : 0.0);
+        }
+        const V va = a.io.trA[pt], vb = a.io.trB[pt];
+        ta = cmk<V>(tr ? va.x : 0.0, tr ? va.y : 0.0);
+        tb = cmk<V>(tr ? vb.x : 0.0, tr ? vb.y : 0.0);
+    };
+    V z[4], zn[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) { z[j] = cmk<V>(0.0, 0.0); zn[j] = z[j]; }
+    V cnext = a.cy[r0], bnext = a.by[r0];
+    load_rhs(r0);
+
+    auto mfma_block = [&](V (&g)[16], const V (*Vb)[R], V (&out)[4], int knext) {
+        const V* Gn = g_ptr(knext);
+        md4 cr = {0.0, 0.0, 0.0, 0.0}, ci = cr;
+#pragma unroll
+        for (int s = 0; s < 16; ++s) {
+            const V gs = g[s], v = Vb[4 * s + q4][n];
+            cr = __builtin_amdgcn_mfma_f64_16x16x4f64(gs.x, v.x, cr, 0, 0, 0);
+            ci = __builtin_amdgcn_mfma_f64_16x16x4f64(gs.x, v.y, ci, 0, 0, 0);
+            cr = __builtin_amdgcn_mfma_f64_16x16x4f64(-gs.y, v.y, cr, 0, 0, 0);
+            ci = __builtin_amdgcn_mfma_f64_16x16x4f64(gs.y, v.x, ci, 0, 0, 0);
+            g[s] = Gn[4 * s * WP];
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) out[j] = cmk<V>(cr[j], ci[j]);
+    };
+    // ---- forward row l = r0 + k:  z_l = G_l (r_l - c_l z_{l-1})
+    auto fwd_step = [&](int k, int j) {
+        const int buf = k & 1, l = r0 + k;
+        const V cl = cmk<V>(k > 0 ? cnext.x : 0.0, k > 0 ? cnext.y : 0.0);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            V v = rv[u];
+            if (tr_col(a.io, qrow + 4 * u)) {
+                v.x += a.io.coef * (tb.x - ta.x);
+                v.y += a.io.coef * (tb.y - ta.y);
+            }
+            Vs[buf][qrow + 4 * u][n] = csub(v, cmul(cl, z[u]));
+        }
+        const int ln = l + 1 < r1 ? l + 1 : l;
+        cnext = a.cy[ln];
+        load_rhs(ln);
+        __syncthreads();
+        V acc[4];
+        mfma_block(greg[j], Vs[buf], acc, k + 2);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            z[u] = cmk<V>(rn_ok ? acc[u].x : 0.0, rn_ok ? acc[u].y : 0.0);
+            if (rn_ok) a.Yw[ybase + (size_t)l * WP + 4 * u] = acc[u];
+        }
+    };
+    // ---- backward row l = r1 - 2 - (k - nr):  y_l = z_l - b_l G_l y_{l+1}
+    auto bwd_step = [&](int k, int j) {
+        const int buf = k & 1, l = r1 - 2 - (k - nr);
+        V zl[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) zl[u] = zn[u];
+        const V bl = bnext;
+        const int lb = l - 1 >= r0 ? l - 1 : l;
+        bnext = a.by[lb];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) zn[u] = a.Yw[ybase + (size_t)lb * WP + 4 * u];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) Vs[buf][qrow + 4 * u][n] = z[u];
+        __syncthreads();
+        V acc[4];
+        mfma_block(greg[j], Vs[buf], acc, k + 2);
+        const bool store_y = !a.io.targets_only || l == r0;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const V y = csub(zl[u], cmul(bl, acc[u]));
+            z[u] = cmk<V>(rn_ok ? y.x : 0.0, rn_ok ? y.y : 0.0);
+            if (rn_ok && (store_y || tm[u])) a.Yw[ybase + (size_t)l * WP + 4 * u] = y;
+        }
+    };
+    int k = 0;
+    for (; k + 2 <= nr; k += 2) { fwd_step(k, 0); fwd_step(k + 1, 1); }
+    if (k < nr) fwd_step(k, 0);
+    if (nr < 2) return;
+    bnext = a.by[r1 - 2];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) zn[u] = a.Yw[ybase + (size_t)(r1 - 2) * WP + 4 * u];
+    // the first backward step uses ring slot nr % 2
+    auto bwd_loop = [&](auto off_tag) {
+        constexpr int OFF = decltype(off_tag)::value;
+        int kb = nr;
+        for (; kb + 2 <= nsteps; kb += 2) { bwd_step(kb, OFF); bwd_step(kb + 1, OFF ^ 1); }
+        if (kb < nsteps) bwd_step(kb, OFF);
+    };
+    if (nr & 1) bwd_loop(std::integral_constant<int, 1>{});
+    else bwd_loop(std::integral_constant<int, 0>{});
+}
+__global__ void __launch_bounds__(NT) k_phase_a_mfma64(SolveArgs<double> a) { phase_a_mfma64(a, own_blk()); }
 
 // ---------------------------------------------------------------- phase B0
 // a_c = G'_c r^_c for every separator (grid: separators x rhs groups), stored at row s_c.
@@ -1413,13 +1546,22 @@ __global__ void __launch_bounds__(NT) k_phase_c_targets_mfma_multi(MultiArgs<flo
 template <typename T> struct Depth { static constexpr int D = 2; };
 template <> struct Depth<float> { static constexpr int D = 4; };
 
+// R = 4: panels of at most 4 right-hand sides, one workgroup per chunk takes all of them
 template <typename T, int R>
-void launch_phase_a(const SolveArgs<T>& a, int RG, hipStream_t st) {
-    hipLaunchKernelGGL((k_phase_a<T, R>), dim3(a.P, RG), dim3(NT), 0, st, a);
+void launch_phase_a(const SolveArgs<T>& a, int, hipStream_t st) {
+    const dim3 g(a.P), b(NT);
+    if (a.nrhs == 1) hipLaunchKernelGGL((k_phase_a_few<T, 1>), g, b, 0, st, a);
+    else if (a.nrhs == 2) hipLaunchKernelGGL((k_phase_a_few<T, 2>), g, b, 0, st, a);
+    else hipLaunchKernelGGL((k_phase_a_few<T, 4>), g, b, 0, st, a);
 }
 template <>
 void launch_phase_a<float, 16>(const SolveArgs<float>& a, int RG, hipStream_t st) {
     hipLaunchKernelGGL(k_phase_a_mfma<2>, dim3(a.P, RG), dim3(NT), 0, st, a);
+}
+
+template <>
+void launch_phase_a<double, 16>(const SolveArgs<double>& a, int RG, hipStream_t st) {
+    hipLaunchKernelGGL(k_phase_a_mfma64, dim3(a.P, RG), dim3(NT), 0, st, a);
 }
 
 template <typename T, int R>
