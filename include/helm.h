@@ -169,8 +169,8 @@ helm_status helm_factor(helm_t H);
 /*
  * Autotuner of the strip solver's y-partition (2-D): for each candidate number of rows
  * per chunk, refactor and time `reps` applications of the operator one GMRES iteration
- * applies (Algorithm 3 on the reduced columns of `rhs` in REDUCED mode, A P on `rhs` in
- * FULL mode) with HIP events on the handle's stream; the handle is left factored with
+ * applies (Algorithm 3 on the reduced columns of `rhs` and P on `rhs` in REDUCED mode, A P
+ * on `rhs` in FULL mode) with HIP events on the handle's stream; the handle is left factored with
  * the fastest candidate.  The chunk size changes only the order of the substitutions
  * (the strip inverse is the same in exact arithmetic), so any candidate is correct.
  *   rhs     device, nrhs * N_y * N_x complex128 (padded grid): the panel to time on

@@ -27,6 +27,9 @@ struct GJShared {
 // A block whose 1-norm condition estimate ||S||_1 ||S^-1||_1 exceeds this is numerically
 // singular in FP64 (its inverse has no correct digit): the factorisation reports it
 constexpr double GJ_COND_MAX = 1e13;
+// The dense operators of the reduced form (kernels_reduced.hip) are built only from blocks
+// below this: above it the block substitutions, which never form them, stay in use
+constexpr double RED_COND_MAX = 1e9;
 
 // sum over the 64 lanes of a wavefront (butterfly, every lane gets the sum)
 __device__ inline double wave_sum(double v) {
@@ -61,9 +64,9 @@ __device__ inline double readlane_f64(double v, int lane) {
 // Inverse of the leading W x W block of the matrix in M (zero elsewhere), written column-major
 // with leading dimension WP to dst (zero outside the leading block); ends with a barrier so
 // that dst can be read back by the workgroup.  Sets bit 1 of err when a pivot is zero or not
-// finite, bit 2 when the 1-norm condition estimate exceeds GJ_COND_MAX.
+// finite, bit 2 when the 1-norm condition estimate exceeds cond_max.
 __device__ inline void gj_invert_store(double2 (&M)[16], int W, GJShared& sh, double2* __restrict__ dst,
-                                float2* __restrict__ dst32, int* err) {
+                                float2* __restrict__ dst32, int* err, double cond_max = GJ_COND_MAX) {
     const int i = threadIdx.x & (WP - 1), g = threadIdx.x >> 6;
     bool used = i >= W;
     int my_step = i;                               // rows beyond W keep their position
@@ -147,7 +150,7 @@ __device__ inline void gj_invert_store(double2 (&M)[16], int W, GJShared& sh, do
     if (threadIdx.x == 0) {
         double a = 0.0, b = 0.0;
         for (int q = 0; q < 4; ++q) { a = fmax(a, sh.nrm[0][q]); b = fmax(b, sh.nrm[1][q]); }
-        if (!(a * b <= GJ_COND_MAX)) atomicOr(err, 2);
+        if (!(a * b <= cond_max)) atomicOr(err, 2);
     }
 }
 

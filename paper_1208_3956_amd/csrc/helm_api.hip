@@ -66,6 +66,12 @@ struct Work {
     double2* y = nullptr;
     double2* red = nullptr;
     double2* apin = nullptr;    // fixed input of the captured reduced operator
+    // dense reduced operators: the sweeps' input panels of every strip, a strip's separator
+    // right-hand sides and solutions (operand order; sized for rnrhs right-hand sides of
+    // plan generation rgen)
+    void *rp = nullptr, *rrh = nullptr, *rxs = nullptr;
+    int rnrhs = 0;
+    long rgen = -1;
     double2* basis_old = nullptr;   // the previous cycle's basis, kept through a restart
     int mcap_old = 0;
 };
@@ -143,6 +149,13 @@ struct helm_problem {
     double2* F64 = nullptr;     // FP64 factor (the complex64 path's factorisation workspace)
     double2* Fs64 = nullptr;    // FP64 propagators (idem)
     int fac_m = 0;              // rows per chunk the factor buffers were laid out for
+    // dense strip operators of the reduced form (kernels_reduced.hip): in use when red.kappa > 0
+    helm::RedPlan red;
+    void *red_T = nullptr, *red_R = nullptr, *red_S = nullptr;
+    void* red_ws = nullptr;     // build workspace
+    size_t red_ws_bytes = 0;
+    long red_gen = 0;           // generation of the plan and its buffers
+    int red_m = 0;              // rows per fine chunk they were laid out for
     int factor_path = 0;        // 3-D: 1 = complex64 blocked Gauss-Jordan, 0 = FP64 inverses
     // strips with identical operators share one factorisation: fidx[s] is the factor slot
     // of strip s; the factor kernels run on the slots' representative strips (tf, gf: the
@@ -395,7 +408,7 @@ helm_status upload(helm_t H, void** dptr, const void* src, size_t bytes) {
 void free_work(Work& w) {
     void* ps[] = {w.Yw, w.V, w.G, w.PF, w.Psi, w.Wf, w.Hf, w.Vw, w.Gw, w.Ww, w.Ut, w.R, w.Tup, w.Tdn, w.basis,
                   w.w, w.h1, w.h2, w.nrm, w.partial, w.npartial, w.y, w.red, w.apin, w.basis_old,
-                  w.Yw2, w.Yw3, w.PsiC, w.Rob, w.RobR};
+                  w.Yw2, w.Yw3, w.PsiC, w.Rob, w.RobR, w.rp, w.rrh, w.rxs};
     for (void* p : ps) dfree(p);
     w = Work();
 }
@@ -673,6 +686,88 @@ helm_status sweep_down(helm_t H, int nrhs, double2* dst, bool full) {
     return HELM_OK;
 }
 
+// Panels of the dense reduced operators for nrhs right-hand sides.  Rows beyond a chunk's
+// last and the separator slots outside the strip are never written: they must read as zero.
+helm_status ensure_red_ws(helm_t H, int nrhs) {
+    Work& w = H->wk;
+    const auto& p = H->red;
+    const int G = (nrhs + 15) / 16;
+    if (!p.kappa || (w.rp && w.rnrhs >= nrhs && w.rgen == H->red_gen)) return HELM_OK;
+    dfree(w.rp); dfree(w.rrh); dfree(w.rxs);
+    w.rp = w.rrh = w.rxs = nullptr;
+    w.rnrhs = 0;
+    H->ws_epoch += 1;
+    const size_t esz = H->prec == HELM_C128 ? sizeof(double2) : sizeof(float2);
+    const size_t pb = (size_t)H->g.J * G * p.P * 3 * p.Mp * 16 * esz;
+    const size_t xb = (size_t)G * (p.ns + 2) * WP * 16 * esz;
+    CHK(dmalloc(H, &w.rp, pb));
+    CHK(dmalloc(H, &w.rrh, (size_t)G * p.ns * WP * 16 * esz));
+    CHK(dmalloc(H, &w.rxs, xb));
+    HIPCHK(hipMemsetAsync(w.rp, 0, pb, H->st));
+    HIPCHK(hipMemsetAsync(w.rxs, 0, xb, H->st));
+    w.rnrhs = nrhs;
+    w.rgen = H->red_gen;
+    return HELM_OK;
+}
+
+// A reduced sweep with the dense strip operators: up (psi -> Vw), strips 1 .. J - 1, or down
+// (Gw -> Ww), strips J - 2 .. 0.  The outputs land where the block substitutions put them.
+template <typename T>
+helm_status red_sweep(helm_t H, int nrhs, bool up, const double2* psi) {
+    using V = helm::cplx<T>;
+    const auto& g = H->g;
+    const auto& p = H->red;
+    Work& w = H->wk;
+    const int wrow = (g.J - 1) * helm::IWIN, G = (nrhs + 15) / 16;
+    const size_t strip = (size_t)G * p.P * 3 * p.Mp * 16;
+    V* panels = static_cast<V*>(w.rp);
+    helm::RedIn<T> in;
+    in.p = panels;
+    in.M = p.M; in.Mp = p.Mp; in.P = p.P; in.Ny = g.Ny; in.nrhs = nrhs; in.G = G;
+    if (up) { in.src = psi; in.ls = 2 * (g.J - 1); in.cs = 2; in.s0 = 1; in.s1 = g.J; in.sfirst = 1; }
+    else { in.src = w.Gw; in.ls = wrow; in.cs = helm::IWIN; in.c0 = 1; in.s0 = 0; in.s1 = g.J - 1; in.sfirst = g.J - 2; }
+    HIPCHK(TIMED(H, helm::K_OTHER, helm::launch_red_inputs<T>(in, H->st)));
+    helm::RedArgs<T> a;
+    a.rh = static_cast<V*>(w.rrh);
+    a.xs = static_cast<V*>(w.rxs);
+    a.dst = up ? w.Vw : w.Ww;
+    a.dst_rs = g.Nrow() * wrow;
+    a.dst_ls = wrow;
+    a.M = p.M; a.Mp = p.Mp; a.P = p.P; a.ns = p.ns; a.Ny = g.Ny; a.nrhs = nrhs; a.G = G;
+    for (int k = 0; k < g.J - 1; ++k) {
+        const int s = up ? 1 + k : g.J - 2 - k;
+        const bool last = k == g.J - 2;
+        // columns beta_s, beta_s + 1 | beta_{s+1} - 2, beta_{s+1} - 1 (up),
+        // beta_{s+1} - 1, beta_{s+1} | beta_s + 1, beta_s + 2 (down) in the interfaces' windows
+        const int left = (s - 1) * helm::IWIN, right = s * helm::IWIN;
+        if (up) { a.oat[0] = left + 2; a.oat[1] = left + 3; a.oat[2] = right; a.oat[3] = right + 1; }
+        else { a.oat[0] = right + 1; a.oat[1] = right + 2; a.oat[2] = left + 3; a.oat[3] = left + 4; }
+        a.nout = 0;
+        for (int o = 0; o < 5; ++o)
+            if (!last || o < 2) a.omap[a.nout++] = o;
+        a.p = panels + s * strip;
+        a.pn = last ? nullptr : panels + (up ? s + 1 : s - 1) * strip;
+        const size_t fs = H->fidx[s];
+        const V* Tm = static_cast<const V*>(H->red_T) + (fs * 2 + (up ? 0 : 1)) * p.tsz;
+        const V* Rm = static_cast<const V*>(H->red_R) + (fs * 2 + (up ? 0 : 1)) * p.rsz;
+        const V* Sm = static_cast<const V*>(H->red_S) + fs * p.ssz;
+        HIPCHK(TIMED(H, helm::K_OTHER, helm::launch_red_strip<T>(a, Tm, Rm, Sm, H->st)));
+    }
+    return HELM_OK;
+}
+
+// the two reduced sweeps, in the form the handle holds
+helm_status reduced_up(helm_t H, int nrhs, const double2* psi) {
+    if (!H->red.kappa) return sweep_up(H, nrhs, nullptr, 1, false, psi);
+    CHK(ensure_red_ws(H, nrhs));
+    return H->prec == HELM_C128 ? red_sweep<double>(H, nrhs, true, psi) : red_sweep<float>(H, nrhs, true, psi);
+}
+helm_status reduced_down(helm_t H, int nrhs) {
+    if (!H->red.kappa) return sweep_down(H, nrhs, H->wk.Ww, false);
+    CHK(ensure_red_ws(H, nrhs));
+    return H->prec == HELM_C128 ? red_sweep<double>(H, nrhs, false, nullptr) : red_sweep<float>(H, nrhs, false, nullptr);
+}
+
 // out = P f = v + w  (full form, Sec. 2.1)
 helm_status apply_P_full(helm_t H, int nrhs, const double2* f, double2* out) {
     CHK(ensure_sweep_ws(H, nrhs));
@@ -694,9 +789,9 @@ helm_status apply_AP_reduced(helm_t H, int nrhs, const double2* psi, double2* ou
     Work& w = H->wk;
     if (g.J < 2) return HELM_OK;
     // v^(1) = 0 (Algorithm 3 starts at j = 2): strip 1 never writes its window columns
-    CHK(sweep_up(H, nrhs, nullptr, 1, false, psi));
+    CHK(reduced_up(H, nrhs, psi));
     HIPCHK(TIMED(H, helm::K_STENCIL, helm::launch_stencil_win(0, H->t, g, nrhs, w.Vw, psi, w.Gw, nullptr, H->st)));
-    CHK(sweep_down(H, nrhs, w.Ww, false));
+    CHK(reduced_down(H, nrhs));
     // h = g - A w on the reduced columns; output psi - h
     HIPCHK(TIMED(H, helm::K_STENCIL, helm::launch_stencil_win(1, H->t, g, nrhs, w.Ww, psi, w.Gw, out, H->st)));
     return HELM_OK;
@@ -718,7 +813,7 @@ helm_status restart_rhs_reduced(helm_t H, int nrhs, const double2* r, double2* b
     // window of v holding zeros where the first strip would write
     HIPCHK(TIMED(H, helm::K_OTHER, helm::launch_clear_win_cols(w.Vw, (long)nrhs * g.Nrow(),
                                                                (long)(g.J - 1) * helm::IWIN, 0, helm::IWIN, H->st)));
-    CHK(sweep_down(H, nrhs, w.Ww, false));
+    CHK(reduced_down(H, nrhs));
     HIPCHK(TIMED(H, helm::K_STENCIL, helm::launch_stencil_win(4, H->t, g, nrhs, w.Ww, nullptr, w.Gw, b, H->st)));
     return HELM_OK;
 }
@@ -977,6 +1072,49 @@ helm_status apply_P_any(helm_t H, int nrhs, const double2* f, double2* out) {
     return H->sweep == 1 ? apply_Pc_full(H, nrhs, f, out) : apply_P_full(H, nrhs, f, out);
 }
 
+// The dense strip operators of the reduced sweeps, after the factorisation (2-D, reduced form
+// of the double sweep).  Their memory and the build's workspace are kept for the handle's
+// life; where they would take more than half of what is free the sweeps keep the block
+// substitutions.
+helm_status build_reduced(helm_t H) {
+    const auto& g = H->g;
+    if (g.dim != 2 || H->mode != HELM_REDUCED || H->sweep != 0 || H->trans != 0 || g.J < 2) return HELM_OK;
+    helm::RedPlan p = helm::red_plan(H->ch, g.Ny);
+    const helm::RedBuildSize bs = helm::red_build_size(p, H->ch, H->nfac);
+    const size_t esz = H->prec == HELM_C128 ? sizeof(double2) : sizeof(float2);
+    const size_t nf = (size_t)H->nfac;
+    if (!p.kappa) { H->red = p; return HELM_OK; }
+    if (H->red_m != H->ch.m) {
+        dfree(H->red_T); dfree(H->red_R); dfree(H->red_S); dfree(H->red_ws);
+        H->red_T = H->red_R = H->red_S = H->red_ws = nullptr;
+        H->red_m = 0;
+        H->red = helm::RedPlan();
+        H->red_gen += 1;
+        size_t freeb = 0, totb = 0;
+        HIPCHK(hipMemGetInfo(&freeb, &totb));
+        if (nf * (2 * p.tsz + 2 * p.rsz + p.ssz) * esz + bs.bytes > freeb / 2) return HELM_OK;
+        CHK(dmalloc(H, &H->red_T, nf * 2 * p.tsz * esz));
+        CHK(dmalloc(H, &H->red_R, nf * 2 * p.rsz * esz));
+        CHK(dmalloc(H, &H->red_S, nf * p.ssz * esz));
+        CHK(dmalloc(H, &H->red_ws, bs.bytes));
+        H->red_m = H->ch.m;
+    }
+    if (!H->red_T) return HELM_OK;
+    H->red = p;
+    double2* ws = static_cast<double2*>(H->red_ws);
+    if (H->prec == HELM_C128)
+        HIPCHK(TIMED(H, helm::K_OTHER,
+                     helm::launch_red_build<double>(p, bs, H->tf, H->gf, H->ch, H->nfac, H->F64, ws, H->d_err + 1,
+                                                    static_cast<double2*>(H->red_T), static_cast<double2*>(H->red_R),
+                                                    static_cast<double2*>(H->red_S), H->st)));
+    else
+        HIPCHK(TIMED(H, helm::K_OTHER,
+                     helm::launch_red_build<float>(p, bs, H->tf, H->gf, H->ch, H->nfac, H->F64, ws, H->d_err + 1,
+                                                   static_cast<float2*>(H->red_T), static_cast<float2*>(H->red_R),
+                                                   static_cast<float2*>(H->red_S), H->st)));
+    return HELM_OK;
+}
+
 // Algorithm 2: u~ on D~^(j) from independent strip solves with f on D~^(j).
 helm_status reduced_setup(helm_t H, int nrhs, const double2* f, double2* ut) {
     const auto& g = H->g;
@@ -1116,6 +1254,7 @@ helm_status apply_op(helm_t H, int nrhs, const double2* x, double2* out) {
     // graph replay: the captured launches read the fixed buffer apin and write `out`
     Work& w = H->wk;
     CHK(ensure_sweep_ws(H, nrhs));
+    CHK(ensure_red_ws(H, nrhs));
     const size_t bytes = (size_t)nrhs * H->g.Nrow() * 2 * (H->g.J - 1) * sizeof(double2);
     if (x != w.apin) HIPCHK(hipMemcpyAsync(w.apin, x, bytes, hipMemcpyDeviceToDevice, H->st));
     int slot = -1, lru = 0;
@@ -1956,7 +2095,7 @@ helm_status helm_setup(const double* c, double omega, double h, const helm_opts*
         if ((st = upload(H, (void**)&t.az, az.data(), az.size() * sizeof(double2))) != HELM_OK) return st;
         if ((st = upload(H, (void**)&t.azh, azh.data(), azh.size() * sizeof(double2))) != HELM_OK) return st;
     }
-    if ((st = dmalloc(H, &H->d_err, sizeof(int))) != HELM_OK) return st;
+    if ((st = dmalloc(H, &H->d_err, 2 * sizeof(int))) != HELM_OK) return st;
     H->err.clear();
     *out = H;
     return HELM_OK;
@@ -2166,7 +2305,7 @@ helm_status helm_factor(helm_t H) {
     }
     double2* F64 = H->F64;
     float2* F32 = single ? static_cast<float2*>(H->F) : nullptr;
-    HIPCHK(hipMemsetAsync(H->d_err, 0, sizeof(int), H->st));
+    HIPCHK(hipMemsetAsync(H->d_err, 0, 2 * sizeof(int), H->st));
     // one factorisation per distinct strip operator (factor slots 0 .. nfac - 1)
     const auto& gf = H->gf;
     HIPCHK(TIMED(H, helm::K_FACTOR_CHUNKS, helm::launch_factor_chunks(H->tf, gf, H->ch, F64, F32, H->d_err, H->st)));
@@ -2186,11 +2325,15 @@ helm_status helm_factor(helm_t H) {
     else
         HIPCHK(TIMED(H, helm::K_OTHER, helm::launch_extract_targets<double2>(F64, static_cast<double2*>(H->Fc),
                                                                             H->tf.tcol, gf, H->ch, H->st)));
-    int herr = 0;
-    HIPCHK(hipMemcpyAsync(&herr, H->d_err, sizeof(int), hipMemcpyDeviceToHost, H->st));
+    CHK(build_reduced(H));
+    int herr[2] = {0, 0};
+    HIPCHK(hipMemcpyAsync(herr, H->d_err, 2 * sizeof(int), hipMemcpyDeviceToHost, H->st));
     HIPCHK(hipStreamSynchronize(H->st));
-    if (herr & 1) return fail(H, HELM_ESINGULAR, "zero or non-finite pivot in a strip factorisation");
-    if (herr & 2)
+    // the strip operators stay with the block substitutions where a joined block is too
+    // ill-conditioned to be applied as an explicit inverse
+    if (herr[1]) H->red.kappa = 0;
+    if (herr[0] & 1) return fail(H, HELM_ESINGULAR, "zero or non-finite pivot in a strip factorisation");
+    if (herr[0] & 2)
         return fail(H, HELM_ESINGULAR, "a strip block is numerically singular (1-norm condition estimate "
                                        "above 1e13): the strip operator is at or near a resonance");
     H->factored = true;
@@ -2234,7 +2377,9 @@ helm_status helm_autotune(helm_t H, int nrhs, const void* rhs, const int* cand, 
     const int nred = 2 * (g.J - 1);
     CHK(ensure_sweep_ws(H, nrhs));
     // the operator one GMRES iteration applies: Algorithm 3 on the right-hand sides'
-    // reduced columns (REDUCED), or P followed by A (FULL)
+    // reduced columns (REDUCED), or P followed by A (FULL).  The dense strip operators of the
+    // reduced form hardly depend on the chunk size, so REDUCED times one application of P
+    // as well (Algorithms 2 and 4 and the restarts run it, and there the chunk size counts)
     const size_t in_bytes = reduced ? (size_t)nrhs * g.Nrow() * nred * sizeof(double2) : field_bytes(H, nrhs);
     double2 *xin = nullptr, *xout = nullptr;
     struct Bufs { double2** a; double2** b; ~Bufs() { dfree(*a); dfree(*b); } } bufs{&xin, &xout};
@@ -2250,7 +2395,10 @@ helm_status helm_autotune(helm_t H, int nrhs, const void* rhs, const int* cand, 
     HIPCHK(hipEventCreate(&e1));
     struct Ev { hipEvent_t a, b; ~Ev() { (void)hipEventDestroy(a); (void)hipEventDestroy(b); } } ev{e0, e1};
     auto apply = [&]() -> helm_status {
-        if (reduced) return apply_AP_red(H, nrhs, xin, xout);
+        if (reduced) {
+            CHK(apply_AP_red(H, nrhs, xin, xout));
+            return apply_P_any(H, nrhs, static_cast<const double2*>(rhs), H->wk.PF);
+        }
         CHK(apply_P_any(H, nrhs, xin, H->wk.PF));
         HIPCHK(helm::launch_apply_A(H->t, g, nrhs, H->wk.PF, nullptr, xout, H->st));
         return HELM_OK;
@@ -2604,6 +2752,10 @@ void helm_destroy(helm_t H) {
     dfree(H->Fc);
     dfree(H->Fa);
     dfree(H->Fw);
+    dfree(H->red_T);
+    dfree(H->red_R);
+    dfree(H->red_S);
+    dfree(H->red_ws);
     dfree(H->d_err);
     for (void* p : H->owned) dfree(p);
     delete H;

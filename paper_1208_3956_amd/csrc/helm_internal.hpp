@@ -303,6 +303,55 @@ hipError_t launch_factor3_plane_f32(const Fac3Args& a, int l, float2* F, size_t 
 template <typename T>
 hipError_t launch_strip_solve3(const Solve3Args<T>& a, hipStream_t st, KTimer* kt);
 
+// ---- strip operators of the reduced form as dense blocks (kernels_reduced.hip)
+// Coarse chunks of M rows (kappa fine ones of n / kappa rows joined, n = M unless one chunk
+// holds the whole strip), Mp = M rounded up to 16, ns separators; element counts of the
+// three operators per factor slot (and direction: Tm, Rm).  kappa = 0: not built.
+struct RedPlan {
+    int kappa = 0, levels = 0, M = 0, Mp = 0, P = 0, ns = 0, n = 0;
+    size_t tsz = 0, rsz = 0, ssz = 0;
+};
+RedPlan red_plan(const Chunks& ch, int Ny);
+// build workspace: element counts per slot of its parts, slots per batch, bytes in all
+struct RedBuildSize {
+    size_t K = 0, X = 0, g = 0, z = 0, bytes = 0;
+    int batch = 1;
+};
+RedBuildSize red_build_size(const RedPlan& p, const Chunks& ch, int nfac);
+// one strip solve of G groups of 16 right-hand sides; panels in operand order
+template <typename T>
+struct RedArgs {
+    const cplx<T>* A = nullptr;   // set by the launcher
+    const cplx<T>* p = nullptr;   // inputs of the strip [G][P][3][Mp][16]
+    cplx<T>* pn = nullptr;        // inputs of the next strip of the sweep (entry 0 is written)
+    cplx<T>* rh = nullptr;        // [G][64 ns][16]
+    cplx<T>* xs = nullptr;        // [G][64 (ns + 2)][16], first and last 64 rows zero
+    double2* dst = nullptr; long dst_rs = 0; int dst_ls = 0;
+    int oat[4] = {0, 0, 0, 0};    // output o goes to dst[r dst_rs + row dst_ls + oat[o]]
+    int omap[5] = {0, 0, 0, 0, 0}, nout = 0;   // active outputs (4: the next strip's entry 0)
+    int M = 0, Mp = 0, P = 0, ns = 0, Ny = 0, nrhs = 0, G = 0;
+};
+template <typename T>
+hipError_t launch_red_strip(const RedArgs<T>& a, const cplx<T>* Tm, const cplx<T>* Rm, const cplx<T>* Sm,
+                            hipStream_t st);
+// inputs of the strips s0 .. s1 - 1: entries 1, 2 of row l, right-hand side r from
+// src[(r Ny + l) ls + (s - s0) cs + c0 + {0, 1}]; entry 0 of strip sfirst cleared
+template <typename T>
+struct RedIn {
+    cplx<T>* p = nullptr;
+    const double2* src = nullptr;
+    int ls = 0, cs = 0, c0 = 0, s0 = 0, s1 = 0, sfirst = 0;
+    int M = 0, Mp = 0, P = 0, Ny = 0, nrhs = 0, G = 0;
+};
+template <typename T>
+hipError_t launch_red_inputs(const RedIn<T>& a, hipStream_t st);
+// operators of nfac factor slots from the FP64 factor (t: the slots' tables); err: bits as in
+// launch_factor_chunks, for blocks too ill-conditioned to be used in this form
+template <typename T>
+hipError_t launch_red_build(const RedPlan& p, const RedBuildSize& sz, const DevTables& t, const Geom& g,
+                            const Chunks& ch, int nfac, const double2* F64, double2* ws, int* err, cplx<T>* Tm,
+                            cplx<T>* Rm, cplx<T>* Sm, hipStream_t st);
+
 // ---- host core (helm_api.hip) shared with other entry points
 // bytes of strip-solver workspace one strip solve of nrhs right-hand sides needs
 size_t strip_workspace_bytes(helm_t H, int nrhs);
