@@ -69,9 +69,15 @@ struct Work {
     // dense reduced operators: the sweeps' input panels of every strip, a strip's separator
     // right-hand sides and solutions (operand order; sized for rnrhs right-hand sides of
     // plan generation rgen)
-    void *rp = nullptr, *rrh = nullptr, *rxs = nullptr;
+    void *rp = nullptr, *rpd = nullptr, *rrh = nullptr, *rxs = nullptr;   // rp upward, rpd downward
     int rnrhs = 0;
     long rgen = -1;
+    // batches of strips: strip-solver workspace of bstrips strips, and the window field of
+    // the strips' solutions of a full field (the base of an upward sweep)
+    void* Yb = nullptr;
+    double2* Vb = nullptr;
+    int bstrips = 0, bnrhs = 0, bP = 0;
+    size_t bcap = 0;            // strips x right-hand sides Yb holds
     double2* basis_old = nullptr;   // the previous cycle's basis, kept through a restart
     int mcap_old = 0;
 };
@@ -94,8 +100,8 @@ struct EventTimer : helm::KTimer {
         }
         return pool[idx];
     }
-    void begin(int c, hipStream_t st) override {
-        counts[c] += 1;
+    void begin(int c, hipStream_t st, int n = 1) override {
+        counts[c] += n;
         if (used >= kMax || !(mask & (1u << c))) { pending_cls = -1; return; }
         hipEvent_t e = get(2 * used);
         if (!e || !get(2 * used + 1)) { pending_cls = -1; return; }
@@ -156,6 +162,9 @@ struct helm_problem {
     size_t red_ws_bytes = 0;
     long red_gen = 0;           // generation of the plan and its buffers
     int red_m = 0;              // rows per fine chunk they were laid out for
+    // per-strip tables of the batches of strips, J entries each: Algorithm 2, the base of an
+    // upward sweep, the field of P
+    helm::StripIO* sio[3] = {};
     int factor_path = 0;        // 3-D: 1 = complex64 blocked Gauss-Jordan, 0 = FP64 inverses
     // strips with identical operators share one factorisation: fidx[s] is the factor slot
     // of strip s; the factor kernels run on the slots' representative strips (tf, gf: the
@@ -408,7 +417,7 @@ helm_status upload(helm_t H, void** dptr, const void* src, size_t bytes) {
 void free_work(Work& w) {
     void* ps[] = {w.Yw, w.V, w.G, w.PF, w.Psi, w.Wf, w.Hf, w.Vw, w.Gw, w.Ww, w.Ut, w.R, w.Tup, w.Tdn, w.basis,
                   w.w, w.h1, w.h2, w.nrm, w.partial, w.npartial, w.y, w.red, w.apin, w.basis_old,
-                  w.Yw2, w.Yw3, w.PsiC, w.Rob, w.RobR, w.rp, w.rrh, w.rxs};
+                  w.Yw2, w.Yw3, w.PsiC, w.Rob, w.RobR, w.rp, w.rpd, w.rrh, w.rxs, w.Yb, w.Vb};
     for (void* p : ps) dfree(p);
     w = Work();
 }
@@ -693,14 +702,16 @@ helm_status ensure_red_ws(helm_t H, int nrhs) {
     const auto& p = H->red;
     const int G = (nrhs + 15) / 16;
     if (!p.kappa || (w.rp && w.rnrhs >= nrhs && w.rgen == H->red_gen)) return HELM_OK;
-    dfree(w.rp); dfree(w.rrh); dfree(w.rxs);
-    w.rp = w.rrh = w.rxs = nullptr;
+    dfree(w.rp); dfree(w.rpd); dfree(w.rrh); dfree(w.rxs);
+    w.rp = w.rpd = w.rrh = w.rxs = nullptr;
     w.rnrhs = 0;
     H->ws_epoch += 1;
     const size_t esz = H->prec == HELM_C128 ? sizeof(double2) : sizeof(float2);
     const size_t pb = (size_t)H->g.J * G * p.P * 3 * p.Mp * 16 * esz;
     const size_t xb = (size_t)G * (p.ns + 2) * WP * 16 * esz;
     CHK(dmalloc(H, &w.rp, pb));
+    CHK(dmalloc(H, &w.rpd, pb));
+    HIPCHK(hipMemsetAsync(w.rpd, 0, pb, H->st));
     CHK(dmalloc(H, &w.rrh, (size_t)G * p.ns * WP * 16 * esz));
     CHK(dmalloc(H, &w.rxs, xb));
     HIPCHK(hipMemsetAsync(w.rp, 0, pb, H->st));
@@ -710,22 +721,30 @@ helm_status ensure_red_ws(helm_t H, int nrhs) {
     return HELM_OK;
 }
 
-// A reduced sweep with the dense strip operators: up (psi -> Vw), strips 1 .. J - 1, or down
-// (Gw -> Ww), strips J - 2 .. 0.  The outputs land where the block substitutions put them.
+// A reduced sweep with the dense strip operators: up (psi, null for zero, -> Vw), strips
+// 1 .. J - 1, or down (Gw -> Ww), strips J - 2 .. 0.  The outputs land where the block
+// substitutions put them.  base: the upward sweep's strips also have sources of their own,
+// whose solutions (strip_base) are in Vb and the traces Tup.
 template <typename T>
-helm_status red_sweep(helm_t H, int nrhs, bool up, const double2* psi) {
+helm_status red_sweep(helm_t H, int nrhs, bool up, const double2* psi, bool base) {
     using V = helm::cplx<T>;
     const auto& g = H->g;
     const auto& p = H->red;
     Work& w = H->wk;
     const int wrow = (g.J - 1) * helm::IWIN, G = (nrhs + 15) / 16;
     const size_t strip = (size_t)G * p.P * 3 * p.Mp * 16;
-    V* panels = static_cast<V*>(w.rp);
+    const double tc = -1.0 / (g.h * g.h);               // -2 delta d_x v, delta = 1/(2h)
+    V* panels = static_cast<V*>(up ? w.rp : w.rpd);
     helm::RedIn<T> in;
     in.p = panels;
     in.M = p.M; in.Mp = p.Mp; in.P = p.P; in.Ny = g.Ny; in.nrhs = nrhs; in.G = G;
     if (up) { in.src = psi; in.ls = 2 * (g.J - 1); in.cs = 2; in.s0 = 1; in.s1 = g.J; in.sfirst = 1; }
     else { in.src = w.Gw; in.ls = wrow; in.cs = helm::IWIN; in.c0 = 1; in.s0 = 0; in.s1 = g.J - 1; in.sfirst = g.J - 2; }
+    if (base) {
+        in.trA = trace(w.Tup, 0, 0, nrhs, g.Nrow());
+        in.trB = trace(w.Tup, 0, 1, nrhs, g.Nrow());
+        in.tc = tc;
+    }
     HIPCHK(TIMED(H, helm::K_OTHER, helm::launch_red_inputs<T>(in, H->st)));
     helm::RedArgs<T> a;
     a.rh = static_cast<V*>(w.rrh);
@@ -733,6 +752,8 @@ helm_status red_sweep(helm_t H, int nrhs, bool up, const double2* psi) {
     a.dst = up ? w.Vw : w.Ww;
     a.dst_rs = g.Nrow() * wrow;
     a.dst_ls = wrow;
+    a.base = base ? w.Vb : nullptr;
+    a.tc = tc;
     a.M = p.M; a.Mp = p.Mp; a.P = p.P; a.ns = p.ns; a.Ny = g.Ny; a.nrhs = nrhs; a.G = G;
     for (int k = 0; k < g.J - 1; ++k) {
         const int s = up ? 1 + k : g.J - 2 - k;
@@ -747,6 +768,10 @@ helm_status red_sweep(helm_t H, int nrhs, bool up, const double2* psi) {
             if (!last || o < 2) a.omap[a.nout++] = o;
         a.p = panels + s * strip;
         a.pn = last ? nullptr : panels + (up ? s + 1 : s - 1) * strip;
+        if (base) {
+            a.trA = trace(w.Tup, s, 0, nrhs, g.Nrow());
+            a.trB = trace(w.Tup, s, 1, nrhs, g.Nrow());
+        }
         const size_t fs = H->fidx[s];
         const V* Tm = static_cast<const V*>(H->red_T) + (fs * 2 + (up ? 0 : 1)) * p.tsz;
         const V* Rm = static_cast<const V*>(H->red_R) + (fs * 2 + (up ? 0 : 1)) * p.rsz;
@@ -760,12 +785,131 @@ helm_status red_sweep(helm_t H, int nrhs, bool up, const double2* psi) {
 helm_status reduced_up(helm_t H, int nrhs, const double2* psi) {
     if (!H->red.kappa) return sweep_up(H, nrhs, nullptr, 1, false, psi);
     CHK(ensure_red_ws(H, nrhs));
-    return H->prec == HELM_C128 ? red_sweep<double>(H, nrhs, true, psi) : red_sweep<float>(H, nrhs, true, psi);
+    return H->prec == HELM_C128 ? red_sweep<double>(H, nrhs, true, psi, false)
+                                : red_sweep<float>(H, nrhs, true, psi, false);
 }
 helm_status reduced_down(helm_t H, int nrhs) {
     if (!H->red.kappa) return sweep_down(H, nrhs, H->wk.Ww, false);
     CHK(ensure_red_ws(H, nrhs));
-    return H->prec == HELM_C128 ? red_sweep<double>(H, nrhs, false, nullptr) : red_sweep<float>(H, nrhs, false, nullptr);
+    return H->prec == HELM_C128 ? red_sweep<double>(H, nrhs, false, nullptr, false)
+                                : red_sweep<float>(H, nrhs, false, nullptr, false);
+}
+
+// ---------------------------------------------------------------- batches of strips
+// With the dense operators the sweeps' chain (transmission sources, interface columns) costs
+// three small products per strip, and whole strip solves are needed only for fields: those
+// of Algorithm 2, of the sources a full field puts into every strip, and of the field P
+// returns.  None of them depends on another strip, so they run in batches, one launch per
+// phase for many strips, instead of one after another: a single strip leaves most of the
+// chip idle when it has few right-hand sides, and the field of P takes J strip solves, both
+// sweeps' sources added, instead of 2 J - 1.  (Handles that fuse their strip solves with
+// other problems' keep the sequential sweeps.)
+bool batched(helm_t H) { return H->red.kappa > 0 && !H->batch_fuse; }
+
+helm_status ensure_batch_ws(helm_t H, int nrhs) {
+    Work& w = H->wk;
+    const auto& g = H->g;
+    if (w.Yb && w.bnrhs == nrhs && w.bP == H->ch.P) return HELM_OK;
+    const size_t esz = H->prec == HELM_C128 ? sizeof(double2) : sizeof(float2);
+    const size_t per = (size_t)nrhs * g.Ny * WP * esz;
+    // four workgroups of phase A per CU, or 2 GB
+    const int wgs = H->ch.P * ((nrhs + 15) / 16);
+    int nb = std::min(g.J, std::max(1, (1024 + wgs - 1) / wgs));
+    nb = (int)std::max<size_t>(1, std::min<size_t>(nb, ((size_t)2 << 30) / per));
+    const int nsub = (g.J + nb - 1) / nb;
+    nb = (g.J + nsub - 1) / nsub;
+    if (!w.Yb || w.bcap < (size_t)nb * nrhs) {
+        dfree(w.Yb);
+        w.Yb = nullptr;
+        w.bnrhs = 0;
+        CHK(dmalloc(H, &w.Yb, per * nb));
+        w.bcap = (size_t)nb * nrhs;
+    }
+    if (!w.Vb) {
+        const size_t wb = (size_t)w.nrhs * g.Nrow() * (g.J - 1) * helm::IWIN * sizeof(double2);
+        CHK(dmalloc(H, &w.Vb, wb));
+        HIPCHK(hipMemsetAsync(w.Vb, 0, wb, H->st));
+    }
+    w.bstrips = nb;
+    w.bnrhs = nrhs;
+    w.bP = H->ch.P;
+    return HELM_OK;
+}
+
+// One batch of strip solves over all strips: kind 0 Algorithm 2 (f -> dst), 1 the base of an
+// upward sweep (f -> Vb, Tup), 2 the field of P (f and the sweeps' inputs -> dst)
+template <typename T>
+helm_status strip_batch(helm_t H, int nrhs, int kind, const double2* f, double2* dst) {
+    using V = helm::cplx<T>;
+    CHK(ensure_red_ws(H, nrhs));
+    CHK(ensure_batch_ws(H, nrhs));
+    const auto& g = H->g;
+    const auto& p = H->red;
+    Work& w = H->wk;
+    helm::BatchRhs<T> rhs;
+    rhs.Yw = static_cast<V*>(w.Yb);
+    rhs.f = f;
+    rhs.nrhs = nrhs; rhs.Ny = g.Ny; rhs.Nx = g.Nx;
+    if (kind == 2) {
+        rhs.pu = static_cast<const V*>(w.rp);
+        rhs.pd = static_cast<const V*>(w.rpd);
+        rhs.M = p.M; rhs.Mp = p.Mp; rhs.P = p.P; rhs.G = (nrhs + 15) / 16;
+    }
+    helm::IOSpec io;
+    io.dst = kind == 1 ? w.Vb : dst;
+    io.dst_ls = kind == 1 ? (g.J - 1) * helm::IWIN : g.Nx;
+    io.dst_rs = g.Nrow() * io.dst_ls;
+    io.targets_only = kind == 1 ? 1 : 0;
+    for (int s0 = 0; s0 < g.J; s0 += w.bstrips) {
+        const int ns = std::min(w.bstrips, g.J - s0);
+        rhs.s0 = s0;
+        rhs.io = H->sio[kind] + s0;
+        if (kind == 1) {
+            io.tro0 = trace(w.Tup, s0, 0, nrhs, g.Nrow());
+            io.tro1 = trace(w.Tup, s0, 1, nrhs, g.Nrow());
+        }
+        HIPCHK(helm::launch_strip_batch<T>(H->t, g, H->ch, rhs, ns, static_cast<const V*>(H->F),
+                                           static_cast<const V*>(H->Fc), static_cast<const V*>(H->Fs),
+                                           static_cast<const V*>(H->Fa), static_cast<const V*>(H->Fw), io, H->st,
+                                           H->kt()));
+    }
+    return HELM_OK;
+}
+helm_status strip_batch_any(helm_t H, int nrhs, int kind, const double2* f, double2* dst) {
+    return H->prec == HELM_C128 ? strip_batch<double>(H, nrhs, kind, f, dst)
+                                : strip_batch<float>(H, nrhs, kind, f, dst);
+}
+
+// Both sweeps on the interface windows for the source f + psi: v -> Vw, g -> Gw, w -> Ww, and
+// every strip's inputs in the panels.  base: f is a full field whose strip solutions are in
+// Vb, Tup (it holds psi too if psi is given); else f is psi on the reduced columns.
+helm_status sweeps_inputs(helm_t H, int nrhs, const double2* f, const double2* psi, bool base) {
+    const auto& g = H->g;
+    Work& w = H->wk;
+    const long nrows = (long)nrhs * g.Nrow(), wrow = (long)(g.J - 1) * helm::IWIN;
+    CHK(ensure_red_ws(H, nrhs));
+    if (H->prec == HELM_C128) CHK(red_sweep<double>(H, nrhs, true, psi, base));
+    else CHK(red_sweep<float>(H, nrhs, true, psi, base));
+    if (base) {
+        // the first strip takes no part in the sweep: its window columns are its base's
+        HIPCHK(TIMED(H, helm::K_OTHER, helm::launch_copy_win_cols(w.Vb, w.Vw, nrows, wrow, 0, 2, H->st)));
+        HIPCHK(TIMED(H, helm::K_STENCIL, helm::launch_stencil_win(3, H->t, g, nrhs, w.Vw, f, w.Gw, nullptr, H->st)));
+        // Algorithm 3's upward sweeps rely on zeros there
+        HIPCHK(TIMED(H, helm::K_OTHER, helm::launch_clear_win_cols(w.Vw, nrows, wrow, 0, 2, H->st)));
+    } else {
+        HIPCHK(TIMED(H, helm::K_STENCIL, helm::launch_stencil_win(0, H->t, g, nrhs, w.Vw, psi, w.Gw, nullptr, H->st)));
+    }
+    return reduced_down(H, nrhs);
+}
+
+// out = P (f): the strips' fields from the inputs of both sweeps; column beta_s is the sum of
+// v (strip s) and w (strip s - 1), every other column one strip's
+helm_status field_of_P(helm_t H, int nrhs, const double2* f, double2* out) {
+    Work& w = H->wk;
+    CHK(strip_batch_any(H, nrhs, 2, f, out));
+    HIPCHK(TIMED(H, helm::K_OTHER, helm::launch_iface_sum(w.Vw, w.Ww, H->t.bw, H->g.J, (long)nrhs * H->g.Nrow(),
+                                                          H->g.Nx, out, H->st)));
+    return HELM_OK;
 }
 
 // out = P f = v + w  (full form, Sec. 2.1)
@@ -773,6 +917,11 @@ helm_status apply_P_full(helm_t H, int nrhs, const double2* f, double2* out) {
     CHK(ensure_sweep_ws(H, nrhs));
     const auto& g = H->g;
     Work& w = H->wk;
+    if (batched(H)) {
+        CHK(strip_batch_any(H, nrhs, 1, f, nullptr));
+        CHK(sweeps_inputs(H, nrhs, f, nullptr, true));
+        return field_of_P(H, nrhs, f, out);
+    }
     CHK(sweep_up(H, nrhs, f, 0, true, nullptr));
     HIPCHK(TIMED(H, helm::K_STENCIL, helm::launch_apply_A_pairs(H->t, g, nrhs, H->t.rcols, g.J - 1, w.V, f, w.G, H->st)));
     HIPCHK(hipMemcpyAsync(out, w.V, field_bytes(H, nrhs), hipMemcpyDeviceToDevice, H->st));
@@ -807,6 +956,12 @@ helm_status restart_rhs_reduced(helm_t H, int nrhs, const double2* r, double2* b
     const auto& g = H->g;
     Work& w = H->wk;
     if (g.J < 2) return HELM_OK;
+    if (batched(H)) {
+        CHK(strip_batch_any(H, nrhs, 1, r, nullptr));
+        CHK(sweeps_inputs(H, nrhs, r, nullptr, true));
+        HIPCHK(TIMED(H, helm::K_STENCIL, helm::launch_stencil_win(4, H->t, g, nrhs, w.Ww, nullptr, w.Gw, b, H->st)));
+        return HELM_OK;
+    }
     CHK(sweep_up(H, nrhs, r, 0, false, nullptr));
     HIPCHK(TIMED(H, helm::K_STENCIL, helm::launch_stencil_win(3, H->t, g, nrhs, w.Vw, r, w.Gw, nullptr, H->st)));
     // Algorithm 3's upward sweeps start at the second strip and rely on the first interface's
@@ -1072,13 +1227,15 @@ helm_status apply_P_any(helm_t H, int nrhs, const double2* f, double2* out) {
     return H->sweep == 1 ? apply_Pc_full(H, nrhs, f, out) : apply_P_full(H, nrhs, f, out);
 }
 
-// The dense strip operators of the reduced sweeps, after the factorisation (2-D, reduced form
-// of the double sweep).  Their memory and the build's workspace are kept for the handle's
+// The dense strip operators of the reduced sweeps, after the factorisation (2-D, double sweep
+// with PML transmission).  Their memory and the build's workspace are kept for the handle's
 // life; where they would take more than half of what is free the sweeps keep the block
 // substitutions.
 helm_status build_reduced(helm_t H) {
     const auto& g = H->g;
-    if (g.dim != 2 || H->mode != HELM_REDUCED || H->sweep != 0 || H->trans != 0 || g.J < 2) return HELM_OK;
+    // a full-form handle uses them for the sweeps of P (see batched)
+    if (g.dim != 2 || (H->mode != HELM_REDUCED && H->batch_fuse) || H->sweep != 0 || H->trans != 0 || g.J < 2)
+        return HELM_OK;
     helm::RedPlan p = helm::red_plan(H->ch, g.Ny);
     const helm::RedBuildSize bs = helm::red_build_size(p, H->ch, H->nfac);
     const size_t esz = H->prec == HELM_C128 ? sizeof(double2) : sizeof(float2);
@@ -1118,6 +1275,7 @@ helm_status build_reduced(helm_t H) {
 // Algorithm 2: u~ on D~^(j) from independent strip solves with f on D~^(j).
 helm_status reduced_setup(helm_t H, int nrhs, const double2* f, double2* ut) {
     const auto& g = H->g;
+    if (batched(H)) return strip_batch_any(H, nrhs, 0, f, ut);
     for (int s = 0; s < g.J; ++s) {
         const auto& S = g.strips[s];
         helm::IOSpec io = field_io(H, s);
@@ -1716,13 +1874,24 @@ helm_status solve_impl(helm_t H, int nrhs, const double2* f, double2* u, double 
         if (reduced && cycle > 0 && merge) {
             // Algorithm 4 with the restart's P r folded in: u += P (r + psi)
             HIPCHK(TIMED(H, helm::K_OTHER, helm::launch_scatter_cols(w.w, red_cols(H), nred, nrhs, g.Nrow(), g.Nx, w.R, H->st, true)));
-            CHK(apply_P_any(H, nrhs, w.R, w.Hf));
+            if (batched(H)) {
+                // the strip solutions of r are still in Vb, Tup
+                CHK(sweeps_inputs(H, nrhs, w.R, w.w, true));
+                CHK(field_of_P(H, nrhs, w.R, w.Hf));
+            } else {
+                CHK(apply_P_any(H, nrhs, w.R, w.Hf));
+            }
             HIPCHK(TIMED(H, helm::K_OTHER, helm::launch_sum3(u, w.Hf, nullptr, u, nrhs * nfull, H->st)));
         } else if (reduced) {
             // Algorithm 4: u += P psi + u~   (psi scattered onto the reduced columns of Psi,
             // which is zero everywhere else: nothing but this scatter writes it)
             HIPCHK(TIMED(H, helm::K_OTHER, helm::launch_scatter_cols(w.w, red_cols(H), nred, nrhs, g.Nrow(), g.Nx, w.Psi, H->st)));
-            CHK(apply_P_any(H, nrhs, w.Psi, w.Hf));
+            if (batched(H)) {
+                CHK(sweeps_inputs(H, nrhs, w.Psi, w.w, false));
+                CHK(field_of_P(H, nrhs, w.Psi, w.Hf));
+            } else {
+                CHK(apply_P_any(H, nrhs, w.Psi, w.Hf));
+            }
             HIPCHK(TIMED(H, helm::K_OTHER, helm::launch_sum3(cycle == 0 ? nullptr : u, w.Hf, w.Ut, u, nrhs * nfull, H->st)));
         } else {
             CHK(apply_P_any(H, nrhs, w.w, w.Hf));
@@ -2091,6 +2260,41 @@ helm_status helm_setup(const double* c, double omega, double h, const helm_opts*
     for (int u = 0; u < H->nfac; ++u) H->gf.strips.push_back(g.strips[urep[u]]);
     if ((st = upload(H, (void**)&t.bw, bw.data(), bw.size() * sizeof(int))) != HELM_OK) return st;
     if ((st = upload(H, (void**)&t.k2w, k2w.data(), k2w.size() * sizeof(double))) != HELM_OK) return st;
+    if (dim == 2 && !robin) {
+        // batches of strips: Algorithm 2 writes D~^(j); the base of an upward sweep the window
+        // columns and traces sweep_up writes; the field of P every core column but beta_s
+        std::vector<helm::StripIO> x[3];
+        for (int kind = 0; kind < 3; ++kind) {
+            x[kind].resize(J);
+            for (int s = 0; s < J; ++s) {
+                const auto& S = g.strips[s];
+                helm::StripIO& y = x[kind][s];
+                y.fs = H->fidx[s]; y.W = S.W; y.a = S.a;
+                y.s_lo = (kind == 0 ? S.kdn_lo : S.core_lo) - S.a;
+                y.s_hi = (kind == 0 ? S.kdn_hi : S.core_hi) - S.a;
+                y.o_off[0] = y.o_off[1] = S.a;
+                if (kind == 0) {
+                    y.o_lo[0] = y.s_lo; y.o_hi[0] = y.s_hi;
+                } else if (kind == 1) {
+                    if (s > 0) {
+                        y.o_lo[0] = S.core_lo - S.a; y.o_hi[0] = y.o_lo[0] + 2;
+                        win_off(g, s, s, S.core_lo, 2, &y.o_off[0]);
+                    }
+                    if (s < J - 1) {
+                        y.o_lo[1] = S.core_hi - 2 - S.a; y.o_hi[1] = S.core_hi - S.a;
+                        win_off(g, s, s + 1, S.core_hi - 2, 2, &y.o_off[1]);
+                        y.qo0 = g.beta[s + 1] - 1 - S.a;
+                        y.qo1 = g.beta[s + 1] - S.a;
+                    }
+                } else {
+                    y.o_lo[0] = S.core_lo + (s > 0 ? 1 : 0) - S.a; y.o_hi[0] = S.core_hi - S.a;
+                    if (s > 0) y.eL = g.beta[s] - S.a;
+                    if (s < J - 1) y.eR = g.beta[s + 1] - S.a;
+                }
+            }
+            if ((st = upload(H, (void**)&H->sio[kind], x[kind].data(), J * sizeof(helm::StripIO))) != HELM_OK) return st;
+        }
+    }
     if (dim == 3) {
         if ((st = upload(H, (void**)&t.az, az.data(), az.size() * sizeof(double2))) != HELM_OK) return st;
         if ((st = upload(H, (void**)&t.azh, azh.data(), azh.size() * sizeof(double2))) != HELM_OK) return st;

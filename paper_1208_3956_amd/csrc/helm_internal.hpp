@@ -98,6 +98,8 @@ struct IOSpec {
     // every requested column is one of the strip's 8 compact target columns: phase C may
     // compute only those (reduced form)
     int targets_only = 0;
+    // the right-hand side is already in the strip solver's workspace rows (batches of strips)
+    int pre = 0;
     // columns receiving the transmission source: 2 (q_t and q_t + 1, the PML transmission)
     // or 1 (q_t only, a Robin side)
     int t_cols = 2;
@@ -132,6 +134,34 @@ hipError_t launch_strip_solve_multi(const StripJob* jobs, int n, hipStream_t st,
 __host__ __device__ inline bool tr_col(const IOSpec& io, int q) {
     return io.q_t >= 0 && (q == io.q_t || (io.t_cols == 2 && q == io.q_t + 1));
 }
+
+// What differs from strip to strip in a batch of strip solves: factor slot, width and first
+// column; strip-local source columns; output ranges and offsets, trace columns (as in IOSpec);
+// strip-local columns beta_s (eL) and beta_{s+1} (eR) of its interfaces, -1: none.
+struct StripIO {
+    int fs = 0, W = 0, a = 0, s_lo = 0, s_hi = 0;
+    int o_lo[2] = {0, 0}, o_hi[2] = {0, 0}, o_off[2] = {0, 0};
+    int qo0 = -1, qo1 = -1, eL = -1, eR = -1;
+};
+
+// position of (k, n) in an operand-order tile of 16 columns (see kernels_reduced.hip)
+template <typename T>
+__host__ __device__ inline size_t red_pos(int k, int n) {
+    const int lane = 16 * (k & 3) + n;
+    if (sizeof(T) == 4) return ((size_t)(k >> 3) * 64 + lane) * 2 + ((k >> 2) & 1);
+    return ((size_t)(k >> 3) * 2 + ((k >> 2) & 1)) * 64 + lane;
+}
+
+// Right-hand sides of the strips s0 .. s0 + ns - 1 of a batch: the source columns of field f
+// and, unless pu is null, the sweeps' inputs (pu upward, pd downward, see RedArgs)
+template <typename T>
+struct BatchRhs {
+    cplx<T>* Yw = nullptr;        // [strip][nrhs][Ny][WP]
+    const StripIO* io = nullptr;  // device, strip s0 first
+    const double2* f = nullptr;
+    const cplx<T>* pu = nullptr; const cplx<T>* pd = nullptr;
+    int s0 = 0, nrhs = 0, Ny = 0, Nx = 0, M = 1, Mp = 0, P = 0, G = 0;
+};
 
 // Device tables of one problem.
 struct DevTables {
@@ -191,7 +221,8 @@ struct Solve3Args {
 
 // Optional per-launch event timing: launchers call begin/end around each kernel.
 struct KTimer {
-    virtual void begin(int cls, hipStream_t st) = 0;
+    // n: strips the launch serves (a batch of strips counts once per strip)
+    virtual void begin(int cls, hipStream_t st, int n = 1) = 0;
     virtual void end(int cls, hipStream_t st) = 0;
     virtual ~KTimer() = default;
 };
@@ -233,6 +264,13 @@ hipError_t launch_strip_solve(const DevTables& t, const Geom& g, const Chunks& c
                               const cplx<T>* F, const cplx<T>* Fc, const cplx<T>* Fs, const cplx<T>* Fa,
                               const cplx<T>* Fw, cplx<T>* Yw, int nrhs, const IOSpec& io, hipStream_t st,
                               KTimer* kt = nullptr);
+
+// ns strips from rhs.s0 on, each with its own right-hand side (rhs) and outputs (rhs.io; io:
+// destination, strides and traces, targets_only): one launch per phase for all of them
+template <typename T>
+hipError_t launch_strip_batch(const DevTables& t, const Geom& g, const Chunks& ch, const BatchRhs<T>& rhs,
+                              int ns, const cplx<T>* F, const cplx<T>* Fc, const cplx<T>* Fs, const cplx<T>* Fa,
+                              const cplx<T>* Fw, const IOSpec& io, hipStream_t st, KTimer* kt);
 
 hipError_t launch_apply_A(const DevTables& t, const Geom& g, int nrhs, const double2* u,
                           const double2* f, double2* out, hipStream_t st);
@@ -328,6 +366,9 @@ struct RedArgs {
     cplx<T>* xs = nullptr;        // [G][64 (ns + 2)][16], first and last 64 rows zero
     double2* dst = nullptr; long dst_rs = 0; int dst_ls = 0;
     int oat[4] = {0, 0, 0, 0};    // output o goes to dst[r dst_rs + row dst_ls + oat[o]]
+    // added to the outputs (null: nothing): base to dst, laid out alike; tc (trB - trA) of the
+    // strip's own traces [rhs][row] to the next strip's entry 0
+    const double2* base = nullptr; const double2* trA = nullptr; const double2* trB = nullptr; double tc = 0;
     int omap[5] = {0, 0, 0, 0, 0}, nout = 0;   // active outputs (4: the next strip's entry 0)
     int M = 0, Mp = 0, P = 0, ns = 0, Ny = 0, nrhs = 0, G = 0;
 };
@@ -335,16 +376,23 @@ template <typename T>
 hipError_t launch_red_strip(const RedArgs<T>& a, const cplx<T>* Tm, const cplx<T>* Rm, const cplx<T>* Sm,
                             hipStream_t st);
 // inputs of the strips s0 .. s1 - 1: entries 1, 2 of row l, right-hand side r from
-// src[(r Ny + l) ls + (s - s0) cs + c0 + {0, 1}]; entry 0 of strip sfirst cleared
+// src[(r Ny + l) ls + (s - s0) cs + c0 + {0, 1}] (null: zero); entry 0 of strip sfirst is
+// tc (trB - trA) of the traces [rhs][row] (null: zero)
 template <typename T>
 struct RedIn {
     cplx<T>* p = nullptr;
     const double2* src = nullptr;
+    const double2* trA = nullptr; const double2* trB = nullptr; double tc = 0;
     int ls = 0, cs = 0, c0 = 0, s0 = 0, s1 = 0, sfirst = 0;
     int M = 0, Mp = 0, P = 0, Ny = 0, nrhs = 0, G = 0;
 };
 template <typename T>
 hipError_t launch_red_inputs(const RedIn<T>& a, hipStream_t st);
+// columns of window fields: dst[row wrow + c] = src[row wrow + c], c = c0 .. c0 + n - 1
+hipError_t launch_copy_win_cols(const double2* src, double2* dst, long nrows, long wrow, int c0, int n, hipStream_t st);
+// out[row Nx + beta_s] = v + w of interface s (the middle column of its windows), s = 1 .. J - 1
+hipError_t launch_iface_sum(const double2* vw, const double2* ww, const int* bw, int J, long nrows, int Nx,
+                            double2* out, hipStream_t st);
 // operators of nfac factor slots from the FP64 factor (t: the slots' tables); err: bits as in
 // launch_factor_chunks, for blocks too ill-conditioned to be used in this form
 template <typename T>

@@ -36,14 +36,6 @@ constexpr int NT = 256;
 constexpr int TI = 6;            // target columns / input columns per row of the build's blocks
 typedef float mf4 __attribute__((ext_vector_type(4)));
 
-// position of (k, n) in an operand-order tile
-template <typename T>
-__host__ __device__ inline size_t opos(int k, int n) {
-    const int lane = 16 * (k & 3) + n;
-    if (std::is_same<T, float>::value) return ((size_t)(k >> 3) * 64 + lane) * 2 + ((k >> 2) & 1);
-    return ((size_t)(k >> 3) * 2 + ((k >> 2) & 1)) * 64 + lane;
-}
-
 // ---------------------------------------------------------------- products of a strip solve
 template <typename T> struct Mfma;
 template <> struct Mfma<float> {
@@ -171,14 +163,25 @@ __global__ void __launch_bounds__(NT) k_red_mul(RedArgs<T> a) {
         if (g >= a.G) break;
         const V v = cadd(cadd(red[0][u][row][rn], red[1][u][row][rn]), cadd(red[2][u][row][rn], red[3][u][row][rn]));
         if (MODE == 0) {
-            a.rh[(size_t)g * a.ns * WP * 16 + opos<T>(tile * 16 + row, rn)] = v;
+            a.rh[(size_t)g * a.ns * WP * 16 + red_pos<T>(tile * 16 + row, rn)] = v;
         } else if (MODE == 1) {
-            a.xs[(size_t)g * (a.ns + 2) * WP * 16 + opos<T>(WP + tile * 16 + row, rn)] = v;
+            a.xs[(size_t)g * (a.ns + 2) * WP * 16 + red_pos<T>(WP + tile * 16 + row, rn)] = v;
         } else {
             const int lr = 16 * lg + row, l = c * a.M + lr, r = 16 * g + rn;
             if (lr < a.M && l < a.Ny) {
-                if (o == 4) a.pn[((size_t)g * a.P + c) * KP * 16 + opos<T>(lr, rn)] = v;
-                else if (r < a.nrhs) a.dst[(size_t)r * a.dst_rs + (size_t)l * a.dst_ls + a.oat[o]] = ccast<double2>(v);
+                double2 x = ccast<double2>(v);
+                if (o == 4) {
+                    if (a.trA && r < a.nrhs) {
+                        const double2 ta = a.trA[(size_t)r * a.Ny + l], tb = a.trB[(size_t)r * a.Ny + l];
+                        x.x += a.tc * (tb.x - ta.x);
+                        x.y += a.tc * (tb.y - ta.y);
+                    }
+                    a.pn[((size_t)g * a.P + c) * KP * 16 + red_pos<T>(lr, rn)] = ccast<V>(x);
+                } else if (r < a.nrhs) {
+                    const size_t at = (size_t)r * a.dst_rs + (size_t)l * a.dst_ls + a.oat[o];
+                    if (a.base) x = cadd(x, a.base[at]);
+                    a.dst[at] = x;
+                }
             }
         }
     }
@@ -201,12 +204,40 @@ __global__ void __launch_bounds__(NT) k_red_inputs(RedIn<T> a) {
     for (int h = 0; h < 2; ++h) {
         const int lr = 8 * i8 + 4 * h + q4, l = c * a.M + lr;
         if (lr >= a.M || l >= a.Ny) continue;
-        const double2* src = a.src + ((size_t)r * a.Ny + l) * a.ls + (size_t)(s - a.s0) * a.cs + a.c0;
-        const double2 x = src[0], y = src[1];
-        p[opos<T>(a.Mp + lr, n)] = ccast<V>(x);
-        p[opos<T>(2 * a.Mp + lr, n)] = ccast<V>(y);
-        if (s == a.sfirst) p[opos<T>(lr, n)] = cmk<V>(0, 0);
+        double2 x = cmk<double2>(0.0, 0.0), y = x;
+        if (a.src) {
+            const double2* src = a.src + ((size_t)r * a.Ny + l) * a.ls + (size_t)(s - a.s0) * a.cs + a.c0;
+            x = src[0];
+            y = src[1];
+        }
+        p[red_pos<T>(a.Mp + lr, n)] = ccast<V>(x);
+        p[red_pos<T>(2 * a.Mp + lr, n)] = ccast<V>(y);
+        if (s == a.sfirst) {
+            double2 t = cmk<double2>(0.0, 0.0);
+            if (a.trA) {
+                const double2 ta = a.trA[(size_t)r * a.Ny + l], tb = a.trB[(size_t)r * a.Ny + l];
+                t = cmk<double2>(a.tc * (tb.x - ta.x), a.tc * (tb.y - ta.y));
+            }
+            p[red_pos<T>(lr, n)] = ccast<V>(t);
+        }
     }
+}
+
+__global__ void k_copy_win_cols(const double2* __restrict__ src, double2* __restrict__ dst, long nrows, long wrow, int c0,
+                                int n) {
+    const long p = blockIdx.x * (long)blockDim.x + threadIdx.x;
+    if (p >= nrows * n) return;
+    const size_t at = (size_t)(p / n) * wrow + c0 + p % n;
+    dst[at] = src[at];
+}
+__global__ void k_iface_sum(const double2* __restrict__ vw, const double2* __restrict__ ww, const int* __restrict__ bw, int NI,
+                            long nrows, int Nx, double2* __restrict__ out) {
+    const long p = blockIdx.x * (long)blockDim.x + threadIdx.x;
+    if (p >= nrows * NI) return;
+    const long row = p / NI;
+    const int j = (int)(p % NI);
+    const size_t at = (size_t)row * NI * IWIN + j * IWIN + 2;
+    out[(size_t)row * Nx + bw[j] + 2] = cadd(vw[at], ww[at]);
 }
 
 // ---------------------------------------------------------------- build (FP64)
@@ -573,7 +604,7 @@ __global__ void __launch_bounds__(NT) k_red_sinv(RedBuild b, int kappa, int ns, 
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const int row = row0 + 4 * j, tile = 4 * rc + (row >> 4);
-            Sm[(size_t)tile * 16 * 64 * ns + opos<T>(kcol, row & 15)] = ccast<V>(y[j]);
+            Sm[(size_t)tile * 16 * 64 * ns + red_pos<T>(kcol, row & 15)] = ccast<V>(y[j]);
         }
     };
     if ((nsf % kappa) == 0) emit(nsf - 1);
@@ -664,7 +695,7 @@ __global__ void __launch_bounds__(NT) k_red_pack_t(RedBuild b, const double2* __
                 }
             }
         }
-        Tm[opos<T>(k, row)] = ccast<V>(v);
+        Tm[red_pos<T>(k, row)] = ccast<V>(v);
     }
 }
 
@@ -696,7 +727,7 @@ __global__ void __launch_bounds__(NT) k_red_pack_r(RedBuild b, const double2* __
                 v = cmul(cmk<double2>(-f.x, -f.y), x);
             }
         }
-        Rm[opos<T>(k, row)] = ccast<V>(v);
+        Rm[red_pos<T>(k, row)] = ccast<V>(v);
     }
 }
 
@@ -733,6 +764,18 @@ hipError_t launch_red_inputs(const RedIn<T>& a, hipStream_t st) {
 }
 template hipError_t launch_red_inputs<float>(const RedIn<float>&, hipStream_t);
 template hipError_t launch_red_inputs<double>(const RedIn<double>&, hipStream_t);
+
+hipError_t launch_copy_win_cols(const double2* src, double2* dst, long nrows, long wrow, int c0, int n, hipStream_t st) {
+    hipLaunchKernelGGL(k_copy_win_cols, dim3((unsigned)((nrows * n + NT - 1) / NT)), dim3(NT), 0, st, src, dst, nrows, wrow,
+                       c0, n);
+    return hipGetLastError();
+}
+hipError_t launch_iface_sum(const double2* vw, const double2* ww, const int* bw, int J, long nrows, int Nx,
+                            double2* out, hipStream_t st) {
+    hipLaunchKernelGGL(k_iface_sum, dim3((unsigned)((nrows * (J - 1) + NT - 1) / NT)), dim3(NT), 0, st, vw, ww, bw, J - 1,
+                       nrows, Nx, out);
+    return hipGetLastError();
+}
 
 // ---------------------------------------------------------------- plan and build (host side)
 RedPlan red_plan(const Chunks& ch, int Ny) {

@@ -71,6 +71,45 @@ __device__ inline bool multi_blk(const MultiArgs<T>& m, int& k, Blk& b) {
     return b.y < m.ny[k] && b.z < m.nz[k];
 }
 
+// Several strips of one problem in one launch: blockIdx.z is the strip (times nz where the
+// kernel uses z blocks of its own); what differs from strip to strip comes from a table.
+template <typename T>
+struct BatchArgs {
+    SolveArgs<T> a;               // factors of slot 0, workspace of the first strip
+    const StripIO* io;            // first strip of the launch
+    const int* tcol;
+    long F_st, Fc_st, Fs_st, Fa_st, Fw_st, Yw_st;
+    long tr_st;                   // elements of one trace (two per strip)
+};
+template <typename T>
+__device__ inline SolveArgs<T> batch_strip(const BatchArgs<T>& b, int nz, Blk& B) {
+    const int k = (int)blockIdx.z / nz;
+    B = Blk{(int)blockIdx.x, (int)blockIdx.y, (int)blockIdx.z - k * nz, nz};
+    const StripIO x = b.io[k];
+    SolveArgs<T> a = b.a;
+    a.F += x.fs * b.F_st;
+    a.Fc += x.fs * b.Fc_st;
+    a.Fs += x.fs * b.Fs_st;
+    a.Fa += x.fs * b.Fa_st;
+    a.Fw += x.fs * b.Fw_st;
+    a.Yw += k * b.Yw_st;
+    a.tcol = b.tcol + 8 * k;
+    a.W = x.W;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        a.io.o_lo[i] = x.o_lo[i];
+        a.io.o_hi[i] = x.o_hi[i];
+        a.io.dst_off[i] = x.o_off[i];
+    }
+    a.io.qo0 = x.qo0;
+    a.io.qo1 = x.qo1;
+    if (a.io.tro0) {
+        a.io.tro0 += 2 * k * b.tr_st;
+        a.io.tro1 += 2 * k * b.tr_st;
+    }
+    return a;
+}
+
 template <typename T>
 __device__ inline cplx<T> gather(const IOSpec& io, int r, int l, int q, int Ny) {
     double2 v = cmk<double2>(0.0, 0.0);
@@ -186,14 +225,16 @@ __device__ inline void matvec(cplx<T> (&acc)[R / G], const cplx<T>* M, const cpl
 // then needs the result only at its own 16 columns: lane (row 16 w + lane % 16, right-hand side
 // lane / 16) adds the four partial sums, forms the next step's operand there and keeps it in a
 // part of LDS that only its wave reads.
-template <typename T, int R>
-__global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1, 1))) k_phase_a_few(SolveArgs<T> a) {
+// PRE (here and below): the right-hand side is in the workspace rows already, in T, and is
+// overwritten by the result (a lane reads a row's entries before it stores the same ones).
+template <typename T, int R, bool PRE>
+__device__ __forceinline__ void phase_a_few(const SolveArgs<T>& a, const Blk& B) {
     using V = cplx<T>;
     constexpr int D = std::is_same<T, double>::value && R > 1 ? 3 : 4;   // 3: no spills
     __shared__ V vecw[4][R][16];
     __shared__ V part[2][4][R][WP];
     const int t = threadIdx.x, i = t & (WP - 1), w = t >> 6, k0 = 16 * w;
-    const int c = blockIdx.x;
+    const int c = B.x;
     const int r0 = c * a.m;
     const int r1 = (c < a.P - 1) ? c * a.m + a.m - 1 : a.Ny;
     const int n = r1 - r0;
@@ -204,7 +245,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1, 1)))
     };
     // this lane's element of the vectors
     const int q = k0 + (i & 15), bl = i >> 4, b = bl < R ? bl : R - 1;
-    const int r = blockIdx.y * R + b;
+    const int r = B.y * R + b;
     const bool own = bl < R && r < a.nrhs;
     V* Yr = a.Yw + (size_t)(own ? r : 0) * a.Ny * WP + q;
     V breg[D][16];
@@ -218,7 +259,13 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1, 1)))
     V z = cmk<V>(0, 0);
     // loads of the next row, issued a step ahead: its right-hand side and coupling (forward),
     // z_l and coupling (backward)
-    RawRhs raw = load_raw(a.io, own ? r : a.nrhs, r0, q, a.Ny, a.nrhs, a.W);
+    RawRhs raw;
+    V pre = z;
+    auto load_rhs = [&](int l) {
+        if constexpr (PRE) pre = Yr[(size_t)l * WP];
+        else raw = load_raw(a.io, own ? r : a.nrhs, l, q, a.Ny, a.nrhs, a.W);
+    };
+    load_rhs(r0);
     double2 cn = a.cy[r0];
     V zn = z;
     // v: the step's operand (this lane's element); returns (G v) there
@@ -242,10 +289,11 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1, 1)))
     auto step = [&](int k, int j) {
         const int l = row_of(k);
         if (k < n) {
-            V v = combine<T>(a.io, raw);
+            V v = pre;
+            if constexpr (!PRE) v = combine<T>(a.io, raw);
             if (k > 0) v = csub(v, cmul(ccast<V>(cn), z));
             const int ln = l + 1 < r1 ? l + 1 : l;
-            raw = load_raw(a.io, own ? r : a.nrhs, ln, q, a.Ny, a.nrhs, a.W);
+            load_rhs(ln);
             cn = a.cy[ln];
             z = product(k, breg[j], v);
             if (own) Yr[(size_t)l * WP] = z;
@@ -268,6 +316,16 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1, 1)))
     for (int j = 0; j < D; ++j)
         if (k + j < steps) step(k + j, j);
 }
+template <typename T, int R>
+__global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1, 1))) k_phase_a_few(SolveArgs<T> a) {
+    phase_a_few<T, R, false>(a, own_blk());
+}
+template <typename T, int R>
+__global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1, 1))) k_phase_a_few_b(BatchArgs<T> b) {
+    Blk B;
+    const SolveArgs<T> a = batch_strip(b, 1, B);
+    phase_a_few<T, R, true>(a, B);
+}
 
 // ---------------------------------------------------------------- phase A, MFMA
 // complex64, 16 right-hand sides per workgroup.  The block product Z = G V (64 x 64 times
@@ -288,7 +346,7 @@ typedef float mf4 __attribute__((ext_vector_type(4)));
 // products that read its pair: the four waves of a workgroup reach their products together
 // after the barrier, and loads issued after the products kept the CU's load path busy
 // while the matrix cores idled (and the stores and right-hand-side loads queued behind).
-template <int D>
+template <int D, bool PRE = false>
 __device__ __forceinline__ void phase_a_mfma(const SolveArgs<float>& a, const Blk& B) {
     using V = float2;
     constexpr int R = 16;
@@ -332,8 +390,18 @@ __device__ __forceinline__ void phase_a_mfma(const SolveArgs<float>& a, const Bl
         }
     };
     RawRhs4 raw;
+    V pre[4];
     auto load_rhs = [&](int l) {
-        load_raw4(raw, a.io, rn, l, qrow, a.Ny, a.nrhs, a.W);
+        if constexpr (PRE) {
+            const float4* y = reinterpret_cast<const float4*>(a.Yw + ybase + (size_t)l * WP);
+            const float4 y0 = y[0], y1 = y[1];
+            pre[0] = make_float2(y0.x, y0.y);
+            pre[1] = make_float2(y0.z, y0.w);
+            pre[2] = make_float2(y1.x, y1.y);
+            pre[3] = make_float2(y1.z, y1.w);
+        } else {
+            load_raw4(raw, a.io, rn, l, qrow, a.Ny, a.nrhs, a.W);
+        }
     };
     V greg[D][16];
     V z[4], zn[4];
@@ -389,7 +457,12 @@ __device__ __forceinline__ void phase_a_mfma(const SolveArgs<float>& a, const Bl
         const V cl = make_float2(clx, cly);
         V v[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) v[u] = csub(combine4(a.io, raw, u, qrow + u), cmul(cl, z[u]));
+        for (int u = 0; u < 4; ++u) {
+            V r;
+            if constexpr (PRE) r = pre[u];
+            else r = combine4(a.io, raw, u, qrow + u);
+            v[u] = csub(r, cmul(cl, z[u]));
+        }
         // next step's small loads first (vmcnt retires in issue order); clamped, branch-free
         const int ln = l + 1 < r1 ? l + 1 : l;
         cnext = a.cy[ln];
@@ -467,6 +540,12 @@ __device__ __forceinline__ void phase_a_mfma(const SolveArgs<float>& a, const Bl
 template <int D>
 __global__ void __launch_bounds__(NT) k_phase_a_mfma(SolveArgs<float> a) { phase_a_mfma<D>(a, own_blk()); }
 template <int D>
+__global__ void __launch_bounds__(NT) k_phase_a_mfma_b(BatchArgs<float> b) {
+    Blk B;
+    const SolveArgs<float> a = batch_strip(b, 1, B);
+    phase_a_mfma<D, true>(a, B);
+}
+template <int D>
 __global__ void __launch_bounds__(NT) k_phase_a_mfma_multi(MultiArgs<float> m) {
     int k;
     Blk b;
@@ -485,6 +564,7 @@ __global__ void __launch_bounds__(NT) k_phase_a_mfma_multi(MultiArgs<float> m) {
 // FP64 lane layout: A[l % 16][l / 16], B[l / 16][l % 16], C[l / 16 + 4 j][l % 16].
 typedef double md4 __attribute__((ext_vector_type(4)));
 
+template <bool PRE>
 __device__ __forceinline__ void phase_a_mfma64(const SolveArgs<double>& a, const Blk& B) {
     using V = double2;
     constexpr int R = 16;
@@ -522,6 +602,11 @@ __device__ __forceinline__ void phase_a_mfma64(const SolveArgs<double>& a, const
     // right-hand-side values of the lane's four rows (clamped, branch-free loads)
     V rv[4], ta, tb;
     auto load_rhs = [&](int l) {
+        if constexpr (PRE) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) rv[j] = a.Yw[ybase + (size_t)l * WP + 4 * j];
+            return;
+        }
         const bool tr = rn_ok && a.io.q_t >= 0;
         const size_t pt = tr ? (size_t)rn * a.Ny + l : 0;
 #pragma unroll
@@ -564,7 +649,7 @@ __device__ __forceinline__ void phase_a_mfma64(const SolveArgs<double>& a, const
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             V v = rv[u];
-            if (tr_col(a.io, qrow + 4 * u)) {
+            if (!PRE && tr_col(a.io, qrow + 4 * u)) {
                 v.x += a.io.coef * (tb.x - ta.x);
                 v.y += a.io.coef * (tb.y - ta.y);
             }
@@ -623,17 +708,22 @@ __device__ __forceinline__ void phase_a_mfma64(const SolveArgs<double>& a, const
     if (nr & 1) bwd_loop(std::integral_constant<int, 1>{});
     else bwd_loop(std::integral_constant<int, 0>{});
 }
-__global__ void __launch_bounds__(NT) k_phase_a_mfma64(SolveArgs<double> a) { phase_a_mfma64(a, own_blk()); }
+__global__ void __launch_bounds__(NT) k_phase_a_mfma64(SolveArgs<double> a) { phase_a_mfma64<false>(a, own_blk()); }
+__global__ void __launch_bounds__(NT) k_phase_a_mfma64_b(BatchArgs<double> b) {
+    Blk B;
+    const SolveArgs<double> a = batch_strip(b, 1, B);
+    phase_a_mfma64<true>(a, B);
+}
 
 // ---------------------------------------------------------------- phase B0
 // a_c = G'_c r^_c for every separator (grid: separators x rhs groups), stored at row s_c.
 template <typename T, int R>
-__global__ void __launch_bounds__(NT) k_phase_b0(SolveArgs<T> a) {
+__device__ __forceinline__ void phase_b0(const SolveArgs<T>& a, const Blk& B) {
     using V = cplx<T>;
     constexpr int G = 4, U = R / G;
     __shared__ V vin[WP][R];
     const int t = threadIdx.x, i = t & (WP - 1), g = t >> 6;
-    const int c = blockIdx.x, rbase = blockIdx.y * R;
+    const int c = B.x, rbase = B.y * R;
     const int s = c * a.m + a.m - 1;
     const V cs = ccast<V>(a.cy[s]), bs = ccast<V>(a.by[s]);
     const V zero = cmk<V>(0, 0);
@@ -642,7 +732,8 @@ __global__ void __launch_bounds__(NT) k_phase_b0(SolveArgs<T> a) {
         const int r = rbase + g + G * u;
         V v = zero;
         if (r < a.nrhs && i < a.W) {
-            v = gather<T>(a.io, r, s, i, a.Ny);
+            if (a.io.pre) v = a.Yw[((size_t)r * a.Ny + s) * WP + i];
+            else v = gather<T>(a.io, r, s, i, a.Ny);
             v = csub(v, cmul(cs, a.Yw[((size_t)r * a.Ny + (s - 1)) * WP + i]));
             v = csub(v, cmul(bs, a.Yw[((size_t)r * a.Ny + (s + 1)) * WP + i]));
         }
@@ -660,6 +751,15 @@ __global__ void __launch_bounds__(NT) k_phase_b0(SolveArgs<T> a) {
     }
 }
 
+template <typename T, int R>
+__global__ void __launch_bounds__(NT) k_phase_b0(SolveArgs<T> a) { phase_b0<T, R>(a, own_blk()); }
+template <typename T, int R>
+__global__ void __launch_bounds__(NT) k_phase_b0_b(BatchArgs<T> b) {
+    Blk B;
+    const SolveArgs<T> a = batch_strip(b, 1, B);
+    phase_b0<T, R>(a, B);
+}
+
 // ---------------------------------------------------------------- phase B
 // One right-hand side per workgroup; the k-sum of every matvec is split over the 4 waves
 // and combined through LDS.  Forward z'_0 = a_0, z'_c = a_c - K_c z'_{c-1}; backward
@@ -674,13 +774,13 @@ constexpr int ZMAX = 64;   // separators whose z' the chain keeps in LDS
 // and the forward inputs a_c are loaded D steps ahead into a register ring (requires
 // P - 1 <= ZMAX); otherwise the next input is loaded one step ahead from global memory.
 template <typename T, int D, bool ZB>
-__global__ void __launch_bounds__(NT) k_phase_b(SolveArgs<T> a) {
+__device__ __forceinline__ void phase_b(const SolveArgs<T>& a, const Blk& B) {
     using V = cplx<T>;
     __shared__ V vec[WP];
     __shared__ V part[4][WP];
     __shared__ V zb[ZB ? ZMAX + 1 : 1][WP];     // row ZMAX: discard row for backward steps
     const int t = threadIdx.x, i = t & (WP - 1), w = t >> 6;
-    const int r = blockIdx.x;
+    const int r = B.x;
     const int ns = a.P - 1;                  // separators
     const int nf = ns - 1;                   // forward steps (c = 1..ns-1)
     const int steps = nf + (ns - 1);         // + backward steps (c = ns-2..0)
@@ -758,6 +858,15 @@ __global__ void __launch_bounds__(NT) k_phase_b(SolveArgs<T> a) {
 #pragma unroll
     for (int j = 0; j < D; ++j)
         if (k + j < steps) step(k + j, j);
+}
+
+template <typename T, int D, bool ZB>
+__global__ void __launch_bounds__(NT) k_phase_b(SolveArgs<T> a) { phase_b<T, D, ZB>(a, own_blk()); }
+template <typename T, int D, bool ZB>
+__global__ void __launch_bounds__(NT) k_phase_b_b(BatchArgs<T> b) {
+    Blk B;
+    const SolveArgs<T> a = batch_strip(b, 1, B);
+    phase_b<T, D, ZB>(a, B);
 }
 
 // ---------------------------------------------------------------- phase B, two levels
@@ -928,7 +1037,8 @@ __device__ __forceinline__ void sep_fwd_local(const SolveArgs<T>& a, const Blk& 
                 const V* Yr = a.Yw + (size_t)r * a.Ny * WP;
                 V v = cmk<V>(0, 0);
                 if (i < a.W) {
-                    v = gather<T>(a.io, r, sr, i, a.Ny);
+                    if (a.io.pre) v = Yr[(size_t)sr * WP + i];
+                    else v = gather<T>(a.io, r, sr, i, a.Ny);
                     v = csub(v, cmul(ccast<V>(a.cy[sr]), Yr[(size_t)(sr - 1) * WP + i]));
                     v = csub(v, cmul(ccast<V>(a.by[sr]), Yr[(size_t)(sr + 1) * WP + i]));
                 }
@@ -1065,13 +1175,14 @@ __device__ __forceinline__ void sep_par_mfma(const SolveArgs<float>& a, const Bl
     for (int s = 0; s < 16; ++s) gA[s] = F[(4 * s + q4) * WP];
     constexpr int NP = 16 * WP / NT;
     RawRhs raw[NP];
-    V ym[NP], yp[NP];
+    V ym[NP], yp[NP], own[NP];
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
         const int idx = threadIdx.x + p * NT, q = idx >> 6, k = idx & (WP - 1), r = rbase + q;
         const V* Yr = a.Yw + (size_t)(r < a.nrhs ? r : a.nrhs - 1) * a.Ny * WP + k;
         if (MODE == 0) {
-            raw[p] = load_raw(a.io, r, sr, k, a.Ny, a.nrhs, a.W);
+            if (a.io.pre) own[p] = Yr[(size_t)sr * WP];
+            else raw[p] = load_raw(a.io, r, sr, k, a.Ny, a.nrhs, a.W);
             ym[p] = Yr[(size_t)(sr - 1) * WP];
             yp[p] = Yr[(size_t)(sr + 1) * WP];
         } else {
@@ -1091,7 +1202,8 @@ __device__ __forceinline__ void sep_par_mfma(const SolveArgs<float>& a, const Bl
         V v = make_float2(0.f, 0.f);
         if (rbase + q < a.nrhs && k < a.W) {
             if (MODE == 0) {
-                v = combine<float>(a.io, raw[p]);
+                if (a.io.pre) v = own[p];
+                else v = combine<float>(a.io, raw[p]);
                 v = csub(v, cmul(ccast<V>(cys), ym[p]));
                 v = csub(v, cmul(ccast<V>(bys), yp[p]));
             } else {
@@ -1173,15 +1285,53 @@ __global__ void __launch_bounds__(NT) k_sep_bwd_fix_multi(MultiArgs<T> m) {
     if (multi_blk(m, k, b)) sep_bwd_fix<T, D>(m.a[k], b);
 }
 
+// the same for the strips of a batch
+template <int MODE>
+__global__ void __launch_bounds__(NT) k_sep_par_mfma_b(BatchArgs<float> b) {
+    Blk B;
+    const SolveArgs<float> a = batch_strip(b, 1, B);
+    sep_par_mfma<MODE>(a, B);
+}
+template <typename T, int D, bool SETUP = true>
+__global__ void __launch_bounds__(NT) k_sep_fwd_local_b(BatchArgs<T> b) {
+    Blk B;
+    const SolveArgs<T> a = batch_strip(b, 1, B);
+    sep_fwd_local<T, D, SETUP>(a, B);
+}
+template <typename T, int D>
+__global__ void __launch_bounds__(NT) k_sep_fwd_top_b(BatchArgs<T> b) {
+    Blk B;
+    const SolveArgs<T> a = batch_strip(b, 1, B);
+    sep_fwd_top<T, D>(a, B);
+}
+template <typename T, int D, bool FIX = true>
+__global__ void __launch_bounds__(NT) k_sep_fix_bwd_local_b(BatchArgs<T> b) {
+    Blk B;
+    const SolveArgs<T> a = batch_strip(b, 1, B);
+    sep_fix_bwd_local<T, D, FIX>(a, B);
+}
+template <typename T, int D>
+__global__ void __launch_bounds__(NT) k_sep_bwd_top_b(BatchArgs<T> b) {
+    Blk B;
+    const SolveArgs<T> a = batch_strip(b, 1, B);
+    sep_bwd_top<T, D>(a, B);
+}
+template <typename T, int D>
+__global__ void __launch_bounds__(NT) k_sep_bwd_fix_b(BatchArgs<T> b) {
+    Blk B;
+    const SolveArgs<T> a = batch_strip(b, 1, B);
+    sep_bwd_fix<T, D>(a, B);
+}
+
 // ---------------------------------------------------------------- phase C (all columns)
 template <typename T, int R>
-__global__ void __launch_bounds__(NT) k_phase_c(SolveArgs<T> a) {
+__device__ __forceinline__ void phase_c(const SolveArgs<T>& a, const Blk& B) {
     using V = cplx<T>;
     constexpr int G = 4, U = R / G;
     __shared__ V va[WP][R];
     __shared__ V vb[WP][R];
     const int t = threadIdx.x, i = t & (WP - 1), g = t >> 6;
-    const int l = blockIdx.x, rbase = blockIdx.y * R;
+    const int l = B.x, rbase = B.y * R;
     const int c = l / a.m;
     const bool is_sep = (c < a.P - 1) && (l == c * a.m + a.m - 1);
     const bool top = !is_sep && c > 0;
@@ -1218,6 +1368,15 @@ __global__ void __launch_bounds__(NT) k_phase_c(SolveArgs<T> a) {
         const int r = rbase + g + G * u;
         if (r < a.nrhs && i < a.W) scatter<T>(a, r, l, i, x[u]);
     }
+}
+
+template <typename T, int R>
+__global__ void __launch_bounds__(NT) k_phase_c(SolveArgs<T> a) { phase_c<T, R>(a, own_blk()); }
+template <typename T, int R>
+__global__ void __launch_bounds__(NT) k_phase_c_b(BatchArgs<T> b) {
+    Blk B;
+    const SolveArgs<T> a = batch_strip(b, 1, B);
+    phase_c<T, R>(a, B);
 }
 
 // ---------------------------------------------------------------- phase C (all columns), MFMA
@@ -1305,6 +1464,11 @@ __device__ __forceinline__ void phase_c_mfma(const SolveArgs<float>& a, const Bl
     }
 }
 __global__ void __launch_bounds__(NT) k_phase_c_mfma(SolveArgs<float> a) { phase_c_mfma(a, own_blk()); }
+__global__ void __launch_bounds__(NT) k_phase_c_mfma_b(BatchArgs<float> b, int nz) {
+    Blk B;
+    const SolveArgs<float> a = batch_strip(b, nz, B);
+    phase_c_mfma(a, B);
+}
 __global__ void __launch_bounds__(NT) k_phase_c_mfma_multi(MultiArgs<float> m) {
     int k;
     Blk b;
@@ -1317,17 +1481,17 @@ __global__ void __launch_bounds__(NT) k_phase_c_mfma_multi(MultiArgs<float> m) {
 constexpr int CT_ROWS = 8;
 
 template <typename T>
-__global__ void __launch_bounds__(NT) k_phase_c_targets(SolveArgs<T> a) {
+__device__ __forceinline__ void phase_c_targets(const SolveArgs<T>& a, const Blk& B) {
     using V = cplx<T>;
     constexpr int RC = 32;
     __shared__ V va[WP][RC];
     __shared__ V vb[WP][RC];
     __shared__ V fr[16][WP];
-    const int t = threadIdx.x, rbase = blockIdx.y * RC;
+    const int t = threadIdx.x, rbase = B.y * RC;
     const int sl = t / RC, rr = t % RC, r = rbase + rr;
     const int q = a.tcol[sl];
     const V zero = cmk<V>(0, 0);
-    const int l0 = blockIdx.x * CT_ROWS, l1 = min(a.Ny, l0 + CT_ROWS);
+    const int l0 = B.x * CT_ROWS, l1 = min(a.Ny, l0 + CT_ROWS);
     int loaded = -1;
     for (int l = l0; l < l1; ++l) {
         const int c = l / a.m;
@@ -1366,6 +1530,15 @@ __global__ void __launch_bounds__(NT) k_phase_c_targets(SolveArgs<T> a) {
         }
         __syncthreads();
     }
+}
+
+template <typename T>
+__global__ void __launch_bounds__(NT) k_phase_c_targets(SolveArgs<T> a) { phase_c_targets<T>(a, own_blk()); }
+template <typename T>
+__global__ void __launch_bounds__(NT) k_phase_c_targets_b(BatchArgs<T> b) {
+    Blk B;
+    const SolveArgs<T> a = batch_strip(b, 1, B);
+    phase_c_targets<T>(a, B);
 }
 
 // complex64 target columns per chunk as one small product on v_mfma_f32_16x16x4f32:
@@ -1537,6 +1710,11 @@ __device__ __forceinline__ void phase_c_targets_mfma(const SolveArgs<float>& a, 
 __global__ void __launch_bounds__(NT) k_phase_c_targets_mfma(SolveArgs<float> a) {
     phase_c_targets_mfma(a, own_blk());
 }
+__global__ void __launch_bounds__(NT) k_phase_c_targets_mfma_b(BatchArgs<float> b, int nz) {
+    Blk B;
+    const SolveArgs<float> a = batch_strip(b, nz, B);
+    phase_c_targets_mfma(a, B);
+}
 __global__ void __launch_bounds__(NT) k_phase_c_targets_mfma_multi(MultiArgs<float> m) {
     int k;
     Blk b;
@@ -1686,6 +1864,97 @@ SolveArgs<float> job_args(const StripJob& j) {
                              static_cast<const float2*>(j.Fa), static_cast<const float2*>(j.Fw),
                              static_cast<float2*>(j.Yw), j.nrhs, j.io);
 }
+// Right-hand sides of a batch of strips, in the workspace rows: the strip's source columns of
+// the field, and (inputs pu, pd given) what the sweeps feed the strip at its interfaces: the
+// transmission sources of both sweeps and the residual at the right interface.  One wave per
+// row, lanes along x.  Grid (rows / 4, right-hand sides, strips).
+template <typename T>
+__global__ void __launch_bounds__(NT) k_batch_rhs(BatchRhs<T> a) {
+    using V = cplx<T>;
+    const int q = threadIdx.x & (WP - 1), l = 4 * blockIdx.x + (threadIdx.x >> 6), r = blockIdx.y, k = blockIdx.z;
+    if (l >= a.Ny) return;
+    const StripIO x = a.io[k];
+    double2 v = cmk<double2>(0.0, 0.0);
+    if (q >= x.s_lo && q < x.s_hi) v = a.f[((size_t)r * a.Ny + l) * a.Nx + x.a + q];
+    if (a.pu) {
+        // inputs of row l: operand order (red_pos), entries t | psi, g | psi, g per chunk
+        const int c = l / a.M, lr = l - c * a.M, n = r & 15;
+        const size_t base = (((size_t)(a.s0 + k) * a.G + (r >> 4)) * a.P + c) * 3 * a.Mp * 16;
+        if (x.eL >= 0 && (q == x.eL - 1 || q == x.eL)) v = cadd(v, ccast<double2>(a.pu[base + red_pos<T>(lr, n)]));
+        if (x.eR >= 0 && q >= x.eR - 1 && q <= x.eR + 1) {
+            if (q < x.eR + 1)
+                v = cadd(v, ccast<double2>(a.pd[base + red_pos<T>((q - x.eR + 2) * a.Mp + lr, n)]));
+            if (q > x.eR - 1) v = cadd(v, ccast<double2>(a.pd[base + red_pos<T>(lr, n)]));
+        }
+    }
+    a.Yw[(((size_t)k * gridDim.y + r) * a.Ny + l) * WP + q] = ccast<V>(v);
+}
+
+template <typename T, int R>
+hipError_t run_batch(const BatchArgs<T>& b, int ns, bool targets, hipStream_t st, KTimer* kt) {
+    const SolveArgs<T>& a = b.a;
+    const unsigned RG = (a.nrhs + R - 1) / R, z = ns;
+    const unsigned nr1 = a.nrhs, RG16 = (a.nrhs + 15) / 16;
+    if (kt) kt->begin(K_PHASE_A, st, ns);
+    if constexpr (R == 4) {
+        const dim3 g(a.P, 1, z);
+        if (a.nrhs == 1) hipLaunchKernelGGL((k_phase_a_few_b<T, 1>), g, dim3(NT), 0, st, b);
+        else if (a.nrhs == 2) hipLaunchKernelGGL((k_phase_a_few_b<T, 2>), g, dim3(NT), 0, st, b);
+        else hipLaunchKernelGGL((k_phase_a_few_b<T, 4>), g, dim3(NT), 0, st, b);
+    } else if constexpr (std::is_same<T, float>::value) {
+        hipLaunchKernelGGL(k_phase_a_mfma_b<2>, dim3(a.P, RG, z), dim3(NT), 0, st, b);
+    } else {
+        hipLaunchKernelGGL(k_phase_a_mfma64_b, dim3(a.P, RG, z), dim3(NT), 0, st, b);
+    }
+    if (kt) kt->end(K_PHASE_A, st);
+    if (a.P > 1) {
+        if (kt) kt->begin(K_PHASE_B, st, ns);
+        constexpr int DS = Depth<T>::D;
+        if (a.P > 2 && a.G >= 2 && a.Fs) {
+            if constexpr (std::is_same<T, float>::value) {
+                const dim3 gp(a.P - 1, RG16, z);
+                const unsigned nl = (a.nrhs + SepLocalRB<T>::RB - 1) / SepLocalRB<T>::RB;
+                hipLaunchKernelGGL(k_sep_par_mfma_b<0>, gp, dim3(NT), 0, st, b);
+                hipLaunchKernelGGL((k_sep_fwd_local_b<T, DS, false>), dim3(nl, a.G, z), dim3(NT), 0, st, b);
+                hipLaunchKernelGGL((k_sep_fwd_top_b<T, DS>), dim3(nr1, 1, z), dim3(NT), 0, st, b);
+                hipLaunchKernelGGL(k_sep_par_mfma_b<1>, gp, dim3(NT), 0, st, b);
+                hipLaunchKernelGGL((k_sep_fix_bwd_local_b<T, DS, false>), dim3(nl, a.G, z), dim3(NT), 0, st, b);
+                hipLaunchKernelGGL((k_sep_bwd_top_b<T, DS>), dim3(nr1, 1, z), dim3(NT), 0, st, b);
+                if (!targets) hipLaunchKernelGGL(k_sep_par_mfma_b<2>, gp, dim3(NT), 0, st, b);
+            } else {
+                hipLaunchKernelGGL((k_sep_fwd_local_b<T, DS>), dim3(nr1, a.G, z), dim3(NT), 0, st, b);
+                hipLaunchKernelGGL((k_sep_fwd_top_b<T, DS>), dim3(nr1, 1, z), dim3(NT), 0, st, b);
+                hipLaunchKernelGGL((k_sep_fix_bwd_local_b<T, DS>), dim3(nr1, a.G, z), dim3(NT), 0, st, b);
+                hipLaunchKernelGGL((k_sep_bwd_top_b<T, DS>), dim3(nr1, 1, z), dim3(NT), 0, st, b);
+                hipLaunchKernelGGL((k_sep_bwd_fix_b<T, DS>), dim3(nr1, a.G - 1, z), dim3(NT), 0, st, b);
+            }
+        } else {
+            hipLaunchKernelGGL((k_phase_b0_b<T, R>), dim3(a.P - 1, RG, z), dim3(NT), 0, st, b);
+            if (a.P > 2) {
+                if (a.P - 1 <= ZMAX) hipLaunchKernelGGL((k_phase_b_b<T, DS, true>), dim3(nr1, 1, z), dim3(NT), 0, st, b);
+                else hipLaunchKernelGGL((k_phase_b_b<T, DS, false>), dim3(nr1, 1, z), dim3(NT), 0, st, b);
+            }
+        }
+        if (kt) kt->end(K_PHASE_B, st);
+    }
+    if (kt) kt->begin(K_PHASE_C, st, ns);
+    if constexpr (std::is_same<T, float>::value) {
+        // tiles and rows spread as in the launches of one strip; a batch fills the chip with fewer
+        const int tiles = ((a.m - 1) * 8 + 15) / 16, per = a.P * (int)RG16 * ns;
+        const int tz = std::min(8, std::max(1, (tiles + 7) / 8));
+        const int cz = std::max(1, std::min(std::min(8, a.m), (1024 + per - 1) / per));
+        if (targets) hipLaunchKernelGGL(k_phase_c_targets_mfma_b, dim3(a.P, RG16, z * tz), dim3(NT), 0, st, b, tz);
+        else hipLaunchKernelGGL(k_phase_c_mfma_b, dim3(a.P, RG16, z * cz), dim3(NT), 0, st, b, cz);
+    } else {
+        if (targets)
+            hipLaunchKernelGGL((k_phase_c_targets_b<T>), dim3((a.Ny + CT_ROWS - 1) / CT_ROWS, (a.nrhs + 31) / 32, z),
+                               dim3(NT), 0, st, b);
+        else hipLaunchKernelGGL((k_phase_c_b<T, R>), dim3(a.Ny, RG, z), dim3(NT), 0, st, b);
+    }
+    if (kt) kt->end(K_PHASE_C, st);
+    return hipGetLastError();
+}
+
 // rows of the full-column phase C per workgroup: about four workgroups per CU
 int phase_c_groups(const SolveArgs<float>& a) {
     const int per = a.P * ((a.nrhs + 15) / 16);
@@ -1696,6 +1965,41 @@ int targets_groups(const SolveArgs<float>& a) {
     return std::min(8, std::max(1, (tiles + 7) / 8));
 }
 }  // namespace
+
+template <typename T>
+hipError_t launch_strip_batch(const DevTables& t, const Geom& g, const Chunks& ch, const BatchRhs<T>& rhs,
+                              int ns, const cplx<T>* F, const cplx<T>* Fc,
+                              const cplx<T>* Fs, const cplx<T>* Fa, const cplx<T>* Fw, const IOSpec& io,
+                              hipStream_t st, KTimer* kt) {
+    const int nrhs = rhs.nrhs;
+    if (std::is_same<T, float>::value && ((nrhs > 4 && !Fa) || (ch.P > 2 && ch.G >= 2 && Fs && !Fw)))
+        return hipErrorInvalidValue;
+    if (kt) kt->begin(K_OTHER, st, 1);
+    hipLaunchKernelGGL((k_batch_rhs<T>), dim3((g.Ny + 3) / 4, nrhs, ns), dim3(NT), 0, st, rhs);
+    if (kt) kt->end(K_OTHER, st);
+    BatchArgs<T> b;
+    b.a = solve_args<T>(t, g, ch, rhs.s0, 0, F, Fc, Fs, Fa, Fw, rhs.Yw, nrhs, io);
+    b.a.io.pre = 1;
+    b.io = rhs.io;
+    b.tcol = t.tcol + 8 * rhs.s0;
+    b.F_st = (long)g.Ny * NSLOT * BLK;
+    b.Fc_st = (long)g.Ny * 2 * 8 * WP;
+    b.Fs_st = (long)(ch.P - 1) * 2 * BLK;
+    b.Fa_st = Fa ? (long)g.Ny * BLK : 0;
+    b.Fw_st = Fw ? (long)(ch.P - 1) * 4 * BLK : 0;
+    if (!Fs) b.Fs_st = 0;
+    b.Yw_st = (long)nrhs * g.Ny * WP;
+    b.tr_st = (long)nrhs * g.Ny;
+    const bool targets = b.a.io.targets_only != 0;
+    if (nrhs <= 4) return run_batch<T, 4>(b, ns, targets, st, kt);
+    return run_batch<T, 16>(b, ns, targets, st, kt);
+}
+template hipError_t launch_strip_batch<float>(const DevTables&, const Geom&, const Chunks&, const BatchRhs<float>&,
+                                              int, const float2*, const float2*, const float2*,
+                                              const float2*, const float2*, const IOSpec&, hipStream_t, KTimer*);
+template hipError_t launch_strip_batch<double>(const DevTables&, const Geom&, const Chunks&, const BatchRhs<double>&,
+                                               int, const double2*, const double2*, const double2*,
+                                               const double2*, const double2*, const IOSpec&, hipStream_t, KTimer*);
 
 bool strip_jobs_fusable(const StripJob* jobs, int n) {
     if (n < 2 || n > MULTI_MAX) return false;
