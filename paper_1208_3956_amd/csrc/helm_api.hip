@@ -162,9 +162,8 @@ struct helm_problem {
     size_t red_ws_bytes = 0;
     long red_gen = 0;           // generation of the plan and its buffers
     int red_m = 0;              // rows per fine chunk they were laid out for
-    // per-strip tables of the batches of strips, J entries each: Algorithm 2, the base of an
-    // upward sweep, the field of P
-    helm::StripIO* sio[3] = {};
+    // per-strip tables of the batches of strips, J entries each (kinds of strip_batch)
+    helm::StripIO* sio[5] = {};
     int factor_path = 0;        // 3-D: 1 = complex64 blocked Gauss-Jordan, 0 = FP64 inverses
     // strips with identical operators share one factorisation: fidx[s] is the factor slot
     // of strip s; the factor kernels run on the slots' representative strips (tf, gf: the
@@ -837,7 +836,9 @@ helm_status ensure_batch_ws(helm_t H, int nrhs) {
 }
 
 // One batch of strip solves over all strips: kind 0 Algorithm 2 (f -> dst), 1 the base of an
-// upward sweep (f -> Vb, Tup), 2 the field of P (f and the sweeps' inputs -> dst)
+// upward sweep (f -> Vb, Tup), 2 the field of P but its columns beta_s (f and both sweeps'
+// inputs -> dst), 3 the field v (f and the upward inputs -> dst), 4 the field w (the downward
+// inputs, added to dst)
 template <typename T>
 helm_status strip_batch(helm_t H, int nrhs, int kind, const double2* f, double2* dst) {
     using V = helm::cplx<T>;
@@ -850,9 +851,9 @@ helm_status strip_batch(helm_t H, int nrhs, int kind, const double2* f, double2*
     rhs.Yw = static_cast<V*>(w.Yb);
     rhs.f = f;
     rhs.nrhs = nrhs; rhs.Ny = g.Ny; rhs.Nx = g.Nx;
-    if (kind == 2) {
-        rhs.pu = static_cast<const V*>(w.rp);
-        rhs.pd = static_cast<const V*>(w.rpd);
+    if (kind >= 2) {
+        if (kind != 4) rhs.pu = static_cast<const V*>(w.rp);
+        if (kind != 3) rhs.pd = static_cast<const V*>(w.rpd);
         rhs.M = p.M; rhs.Mp = p.Mp; rhs.P = p.P; rhs.G = (nrhs + 15) / 16;
     }
     helm::IOSpec io;
@@ -860,8 +861,10 @@ helm_status strip_batch(helm_t H, int nrhs, int kind, const double2* f, double2*
     io.dst_ls = kind == 1 ? (g.J - 1) * helm::IWIN : g.Nx;
     io.dst_rs = g.Nrow() * io.dst_ls;
     io.targets_only = kind == 1 ? 1 : 0;
-    for (int s0 = 0; s0 < g.J; s0 += w.bstrips) {
-        const int ns = std::min(w.bstrips, g.J - s0);
+    io.accumulate = kind == 4 ? 1 : 0;
+    const int J = kind == 4 ? g.J - 1 : g.J;            // the downward sweep starts at strip J - 2
+    for (int s0 = 0; s0 < J; s0 += w.bstrips) {
+        const int ns = std::min(w.bstrips, J - s0);
         rhs.s0 = s0;
         rhs.io = H->sio[kind] + s0;
         if (kind == 1) {
@@ -880,36 +883,70 @@ helm_status strip_batch_any(helm_t H, int nrhs, int kind, const double2* f, doub
                                 : strip_batch<float>(H, nrhs, kind, f, dst);
 }
 
-// Both sweeps on the interface windows for the source f + psi: v -> Vw, g -> Gw, w -> Ww, and
-// every strip's inputs in the panels.  base: f is a full field whose strip solutions are in
-// Vb, Tup (it holds psi too if psi is given); else f is psi on the reduced columns.
-helm_status sweeps_inputs(helm_t H, int nrhs, const double2* f, const double2* psi, bool base) {
+// The upward sweep on the interface windows: v -> Vw, every strip's inputs in the panels.
+// base: the source is a full field whose strip solutions are in Vb, Tup, plus psi (may be
+// null) on the reduced columns; else it is psi alone.
+helm_status inputs_up(helm_t H, int nrhs, const double2* psi, bool base) {
+    CHK(ensure_red_ws(H, nrhs));
+    return H->prec == HELM_C128 ? red_sweep<double>(H, nrhs, true, psi, base)
+                                : red_sweep<float>(H, nrhs, true, psi, base);
+}
+
+// The residual g = f - A v -> Gw of windows whose first strip's columns are set, and the
+// downward sweep on it: w -> Ww
+helm_status inputs_down(helm_t H, int nrhs, const double2* f) {
     const auto& g = H->g;
     Work& w = H->wk;
-    const long nrows = (long)nrhs * g.Nrow(), wrow = (long)(g.J - 1) * helm::IWIN;
-    CHK(ensure_red_ws(H, nrhs));
-    if (H->prec == HELM_C128) CHK(red_sweep<double>(H, nrhs, true, psi, base));
-    else CHK(red_sweep<float>(H, nrhs, true, psi, base));
-    if (base) {
-        // the first strip takes no part in the sweep: its window columns are its base's
-        HIPCHK(TIMED(H, helm::K_OTHER, helm::launch_copy_win_cols(w.Vb, w.Vw, nrows, wrow, 0, 2, H->st)));
-        HIPCHK(TIMED(H, helm::K_STENCIL, helm::launch_stencil_win(3, H->t, g, nrhs, w.Vw, f, w.Gw, nullptr, H->st)));
-        // Algorithm 3's upward sweeps rely on zeros there
-        HIPCHK(TIMED(H, helm::K_OTHER, helm::launch_clear_win_cols(w.Vw, nrows, wrow, 0, 2, H->st)));
-    } else {
-        HIPCHK(TIMED(H, helm::K_STENCIL, helm::launch_stencil_win(0, H->t, g, nrhs, w.Vw, psi, w.Gw, nullptr, H->st)));
-    }
+    HIPCHK(TIMED(H, helm::K_STENCIL, helm::launch_stencil_win(3, H->t, g, nrhs, w.Vw, f, w.Gw, nullptr, H->st)));
+    // Algorithm 3's upward sweeps rely on zeros in the first strip's window columns
+    HIPCHK(TIMED(H, helm::K_OTHER, helm::launch_clear_win_cols(w.Vw, (long)nrhs * g.Nrow(),
+                                                               (long)(g.J - 1) * helm::IWIN, 0, 2, H->st)));
     return reduced_down(H, nrhs);
 }
 
-// out = P (f): the strips' fields from the inputs of both sweeps; column beta_s is the sum of
-// v (strip s) and w (strip s - 1), every other column one strip's
-helm_status field_of_P(helm_t H, int nrhs, const double2* f, double2* out) {
+// Both sweeps on the windows for a full field f whose strip solutions are in Vb, Tup
+// (f holds psi too if psi is given)
+helm_status inputs_both(helm_t H, int nrhs, const double2* f, const double2* psi) {
+    const auto& g = H->g;
     Work& w = H->wk;
-    CHK(strip_batch_any(H, nrhs, 2, f, out));
-    HIPCHK(TIMED(H, helm::K_OTHER, helm::launch_iface_sum(w.Vw, w.Ww, H->t.bw, H->g.J, (long)nrhs * H->g.Nrow(),
-                                                          H->g.Nx, out, H->st)));
-    return HELM_OK;
+    CHK(inputs_up(H, nrhs, psi, true));
+    // the first strip takes no part in the sweep: its window columns are its base's
+    HIPCHK(TIMED(H, helm::K_OTHER, helm::launch_copy_win_cols(w.Vb, w.Vw, (long)nrhs * g.Nrow(),
+                                                              (long)(g.J - 1) * helm::IWIN, 0, 2, H->st)));
+    return inputs_down(H, nrhs, f);
+}
+
+// out = P f.  f: full field with its strip solutions in Vb, Tup (base), holding psi as well
+// if psi is given; without base f holds psi (required) alone.
+// complex128: both sweeps on the windows, then one solve per strip with both sweeps' inputs;
+// column beta_s is the sum of v (strip s) and w (strip s - 1), every other column one strip's.
+// complex64: the fields v and w one after the other, the residual between them taken from
+// the field v itself.  The strips' fields carry the rounding of their block substitutions
+// (1.6e-6, mostly smooth), which jumps at the interfaces; the residual on beta_j - 1, beta_j
+// sees the jumps of v and the downward sweep removes them, as in the sequential sweeps.
+// From the windows' v, which never held them, they stayed in the field and cost the solves a
+// further iteration.
+helm_status field_of_P(helm_t H, int nrhs, const double2* f, const double2* psi, bool base, double2* out) {
+    const auto& g = H->g;
+    Work& w = H->wk;
+    if (H->prec == HELM_C128) {
+        if (base) {
+            CHK(inputs_both(H, nrhs, f, psi));
+        } else {
+            CHK(inputs_up(H, nrhs, psi, false));
+            HIPCHK(TIMED(H, helm::K_STENCIL, helm::launch_stencil_win(0, H->t, g, nrhs, w.Vw, psi, w.Gw, nullptr, H->st)));
+            CHK(reduced_down(H, nrhs));
+        }
+        CHK(strip_batch_any(H, nrhs, 2, f, out));
+        HIPCHK(TIMED(H, helm::K_OTHER, helm::launch_iface_sum(w.Vw, w.Ww, H->t.bw, g.J, (long)nrhs * g.Nrow(), g.Nx,
+                                                              out, H->st)));
+        return HELM_OK;
+    }
+    CHK(inputs_up(H, nrhs, psi, base));
+    CHK(strip_batch_any(H, nrhs, 3, f, out));
+    HIPCHK(TIMED(H, helm::K_OTHER, helm::launch_gather_win(out, H->t.bw, g.J, (long)nrhs * g.Nrow(), g.Nx, w.Vw, H->st)));
+    CHK(inputs_down(H, nrhs, f));
+    return strip_batch_any(H, nrhs, 4, nullptr, out);
 }
 
 // out = P f = v + w  (full form, Sec. 2.1)
@@ -917,10 +954,11 @@ helm_status apply_P_full(helm_t H, int nrhs, const double2* f, double2* out) {
     CHK(ensure_sweep_ws(H, nrhs));
     const auto& g = H->g;
     Work& w = H->wk;
-    if (batched(H)) {
+    // complex64 solves three batches instead of 2 J - 1 single strips: worth it while a
+    // single strip fills at most half of the 256 CUs
+    if (batched(H) && (H->prec == HELM_C128 || H->ch.P * ((nrhs + 15) / 16) <= 128)) {
         CHK(strip_batch_any(H, nrhs, 1, f, nullptr));
-        CHK(sweeps_inputs(H, nrhs, f, nullptr, true));
-        return field_of_P(H, nrhs, f, out);
+        return field_of_P(H, nrhs, f, nullptr, true, out);
     }
     CHK(sweep_up(H, nrhs, f, 0, true, nullptr));
     HIPCHK(TIMED(H, helm::K_STENCIL, helm::launch_apply_A_pairs(H->t, g, nrhs, H->t.rcols, g.J - 1, w.V, f, w.G, H->st)));
@@ -958,7 +996,7 @@ helm_status restart_rhs_reduced(helm_t H, int nrhs, const double2* r, double2* b
     if (g.J < 2) return HELM_OK;
     if (batched(H)) {
         CHK(strip_batch_any(H, nrhs, 1, r, nullptr));
-        CHK(sweeps_inputs(H, nrhs, r, nullptr, true));
+        CHK(inputs_both(H, nrhs, r, nullptr));
         HIPCHK(TIMED(H, helm::K_STENCIL, helm::launch_stencil_win(4, H->t, g, nrhs, w.Ww, nullptr, w.Gw, b, H->st)));
         return HELM_OK;
     }
@@ -1876,8 +1914,7 @@ helm_status solve_impl(helm_t H, int nrhs, const double2* f, double2* u, double 
             HIPCHK(TIMED(H, helm::K_OTHER, helm::launch_scatter_cols(w.w, red_cols(H), nred, nrhs, g.Nrow(), g.Nx, w.R, H->st, true)));
             if (batched(H)) {
                 // the strip solutions of r are still in Vb, Tup
-                CHK(sweeps_inputs(H, nrhs, w.R, w.w, true));
-                CHK(field_of_P(H, nrhs, w.R, w.Hf));
+                CHK(field_of_P(H, nrhs, w.R, w.w, true, w.Hf));
             } else {
                 CHK(apply_P_any(H, nrhs, w.R, w.Hf));
             }
@@ -1887,8 +1924,7 @@ helm_status solve_impl(helm_t H, int nrhs, const double2* f, double2* u, double 
             // which is zero everywhere else: nothing but this scatter writes it)
             HIPCHK(TIMED(H, helm::K_OTHER, helm::launch_scatter_cols(w.w, red_cols(H), nred, nrhs, g.Nrow(), g.Nx, w.Psi, H->st)));
             if (batched(H)) {
-                CHK(sweeps_inputs(H, nrhs, w.Psi, w.w, false));
-                CHK(field_of_P(H, nrhs, w.Psi, w.Hf));
+                CHK(field_of_P(H, nrhs, w.Psi, w.w, false, w.Hf));
             } else {
                 CHK(apply_P_any(H, nrhs, w.Psi, w.Hf));
             }
@@ -2262,9 +2298,10 @@ helm_status helm_setup(const double* c, double omega, double h, const helm_opts*
     if ((st = upload(H, (void**)&t.k2w, k2w.data(), k2w.size() * sizeof(double))) != HELM_OK) return st;
     if (dim == 2 && !robin) {
         // batches of strips: Algorithm 2 writes D~^(j); the base of an upward sweep the window
-        // columns and traces sweep_up writes; the field of P every core column but beta_s
-        std::vector<helm::StripIO> x[3];
-        for (int kind = 0; kind < 3; ++kind) {
+        // columns and traces sweep_up writes; the field of P every core column but beta_s, v
+        // the cores, w D~^(j)
+        std::vector<helm::StripIO> x[5];
+        for (int kind = 0; kind < 5; ++kind) {
             x[kind].resize(J);
             for (int s = 0; s < J; ++s) {
                 const auto& S = g.strips[s];
@@ -2287,7 +2324,9 @@ helm_status helm_setup(const double* c, double omega, double h, const helm_opts*
                         y.qo1 = g.beta[s + 1] - S.a;
                     }
                 } else {
-                    y.o_lo[0] = S.core_lo + (s > 0 ? 1 : 0) - S.a; y.o_hi[0] = S.core_hi - S.a;
+                    if (kind == 2) { y.o_lo[0] = S.core_lo + (s > 0 ? 1 : 0) - S.a; y.o_hi[0] = S.core_hi - S.a; }
+                    if (kind == 3) { y.o_lo[0] = S.core_lo - S.a; y.o_hi[0] = S.core_hi - S.a; }
+                    if (kind == 4) { y.o_lo[0] = S.kdn_lo - S.a; y.o_hi[0] = S.kdn_hi - S.a; }
                     if (s > 0) y.eL = g.beta[s] - S.a;
                     if (s < J - 1) y.eR = g.beta[s + 1] - S.a;
                 }

@@ -152,8 +152,9 @@ __host__ __device__ inline size_t red_pos(int k, int n) {
     return ((size_t)(k >> 3) * 2 + ((k >> 2) & 1)) * 64 + lane;
 }
 
-// Right-hand sides of the strips s0 .. s0 + ns - 1 of a batch: the source columns of field f
-// and, unless pu is null, the sweeps' inputs (pu upward, pd downward, see RedArgs)
+// Right-hand sides of the strips s0 .. s0 + ns - 1 of a batch: the source columns of field f,
+// the upward sweep's transmission sources (panels pu) and the downward sweep's inputs
+// (panels pd, see RedArgs); null ones are left out
 template <typename T>
 struct BatchRhs {
     cplx<T>* Yw = nullptr;        // [strip][nrhs][Ny][WP]
@@ -390,6 +391,8 @@ template <typename T>
 hipError_t launch_red_inputs(const RedIn<T>& a, hipStream_t st);
 // columns of window fields: dst[row wrow + c] = src[row wrow + c], c = c0 .. c0 + n - 1
 hipError_t launch_copy_win_cols(const double2* src, double2* dst, long nrows, long wrow, int c0, int n, hipStream_t st);
+// window columns 0 .. 3 (beta_j - 2 .. beta_j + 1) of every interface from a field
+hipError_t launch_gather_win(const double2* field, const int* bw, int J, long nrows, int Nx, double2* win, hipStream_t st);
 // out[row Nx + beta_s] = v + w of interface s (the middle column of its windows), s = 1 .. J - 1
 hipError_t launch_iface_sum(const double2* vw, const double2* ww, const int* bw, int J, long nrows, int Nx,
                             double2* out, hipStream_t st);

@@ -230,6 +230,14 @@ __global__ void k_copy_win_cols(const double2* __restrict__ src, double2* __rest
     const size_t at = (size_t)(p / n) * wrow + c0 + p % n;
     dst[at] = src[at];
 }
+__global__ void k_gather_win(const double2* __restrict__ field, const int* __restrict__ bw, int NI, long nrows, int Nx,
+                             double2* __restrict__ win) {
+    const long p = blockIdx.x * (long)blockDim.x + threadIdx.x;
+    if (p >= nrows * NI * 4) return;
+    const long row = p / (4 * NI);
+    const int j = (int)(p % (4 * NI)) >> 2, c = (int)(p & 3);
+    win[((size_t)row * NI + j) * IWIN + c] = field[(size_t)row * Nx + bw[j] + c];
+}
 __global__ void k_iface_sum(const double2* __restrict__ vw, const double2* __restrict__ ww, const int* __restrict__ bw, int NI,
                             long nrows, int Nx, double2* __restrict__ out) {
     const long p = blockIdx.x * (long)blockDim.x + threadIdx.x;
@@ -768,6 +776,11 @@ template hipError_t launch_red_inputs<double>(const RedIn<double>&, hipStream_t)
 hipError_t launch_copy_win_cols(const double2* src, double2* dst, long nrows, long wrow, int c0, int n, hipStream_t st) {
     hipLaunchKernelGGL(k_copy_win_cols, dim3((unsigned)((nrows * n + NT - 1) / NT)), dim3(NT), 0, st, src, dst, nrows, wrow,
                        c0, n);
+    return hipGetLastError();
+}
+hipError_t launch_gather_win(const double2* field, const int* bw, int J, long nrows, int Nx, double2* win, hipStream_t st) {
+    hipLaunchKernelGGL(k_gather_win, dim3((unsigned)((nrows * (J - 1) * 4 + NT - 1) / NT)), dim3(NT), 0, st, field, bw, J - 1,
+                       nrows, Nx, win);
     return hipGetLastError();
 }
 hipError_t launch_iface_sum(const double2* vw, const double2* ww, const int* bw, int J, long nrows, int Nx,

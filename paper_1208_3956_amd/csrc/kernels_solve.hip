@@ -1875,13 +1875,13 @@ __global__ void __launch_bounds__(NT) k_batch_rhs(BatchRhs<T> a) {
     if (l >= a.Ny) return;
     const StripIO x = a.io[k];
     double2 v = cmk<double2>(0.0, 0.0);
-    if (q >= x.s_lo && q < x.s_hi) v = a.f[((size_t)r * a.Ny + l) * a.Nx + x.a + q];
-    if (a.pu) {
+    if (a.f && q >= x.s_lo && q < x.s_hi) v = a.f[((size_t)r * a.Ny + l) * a.Nx + x.a + q];
+    if (a.pu || a.pd) {
         // inputs of row l: operand order (red_pos), entries t | psi, g | psi, g per chunk
         const int c = l / a.M, lr = l - c * a.M, n = r & 15;
         const size_t base = (((size_t)(a.s0 + k) * a.G + (r >> 4)) * a.P + c) * 3 * a.Mp * 16;
-        if (x.eL >= 0 && (q == x.eL - 1 || q == x.eL)) v = cadd(v, ccast<double2>(a.pu[base + red_pos<T>(lr, n)]));
-        if (x.eR >= 0 && q >= x.eR - 1 && q <= x.eR + 1) {
+        if (a.pu && x.eL >= 0 && (q == x.eL - 1 || q == x.eL)) v = cadd(v, ccast<double2>(a.pu[base + red_pos<T>(lr, n)]));
+        if (a.pd && x.eR >= 0 && q >= x.eR - 1 && q <= x.eR + 1) {
             if (q < x.eR + 1)
                 v = cadd(v, ccast<double2>(a.pd[base + red_pos<T>((q - x.eR + 2) * a.Mp + lr, n)]));
             if (q > x.eR - 1) v = cadd(v, ccast<double2>(a.pd[base + red_pos<T>(lr, n)]));
