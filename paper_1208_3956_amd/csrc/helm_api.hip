@@ -13,9 +13,11 @@
 #include <cstring>
 #include <string>
 #include <condition_variable>
+#include <map>
 #include <mutex>
 #include <thread>
 #include <type_traits>
+#include <unordered_map>
 #include <vector>
 
 #include "helm_internal.hpp"
@@ -358,19 +360,113 @@ helm_status fail(helm_t H, helm_status code, const std::string& msg) {
         if (s_ != HELM_OK) return s_;             \
     } while (0)
 
+// Device memory of closed handles, kept for later ones.  A program that makes a handle per
+// model (a misfit and its gradient) allocated and freed 3.5 GB per call; the frees alone took
+// 6 to 170 ms (the driver clears what it takes back, at about 35 GB/s when it has a backlog)
+// against 28 ms of work.  At most POOL_BYTES per device stay cached, the oldest block goes
+// first, and all of them when an allocation fails.  A block enters only after the stream that
+// used it has been synchronised, so that any thread may take it for any stream.
+struct Pool {
+    static constexpr size_t POOL_BYTES = (size_t)8 << 30;
+    struct Block { size_t size; int dev; unsigned long tick; };
+    std::mutex mu;
+    std::unordered_map<void*, Block> live;                              // every block handed out
+    std::map<std::pair<int, size_t>, std::vector<std::pair<unsigned long, void*>>> idle;   // by device and size
+    std::unordered_map<int, size_t> cached;
+    unsigned long tick = 0;
+
+    static Pool& get() {
+        static Pool* p = new Pool();      // never destroyed: blocks outlive the HIP runtime's teardown otherwise
+        return *p;
+    }
+    static size_t round(size_t n) {
+        const size_t u = n >= ((size_t)1 << 20) ? (size_t)2 << 20 : 4096;
+        return (n + u - 1) / u * u;
+    }
+    // with mu held: an idle block of at least n bytes and at most a quarter more
+    void* take(int dev, size_t n) {
+        auto it = idle.lower_bound({dev, n});
+        if (it == idle.end() || it->first.first != dev || it->first.second > n + n / 4) return nullptr;
+        void* p = it->second.back().second;
+        const size_t sz = it->first.second;
+        it->second.pop_back();
+        if (it->second.empty()) idle.erase(it);
+        cached[dev] -= sz;
+        live[p] = Block{sz, dev, 0};
+        return p;
+    }
+    // with mu held: frees idle blocks of dev, oldest first, until at most `keep` bytes stay
+    void trim(int dev, size_t keep) {
+        while (cached[dev] > keep) {
+            auto best = idle.end();
+            for (auto it = idle.lower_bound({dev, 0}); it != idle.end() && it->first.first == dev; ++it)
+                if (best == idle.end() || it->second.front().first < best->second.front().first) best = it;
+            if (best == idle.end()) return;
+            (void)hipFree(best->second.front().second);
+            cached[dev] -= best->first.second;
+            best->second.erase(best->second.begin());
+            if (best->second.empty()) idle.erase(best);
+        }
+    }
+    hipError_t alloc(void** p, size_t bytes) {
+        const size_t n = round(bytes);
+        int dev = 0;
+        (void)hipGetDevice(&dev);
+        std::lock_guard<std::mutex> lk(mu);
+        if ((*p = take(dev, n))) return hipSuccess;
+        hipError_t e = hipMalloc(p, n);
+        if (e != hipSuccess && cached[dev] > 0) {
+            (void)hipGetLastError();
+            trim(dev, 0);
+            e = hipMalloc(p, n);
+        }
+        if (e == hipSuccess) live[*p] = Block{n, dev, 0};
+        else { *p = nullptr; (void)hipGetLastError(); }
+        return e;
+    }
+    void put(void* p) {
+        std::lock_guard<std::mutex> lk(mu);
+        auto it = live.find(p);
+        if (it == live.end()) return;
+        const Block b = it->second;
+        live.erase(it);
+        if (b.size > POOL_BYTES) { (void)hipFree(p); return; }
+        trim(b.dev, POOL_BYTES - b.size);
+        idle[{b.dev, b.size}].push_back({++tick, p});
+        cached[b.dev] += b.size;
+    }
+    size_t idle_bytes() {
+        int dev = 0;
+        (void)hipGetDevice(&dev);
+        std::lock_guard<std::mutex> lk(mu);
+        return cached[dev];
+    }
+};
+
 template <typename P>
 helm_status dmalloc(helm_t H, P** p, size_t bytes) {
     *p = nullptr;
     if (bytes == 0) bytes = 16;
-    hipError_t e = hipMalloc((void**)p, bytes);
+    hipError_t e = Pool::get().alloc((void**)p, bytes);
     if (e != hipSuccess)
         return fail(H, HELM_ENOMEM, "hipMalloc of " + std::to_string(bytes) + " bytes failed: " +
                                         hipGetErrorString(e));
     return HELM_OK;
 }
 
-void dfree(void* p) {
-    if (p) (void)hipFree(p);
+// memory of handle H, which only work ordered on its stream uses
+void dfree(helm_t H, void* p) {
+    if (!p) return;
+    (void)(H->st ? hipStreamSynchronize(H->st) : hipDeviceSynchronize());
+    Pool::get().put(p);
+}
+
+// free device memory, the pool's idle blocks included (an allocation that needs them gets them)
+hipError_t free_bytes(size_t* n) {
+    size_t tot = 0;
+    hipError_t e = hipMemGetInfo(n, &tot);
+    *n += Pool::get().idle_bytes();
+    return e;
 }
 
 // ---------------------------------------------------------------- PML profile
@@ -413,11 +509,12 @@ helm_status upload(helm_t H, void** dptr, const void* src, size_t bytes) {
 }
 
 // ---------------------------------------------------------------- workspaces
-void free_work(Work& w) {
+void free_work(helm_t H) {
+    Work& w = H->wk;
     void* ps[] = {w.Yw, w.V, w.G, w.PF, w.Psi, w.Wf, w.Hf, w.Vw, w.Gw, w.Ww, w.Ut, w.R, w.Tup, w.Tdn, w.basis,
                   w.w, w.h1, w.h2, w.nrm, w.partial, w.npartial, w.y, w.red, w.apin, w.basis_old,
                   w.Yw2, w.Yw3, w.PsiC, w.Rob, w.RobR, w.rp, w.rpd, w.rrh, w.rxs, w.Yb, w.Vb};
-    for (void* p : ps) dfree(p);
+    for (void* p : ps) dfree(H, p);
     w = Work();
 }
 
@@ -428,7 +525,7 @@ int rhs_pad16(int nrhs) { return (nrhs + 15) / 16 * 16; }
 helm_status ensure_sweep_ws(helm_t H, int nrhs) {
     Work& w = H->wk;
     if (w.nrhs >= nrhs && w.V) return HELM_OK;
-    free_work(w);
+    free_work(H);
     H->ws_epoch += 1;
     const auto& g = H->g;
     const size_t fb = field_bytes(H, nrhs);
@@ -701,7 +798,7 @@ helm_status ensure_red_ws(helm_t H, int nrhs) {
     const auto& p = H->red;
     const int G = (nrhs + 15) / 16;
     if (!p.kappa || (w.rp && w.rnrhs >= nrhs && w.rgen == H->red_gen)) return HELM_OK;
-    dfree(w.rp); dfree(w.rpd); dfree(w.rrh); dfree(w.rxs);
+    dfree(H, w.rp); dfree(H, w.rpd); dfree(H, w.rrh); dfree(H, w.rxs);
     w.rp = w.rpd = w.rrh = w.rxs = nullptr;
     w.rnrhs = 0;
     H->ws_epoch += 1;
@@ -818,7 +915,7 @@ helm_status ensure_batch_ws(helm_t H, int nrhs) {
     const int nsub = (g.J + nb - 1) / nb;
     nb = (g.J + nsub - 1) / nsub;
     if (!w.Yb || w.bcap < (size_t)nb * nrhs) {
-        dfree(w.Yb);
+        dfree(H, w.Yb);
         w.Yb = nullptr;
         w.bnrhs = 0;
         CHK(dmalloc(H, &w.Yb, per * nb));
@@ -1280,13 +1377,13 @@ helm_status build_reduced(helm_t H) {
     const size_t nf = (size_t)H->nfac;
     if (!p.kappa) { H->red = p; return HELM_OK; }
     if (H->red_m != H->ch.m) {
-        dfree(H->red_T); dfree(H->red_R); dfree(H->red_S); dfree(H->red_ws);
+        dfree(H, H->red_T); dfree(H, H->red_R); dfree(H, H->red_S); dfree(H, H->red_ws);
         H->red_T = H->red_R = H->red_S = H->red_ws = nullptr;
         H->red_m = 0;
         H->red = helm::RedPlan();
         H->red_gen += 1;
-        size_t freeb = 0, totb = 0;
-        HIPCHK(hipMemGetInfo(&freeb, &totb));
+        size_t freeb = 0;
+        HIPCHK(free_bytes(&freeb));
         if (nf * (2 * p.tsz + 2 * p.rsz + p.ssz) * esz + bs.bytes > freeb / 2) return HELM_OK;
         CHK(dmalloc(H, &H->red_T, nf * 2 * p.tsz * esz));
         CHK(dmalloc(H, &H->red_R, nf * 2 * p.rsz * esz));
@@ -1379,17 +1476,17 @@ struct Givens {
 helm_status ensure_gmres_ws(helm_t H, int nrhs, long n, int mwant) {
     Work& w = H->wk;
     if (w.basis && w.n == n && w.mcap >= mwant && w.gnrhs >= nrhs) return HELM_OK;
-    dfree(w.basis); dfree(w.w); dfree(w.h1); dfree(w.h2); dfree(w.nrm); dfree(w.partial);
-    dfree(w.npartial); dfree(w.y); dfree(w.red); dfree(w.apin); dfree(w.basis_old);
-    dfree(w.R); dfree(w.Ut);
+    dfree(H, w.basis); dfree(H, w.w); dfree(H, w.h1); dfree(H, w.h2); dfree(H, w.nrm); dfree(H, w.partial);
+    dfree(H, w.npartial); dfree(H, w.y); dfree(H, w.red); dfree(H, w.apin); dfree(H, w.basis_old);
+    dfree(H, w.R); dfree(H, w.Ut);
     w.basis = w.w = w.h1 = w.h2 = w.y = w.red = w.apin = w.partial = w.basis_old = nullptr;
     w.R = w.Ut = nullptr;
     w.mcap_old = 0;
     w.gnrhs = 0;
     w.nrm = w.npartial = nullptr;
     H->ws_epoch += 1;
-    size_t freeb = 0, totb = 0;
-    HIPCHK(hipMemGetInfo(&freeb, &totb));
+    size_t freeb = 0;
+    HIPCHK(free_bytes(&freeb));
     const size_t vb = (size_t)nrhs * n * sizeof(double2);
     size_t fit = vb ? (size_t)(0.8 * (double)freeb) / vb : (size_t)mwant + 3;
     int m = (int)std::min<size_t>((size_t)mwant, fit > 3 ? fit - 3 : 1);
@@ -1708,11 +1805,11 @@ helm_status build_aug(helm_t H, int nrhs, long n, double2* b, const std::vector<
     constexpr int RECYCLE_MIN_K = 16;
     if (kmax < RECYCLE_MIN_K || (int)hess.size() != nrhs) return HELM_OK;
     if (!w.basis_old || w.mcap_old < w.mcap) {
-        dfree(w.basis_old);
+        dfree(H, w.basis_old);
         w.basis_old = nullptr;
         w.mcap_old = 0;
         // the same capacity as w.basis (the two buffers are swapped below)
-        if (hipMalloc((void**)&w.basis_old, (size_t)w.gnrhs * n * sizeof(double2) * (w.mcap + 1)) != hipSuccess) {
+        if (Pool::get().alloc((void**)&w.basis_old, (size_t)w.gnrhs * n * sizeof(double2) * (w.mcap + 1)) != hipSuccess) {
             (void)hipGetLastError();
             w.basis_old = nullptr;
             return HELM_OK;                      // no room: a plain restart
@@ -2350,19 +2447,15 @@ helm_status factor3(helm_t H) {
     const size_t BB = (size_t)g.Bp * g.Bp;
     const bool single = H->prec != HELM_C128;
     const size_t esz = single ? sizeof(float2) : sizeof(double2);
-    void* F = nullptr;
     const int nf = H->nfac;               // one factorisation per distinct slab operator
-    CHK(dmalloc(H, &F, (size_t)nf * g.Ny * BB * esz));
-    // F is freed on every early return (HIP errors included) unless it was handed to H
-    struct FOwner {
-        void*& p; bool kept = false;
-        ~FOwner() { if (!kept) dfree(p); }
-    } fown{F};
-    auto keep_F = [&]() { H->F = F; fown.kept = true; };
+    // the handle's for its life: every factorisation overwrites all of it
+    if (!H->F) CHK(dmalloc(H, &H->F, (size_t)nf * g.Ny * BB * esz));
+    void* F = H->F;
     struct Bufs {
+        helm_t H;
         std::vector<void*> p;
-        ~Bufs() { for (void* q : p) dfree(q); }
-    } bufs;
+        ~Bufs() { for (void* q : p) dfree(H, q); }
+    } bufs{H, {}};
     auto alloc = [&](void** q, size_t bytes) -> helm_status {
         CHK(dmalloc(H, q, bytes));
         bufs.p.push_back(*q);
@@ -2457,7 +2550,6 @@ helm_status factor3(helm_t H) {
             if ((st = alloc(&pw, (size_t)nf * BB * sizeof(float2))) != HELM_OK) return st;
             HIPCHK(panelize(F, pw));
             HIPCHK(hipStreamSynchronize(H->st));
-            keep_F();
             H->factored = true;
             return HELM_OK;
         }
@@ -2490,7 +2582,6 @@ helm_status factor3(helm_t H) {
         HIPCHK(panelize(F, S));
         HIPCHK(hipStreamSynchronize(H->st));
     }
-    keep_F();
     if (herr) return fail(H, HELM_ESINGULAR, "zero or non-finite pivot in a slab factorisation");
     H->factored = true;
     return HELM_OK;
@@ -2506,11 +2597,7 @@ helm_status helm_factor(helm_t H) {
     CHK(drop_graph(H));
     HIPCHK(hipStreamSynchronize(H->st));    // no queued work may still read the old factors
     H->factored = false;
-    if (g.dim == 3) {
-        dfree(H->F);
-        H->F = nullptr;
-        return factor3(H);
-    }
+    if (g.dim == 3) return factor3(H);
     // The factor buffers keep their size for the handle's life: they are allocated (and
     // cleared: slots no factorisation writes must read as zero) once, and every later
     // factorisation overwrites the same slots.  The complex64 path keeps the FP64 factor as
@@ -2533,9 +2620,9 @@ helm_status helm_factor(helm_t H) {
         // leaves unwritten read as zero, and the propagators take its separator count
         HIPCHK(hipMemsetAsync(H->F64, 0, nel * sizeof(double2), H->st));
         if (single) HIPCHK(hipMemsetAsync(H->F, 0, nel * esz, H->st));
-        if (H->Fs != H->Fs64) dfree(H->Fs);
-        dfree(H->Fs64);
-        dfree(H->Fw);
+        if (H->Fs != H->Fs64) dfree(H, H->Fs);
+        dfree(H, H->Fs64);
+        dfree(H, H->Fw);
         H->Fs = H->Fs64 = nullptr;
         H->Fw = nullptr;
         if (nsel) {
@@ -2625,7 +2712,7 @@ helm_status helm_autotune(helm_t H, int nrhs, const void* rhs, const int* cand, 
     // as well (Algorithms 2 and 4 and the restarts run it, and there the chunk size counts)
     const size_t in_bytes = reduced ? (size_t)nrhs * g.Nrow() * nred * sizeof(double2) : field_bytes(H, nrhs);
     double2 *xin = nullptr, *xout = nullptr;
-    struct Bufs { double2** a; double2** b; ~Bufs() { dfree(*a); dfree(*b); } } bufs{&xin, &xout};
+    struct Bufs { helm_t H; double2** a; double2** b; ~Bufs() { dfree(H, *a); dfree(H, *b); } } bufs{H, &xin, &xout};
     CHK(dmalloc(H, &xin, in_bytes));
     CHK(dmalloc(H, &xout, in_bytes));
     if (reduced)
@@ -2776,9 +2863,10 @@ helm_status helm_grad(helm_t H, int nsrc, const void* src, int nrec, const int64
     const int nu = (int)upt.size();
 
     struct Bufs {
+        helm_t H;
         std::vector<void*> p;
-        ~Bufs() { for (void* q : p) dfree(q); }
-    } bufs;
+        ~Bufs() { for (void* q : p) dfree(H, q); }
+    } bufs{H, {}};
     auto alloc = [&](void** q, size_t bytes) -> helm_status {
         CHK(dmalloc(H, q, bytes));
         bufs.p.push_back(*q);
@@ -2986,21 +3074,21 @@ void helm_destroy(helm_t H) {
         if (e) (void)hipEventDestroy(e);
     for (hipStream_t q : H->st_fac)
         if (q) (void)hipStreamDestroy(q);
-    free_work(H->wk);
+    free_work(H);
     delete H->timer;
-    if (H->F != H->F64) dfree(H->F);
-    if (H->Fs != H->Fs64) dfree(H->Fs);
-    dfree(H->F64);
-    dfree(H->Fs64);
-    dfree(H->Fc);
-    dfree(H->Fa);
-    dfree(H->Fw);
-    dfree(H->red_T);
-    dfree(H->red_R);
-    dfree(H->red_S);
-    dfree(H->red_ws);
-    dfree(H->d_err);
-    for (void* p : H->owned) dfree(p);
+    if (H->F != H->F64) dfree(H, H->F);
+    if (H->Fs != H->Fs64) dfree(H, H->Fs);
+    dfree(H, H->F64);
+    dfree(H, H->Fs64);
+    dfree(H, H->Fc);
+    dfree(H, H->Fa);
+    dfree(H, H->Fw);
+    dfree(H, H->red_T);
+    dfree(H, H->red_R);
+    dfree(H, H->red_S);
+    dfree(H, H->red_ws);
+    dfree(H, H->d_err);
+    for (void* p : H->owned) dfree(H, p);
     delete H;
 }
 
