@@ -132,14 +132,6 @@ struct EventTimer : helm::KTimer {
     ~EventTimer() override { for (hipEvent_t e : pool) (void)hipEventDestroy(e); }
 };
 
-// slab groups (one stream each) of the 3-D complex64 factorisation
-#ifndef FAC3_GROUPS
-#define FAC3_GROUPS 2
-#endif
-#ifndef FAC3_BATCH
-#define FAC3_BATCH 0      // slabs per group; 0: the slabs split evenly over the streams
-#endif
-
 struct Fuser;
 
 struct helm_problem {
@@ -206,7 +198,7 @@ struct helm_problem {
     int batch_fuse = 0;         // join fused strip-solve launches in helm_solve_batch
     hipStream_t st_c[2] = {};   // concurrent sweep: streams of the downward chain and the z solves
     hipEvent_t ev_c[3] = {};    // fork / join events of the concurrent sweep
-    hipStream_t st_fac[FAC3_GROUPS - 1] = {};   // group streams of the 3-D complex64 factorisation
+    hipStream_t st_fac = nullptr;   // 3-D factorisation: stream of the upper end
     hipStream_t cap_st = nullptr;  // private stream the graph is captured on (capture is not
                                    // allowed on the legacy default stream); replays go to st
     long ws_epoch = 0;          // workspace generation (graphs captured before it are stale)
@@ -2462,8 +2454,8 @@ helm_status factor3(helm_t H) {
         return HELM_OK;
     };
     const size_t nb = helm::factor3_panel_width();
-    double2 *S, *G64, *Tm, *Cm;
-    int *perm, *pi;
+    double2 *S[2], *G64[2], *Tm[2], *Cm[2];
+    int *perm[2], *pi[2];
     void* work32 = nullptr;
     helm_status st;
     helm::Fac3Args a;
@@ -2484,6 +2476,35 @@ helm_status factor3(helm_t H) {
         // one timed unit
         return TIMED(H, helm::K_OTHER, run());
     };
+    // the eliminations from both ends of the slabs meet at plane p.  plane(l, end, stream): the
+    // lower end on the handle's stream, the upper on a second one (default priority), then the
+    // middle plane on both (end says whose workspace it uses)
+    const int p = helm::slab_mid(g.Ny);
+    if (!H->st_fac) HIPCHK(hipStreamCreateWithFlags(&H->st_fac, hipStreamNonBlocking));
+    hipEvent_t evs[2] = {};
+    struct Evs {
+        hipEvent_t* e;
+        ~Evs() { for (int q = 0; q < 2; ++q) if (e[q]) (void)hipEventDestroy(e[q]); }
+    } evguard{evs};
+    for (hipEvent_t& v : evs) HIPCHK(hipEventCreateWithFlags(&v, hipEventDisableTiming));
+    auto two_ends = [&](auto plane) -> hipError_t {
+        hipStream_t q[2] = {H->st, H->st_fac};
+        auto after = [&](int from, int to) {             // stream `to` waits for `from`
+            const hipError_t r = hipEventRecord(evs[from], q[from]);
+            return r == hipSuccess ? hipStreamWaitEvent(q[to], evs[from], 0) : r;
+        };
+        hipError_t r = after(0, 1);
+        for (int k = 0; k < p && r == hipSuccess; ++k) {
+            r = plane(k, 0, q[0]);
+            if (r == hipSuccess && g.Ny - 1 - k > p) r = plane(g.Ny - 1 - k, 1, q[1]);
+        }
+        if (r == hipSuccess) r = after(1, 0);
+        if (r == hipSuccess) r = after(0, 1);
+        for (int end = 0; end < 2 && r == hipSuccess; ++end) r = plane(p, end, q[end]);
+        if (r == hipSuccess) r = after(1, 0);
+        else (void)hipStreamSynchronize(q[1]);           // its buffers are about to be freed
+        return r;
+    };
     // HELM_FACTOR3_FP64=1 sends a complex64 factorisation straight to the FP64 route (the one
     // an ill-conditioned diagonal block would take), so that route can be exercised
     const char* force = std::getenv("HELM_FACTOR3_FP64");
@@ -2491,53 +2512,23 @@ helm_status factor3(helm_t H) {
         // complex64 blocked Gauss-Jordan in place in the stored factor; a diagonal block
         // that is singular or ill-conditioned sends the whole factorisation to the FP64
         // Gauss-Jordan with partial pivoting over the whole column below
-        if ((st = alloc(&work32, helm::factor3_f32_work_bytes(nf, g.Bp))) != HELM_OK) return st;
+        const size_t wb = helm::factor3_f32_work_bytes(nf, g.Bp);
+        if ((st = alloc(&work32, 2 * wb)) != HELM_OK) return st;
         HIPCHK(hipMemsetAsync(H->d_err, 0, sizeof(int), H->st));
-        // the slabs are independent.  FAC3_GROUPS streams (the handle's and streams of their
-        // own, default priority) each factor one group of slabs at a time, all planes of a
-        // group before the next, so that one stream's latency-bound diagonal inverses
-        // overlap the other streams' update GEMMs.  Measured at 80^3 (16 slabs, 2 streams):
-        // groups of 8 slabs 1130 ms, of 4 1226 ms, of 2 1590 ms (smaller groups keep the
-        // updated matrices in the last-level cache but launch too few tiles), one stream
-        // 1425 ms; 4 or 8 streams with one group each changed nothing
-        constexpr int NGR = FAC3_GROUPS;
-        const int batch = FAC3_BATCH > 0 ? std::min(FAC3_BATCH, nf) : (nf + NGR - 1) / NGR;
-        const int ngroups = (nf + batch - 1) / batch;
-        const int nst = std::min(NGR, ngroups);
-        hipStream_t sts[NGR];
-        sts[0] = H->st;
-        for (int q = 1; q < nst; ++q) {
-            if (!H->st_fac[q - 1]) HIPCHK(hipStreamCreateWithFlags(&H->st_fac[q - 1], hipStreamNonBlocking));
-            sts[q] = H->st_fac[q - 1];
-        }
-        hipEvent_t evs[NGR] = {};
-        struct Evs {
-            hipEvent_t* e; int n;
-            ~Evs() { for (int q = 0; q < n; ++q) if (e[q]) (void)hipEventDestroy(e[q]); }
-        } evguard{evs, NGR};
-        for (int q = 0; q < nst; ++q) HIPCHK(hipEventCreateWithFlags(&evs[q], hipEventDisableTiming));
         float2* F32 = static_cast<float2*>(F);
         const size_t stride = (size_t)g.Ny * BB;
-        hipError_t e = TIMED(H, helm::K_FACTOR_CHUNKS, [&]() -> hipError_t {
-            // fork: every group stream waits for the work queued so far on the handle's
-            hipError_t r = hipEventRecord(evs[0], H->st);
-            for (int q = 1; q < nst && r == hipSuccess; ++q) r = hipStreamWaitEvent(sts[q], evs[0], 0);
-            for (int g0 = 0; g0 < ngroups && r == hipSuccess; g0 += nst)
-                for (int l = 0; l < g.Ny && r == hipSuccess; ++l)
-                    for (int q = 0; q < nst && r == hipSuccess; ++q) {
-                        const int gi = g0 + q;
-                        if (gi >= ngroups) continue;
-                        const int s0 = gi * batch;
-                        const int ns = std::min(batch, nf - s0);
-                        r = helm::launch_factor3_plane_f32(a, l, F32, stride, work32, H->d_err, sts[q], s0, ns);
-                    }
-            // join
-            for (int q = 1; q < nst && r == hipSuccess; ++q) {
-                r = hipEventRecord(evs[q], sts[q]);
-                if (r == hipSuccess) r = hipStreamWaitEvent(H->st, evs[q], 0);
-            }
-            return r;
-        }());
+        // the planes below the middle one on the handle's stream, those above on a second one,
+        // all slabs of a plane together, so that one end's latency-bound diagonal inverses
+        // overlap the other end's update GEMMs; the middle plane in two halves of the slabs
+        hipError_t e = TIMED(H, helm::K_FACTOR_CHUNKS, two_ends([&](int l, int end, hipStream_t q) {
+            void* wk = static_cast<char*>(work32) + end * wb;
+            if (l != p)
+                return helm::launch_factor3_plane_f32(a, l, F32, stride, wk, H->d_err, q, 0, nf, end == 0 && l > 0,
+                                                      end == 1 && l < g.Ny - 1);
+            const int s0 = end == 0 ? 0 : (nf + 1) / 2, s1 = end == 0 ? (nf + 1) / 2 : nf;
+            return s1 > s0 ? helm::launch_factor3_plane_f32(a, l, F32, stride, wk, H->d_err, q, s0, s1 - s0, true, true)
+                           : hipSuccess;
+        }));
         HIPCHK(e);
         HIPCHK(hipMemcpyAsync(&herr, H->d_err, sizeof(int), hipMemcpyDeviceToHost, H->st));
         HIPCHK(hipStreamSynchronize(H->st));
@@ -2555,31 +2546,32 @@ helm_status factor3(helm_t H) {
         }
     }
     H->factor_path = 0;
-    if ((st = alloc((void**)&S, nf * BB * sizeof(double2))) != HELM_OK ||
-        (st = alloc((void**)&G64, nf * BB * sizeof(double2))) != HELM_OK ||
-        (st = alloc((void**)&Tm, (size_t)nf * g.Bp * nb * sizeof(double2))) != HELM_OK ||
-        (st = alloc((void**)&Cm, (size_t)nf * g.Bp * nb * sizeof(double2))) != HELM_OK ||
-        (st = alloc((void**)&perm, (size_t)nf * g.Bp * sizeof(int))) != HELM_OK ||
-        (st = alloc((void**)&pi, (size_t)nf * g.Bp * sizeof(int))) != HELM_OK)
-        return st;
+    // one set of work arrays per end
+    for (int end = 0; end < 2; ++end)
+        if ((st = alloc((void**)&S[end], nf * BB * sizeof(double2))) != HELM_OK ||
+            (st = alloc((void**)&G64[end], nf * BB * sizeof(double2))) != HELM_OK ||
+            (st = alloc((void**)&Tm[end], (size_t)nf * g.Bp * nb * sizeof(double2))) != HELM_OK ||
+            (st = alloc((void**)&Cm[end], (size_t)nf * g.Bp * nb * sizeof(double2))) != HELM_OK ||
+            (st = alloc((void**)&perm[end], (size_t)nf * g.Bp * sizeof(int))) != HELM_OK ||
+            (st = alloc((void**)&pi[end], (size_t)nf * g.Bp * sizeof(int))) != HELM_OK)
+            return st;
     HIPCHK(hipMemsetAsync(H->d_err, 0, sizeof(int), H->st));
     // timed as one unit, like the complex64 route
-    hipError_t e = TIMED(H, helm::K_FACTOR_CHUNKS, [&]() -> hipError_t {
-        hipError_t r = hipSuccess;
-        for (int l = 0; l < g.Ny && r == hipSuccess; ++l) {
-            void* out = static_cast<char*>(F) + (size_t)l * BB * esz;
-            r = helm::launch_factor3_plane(a, l, l > 0 ? G64 : nullptr, S, Tm, Cm, perm, pi, H->d_err, G64, out,
-                                           single, (size_t)g.Ny * BB, H->st);
-        }
-        return r;
-    }());
+    hipError_t e = TIMED(H, helm::K_FACTOR_CHUNKS, two_ends([&](int l, int end, hipStream_t q) {
+        if (l == p && end == 1) return hipSuccess;
+        const double2* low = end == 0 && l > 0 ? G64[0] : nullptr;
+        const double2* up = l == p || (end == 1 && l < g.Ny - 1) ? G64[1] : nullptr;
+        void* out = static_cast<char*>(F) + (size_t)l * BB * esz;
+        return helm::launch_factor3_plane(a, l, low, up, S[end], Tm[end], Cm[end], perm[end], pi[end], H->d_err,
+                                          l == p ? nullptr : G64[end], out, single, (size_t)g.Ny * BB, q);
+    }));
     HIPCHK(e);
     herr = 0;
     HIPCHK(hipMemcpyAsync(&herr, H->d_err, sizeof(int), hipMemcpyDeviceToHost, H->st));
     HIPCHK(hipStreamSynchronize(H->st));
     if (single && !herr) {
         // S (nf Bp^2 complex128 entries) is free now and holds the panel scratch
-        HIPCHK(panelize(F, S));
+        HIPCHK(panelize(F, S[0]));
         HIPCHK(hipStreamSynchronize(H->st));
     }
     if (herr) return fail(H, HELM_ESINGULAR, "zero or non-finite pivot in a slab factorisation");
@@ -3072,8 +3064,7 @@ void helm_destroy(helm_t H) {
         if (q) (void)hipStreamDestroy(q);
     for (hipEvent_t e : H->ev_c)
         if (e) (void)hipEventDestroy(e);
-    for (hipStream_t q : H->st_fac)
-        if (q) (void)hipStreamDestroy(q);
+    if (H->st_fac) (void)hipStreamDestroy(H->st_fac);
     free_work(H);
     delete H->timer;
     if (H->F != H->F64) dfree(H, H->F);

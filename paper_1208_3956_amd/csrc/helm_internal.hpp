@@ -197,6 +197,9 @@ constexpr int IWIN = 5;
 
 // ---- 3-D slabs (kernels_3d.hip)
 constexpr int BP3_MAX = 8192;   // largest padded slab block
+// the plane at which the eliminations from both ends of a slab meet: the upper end (N_y - 1 -
+// slab_mid planes) is done at least a step before the lower one
+inline int slab_mid(int Ny) { return (Ny + 1) / 2; }
 
 struct Fac3Args {
     int J, Ny, Nz, Nx, Bp;
@@ -321,24 +324,25 @@ hipError_t launch_sum_diff(const double2* x, const double2* y, const double2* z,
                            hipStream_t st);
 int dots_blocks(long n);
 
-// one plane l of the 3-D slab factorisation for every slab: S = T_l - c_l b_{l-1} Gprev,
-// inverted in place by blocked Gauss-Jordan; the inverse goes to G64 (FP64, may be null)
+// one plane l of the 3-D slab factorisation for every slab: S = T_l - c_l b_{l-1} Glow
+// - b_l c_{l+1} Gup (null: no such term), inverted in place by blocked Gauss-Jordan; the inverse goes to G64 (FP64, may be null)
 // and to out + s * out_stride (complex64 if out_single, else complex128)
-hipError_t launch_factor3_plane(const Fac3Args& a, int l, const double2* Gprev, double2* S,
+hipError_t launch_factor3_plane(const Fac3Args& a, int l, const double2* Glow, const double2* Gup, double2* S,
                                 double2* Tm, double2* Cm, int* perm, int* pi, int* err,
                                 double2* G64, void* out, bool out_single, size_t out_stride,
                                 hipStream_t st);
 size_t factor3_panel_width();
 // complex64 slab factorisation (mixed precision): blocked Gauss-Jordan in place in the
 // stored factor F ([slab][plane][Bp*Bp], slab stride `stride`), one plane of the slabs
-// s0 .. s0 + ns - 1 per call (disjoint slab sets may run on different streams)
+// s0 .. s0 + ns - 1 per call (disjoint slab sets, or planes with work of their own, may run on
+// different streams); low, up: the neighbour planes already inverted
 size_t factor3_f32_work_bytes(int J, int Bp);
 // stored complex64 slab inverses (J slots of Ny planes, slot stride `stride`) rewritten,
 // plane by plane, from column-major into the 16-row panels the sweeps read; work holds
 // J Bp^2 complex64 entries
 hipError_t launch_factor3_panelize(float2* F, size_t stride, int J, int Ny, int Bp, float2* work, hipStream_t st);
 hipError_t launch_factor3_plane_f32(const Fac3Args& a, int l, float2* F, size_t stride, void* work, int* err,
-                                    hipStream_t st, int s0, int ns);
+                                    hipStream_t st, int s0, int ns, bool low, bool up);
 template <typename T>
 hipError_t launch_strip_solve3(const Solve3Args<T>& a, hipStream_t st, KTimer* kt);
 

@@ -5,10 +5,15 @@
 // unknowns (x, z) of the plane y = l, element k = z * W + x.  Its diagonal block T_l is
 // the x- and z-part of the stencil plus the y-diagonal and -k^2; the couplings to the
 // planes l -/+ 1 are the scalars c_l, b_l (the y-PML depends on y only).  Block LU along
-// y (Algorithm 1 with blocks for rows):
-//     S_0 = T_0,  S_l = T_l - c_l b_{l-1} S_{l-1}^{-1},  G_l = S_l^{-1}
-//     forward   y_l = G_l (r_l - c_l y_{l-1})
-//     backward  x_l = y_l - b_l G_l x_{l+1}
+// y from both ends to a middle plane p (Algorithm 1 with blocks for rows), G_l = S_l^{-1}:
+//     below  S_l = T_l - c_l b_{l-1} G_{l-1},   y_l = G_l (r_l - c_l y_{l-1})
+//     above  S_l = T_l - b_l c_{l+1} G_{l+1},   y_l = G_l (r_l - b_l y_{l+1})
+//     S_p = T_p - c_p b_{p-1} G_{p-1} - b_p c_{p+1} G_{p+1},
+//     x_p = G_p (r_p - c_p y_{p-1} - b_p y_{p+1})
+//     below  x_l = y_l - b_l G_l x_{l+1},       above  x_l = y_l - c_l G_l x_{l-1}
+// The two ends advance together: one launch per pair of planes, N_y + 1 dependent steps
+// instead of 2 N_y - 1, each with twice the tiles (a single plane's leave two thirds of the
+// chip idle), for the same operations.
 // The blocks are dense (B = W N_z up to ~2000), so the explicit inverses are computed in
 // FP64 by blocked Gauss-Jordan elimination with partial pivoting over the whole column:
 // per panel of NB columns one workgroup per slab reduces the panel (pivot search, row
@@ -39,24 +44,24 @@ __device__ inline double2 cdiv(double2 a, double2 b) {
     return make_double2((a.x * b.x + a.y * b.y) / d, (a.y * b.x - a.x * b.y) / d);
 }
 
-// S = T_l - c_l b_{l-1} G_{l-1}  on every slab, identity on the padding
-__global__ void __launch_bounds__(256) k3_build_S(Fac3Args a, int l, const double2* __restrict__ Gprev,
-                                                  double2* __restrict__ S) {
+// S = T_l - c_l b_{l-1} Glow - b_l c_{l+1} Gup (null: no such term) on every slab, identity on
+// the padding
+__global__ void __launch_bounds__(256) k3_build_S(Fac3Args a, int l, const double2* __restrict__ Glow,
+                                                  const double2* __restrict__ Gup, double2* __restrict__ S) {
     const int s = blockIdx.y;
     const size_t BB = (size_t)a.Bp * a.Bp;
     const int W = a.sW[s], B = W * a.Nz;
-    double2 cb = make_double2(0.0, 0.0);
-    if (l > 0) cb = cmul(a.cy[l], a.by[l - 1]);
+    double2 cb = make_double2(0.0, 0.0), bc = cb;
+    if (Glow) cb = cmul(a.cy[l], a.by[l - 1]);
+    if (Gup) bc = cmul(a.by[l], a.cy[l + 1]);
     const double2 ay = a.ay[l], ayp = a.ayh[l + 1], aym = a.ayh[l];
     const double2 ydiag = cmul(ay, cadd(ayp, aym));
     for (size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x; e < BB; e += (size_t)gridDim.x * blockDim.x) {
         const int col = (int)(e / a.Bp), row = (int)(e % a.Bp);
         double2 v = make_double2(0.0, 0.0);
         if (row < B && col < B) {
-            if (l > 0) {
-                const double2 gp = Gprev[(size_t)s * BB + e];
-                v = cmk<double2>(-(cb.x * gp.x - cb.y * gp.y), -(cb.x * gp.y + cb.y * gp.x));
-            }
+            if (Glow) v = csub(v, cmul(cb, Glow[(size_t)s * BB + e]));
+            if (Gup) v = csub(v, cmul(bc, Gup[(size_t)s * BB + e]));
             const int xr = row % W, zr = row / W, xc = col % W, zc = col / W;
             const double2* sax = a.sax + (size_t)s * WP;
             const double2* saxh = a.saxh + (size_t)s * (WP + 1);
@@ -428,34 +433,37 @@ __device__ inline void scatter3(const Solve3Args<T>& a, int r, int l, int k, cpl
 
 typedef float mf4 __attribute__((ext_vector_type(4)));
 
-// Right-hand side of plane 0: Tw[i][r] = r_0(i, r), zero on the padding rows and on the
-// right-hand-side columns beyond nrhs.
+// Right-hand sides of the first planes of both ends: Tw[i][r] = r_0(i, r), and r_{Ny-1} in
+// the slot below plane Ny - 1 (k3_fwd), zero on the padding rows and on the right-hand-side
+// columns beyond nrhs.
 template <typename T>
 __global__ void __launch_bounds__(256) k3_rhs0(Solve3Args<T> a, cplx<T>* __restrict__ Tw) {
     const size_t e = (size_t)blockIdx.x * 256 + threadIdx.x;
     if (e >= (size_t)a.Bp * a.RP) return;
     const int i = (int)(e / a.RP), r = (int)(e % a.RP);
-    Tw[pidx<T>(i, r, a.RP)] = (i < a.B && r < a.nrhs) ? gather3<T>(a, r, 0, i) : cmk<cplx<T>>(0, 0);
+    const bool live = i < a.B && r < a.nrhs;
+    const size_t at = pidx<T>(i, r, a.RP);
+    Tw[at] = live ? gather3<T>(a, r, 0, i) : cmk<cplx<T>>(0, 0);
+    a.Yw[(size_t)(a.Ny - 2) * a.Bp * a.RP + at] = live ? gather3<T>(a, r, a.Ny - 1, i) : cmk<cplx<T>>(0, 0);
 }
 
-// Z = G X for a 16-row x 16-column tile: G Bp x Bp, column-major (complex128) or in 16-row
+// z = G X for a 16-row x 16-column tile: G Bp x Bp, column-major (complex128) or in 16-row
 // panels (complex64: entry (i, k) at (i / 16) 16 Bp + 32 (k / 2) + 2 (i % 16) + k % 2, so
 // that the 16 rows of a tile are one contiguous run of 16 Bp entries and each row's pairs of
-// k are adjacent), X a plane vector (pidx).  The k range
-// is cut into blocks of 16; wave w of NW3 takes blocks w, w + NW3, ... (several waves per
-// SIMD hide the load latency; each wave also loads its next block before it multiplies
-// the current one).  The NW3 partial tiles are added through LDS.  Returns, for thread
-// t < 256, the entry (row t / 16, column t % 16) of the tile.
-// complex64: v_mfma_f32_16x16x4f32, three real products per complex one (Gauss's form;
-// lane layout A[l % 16][l / 16], B[l / 16][l % 16], C[4 (l / 16) + j][l % 16] in
-// component j).
+// k are adjacent), X a plane vector (pidx).
+//
+// Blocks of 16 k are dealt to the NW3 waves, whose partial tiles meet in LDS.
+// complex64: v_mfma_f32_16x16x4f32, three real products per complex one (Gauss's form; lane
+// layout A[l % 16][l / 16], B[l / 16][l % 16], C[4 (l / 16) + j][l % 16] in component j).
+// complex128: v_mfma_f64_16x16x4f64, four real products, rows l / 16 + 4 j of C (the FMA form
+// it replaces loaded every operand four times and took 34 us a plane at Bp = 704).
 constexpr int NW3 = 16;
 constexpr int NT3 = 64 * NW3;
+typedef double md4 __attribute__((ext_vector_type(4)));
 
-__device__ inline float2 tile_product(const float2* __restrict__ G, const float2* __restrict__ X, int Bp,
-                                      int RP, int i0, int r0, float2 (*red)[16][16]) {
+__device__ inline void tile_part(const float2* __restrict__ G, const float2* __restrict__ X, int Bp, int RP, int i0,
+                                 int r0, float2 (*red)[16][16]) {
     const int t = threadIdx.x, lane = t & 63, w = t >> 6, n = lane & 15, q4 = lane >> 4;
-    const int nblk = Bp / 16;
     // complex products from three real ones: x1 = sum Gr Xr, x2 = sum Gi Xi,
     // x3 = sum (Gr + Gi)(Xr + Xi); Re = x1 - x2, Im = x3 - x1 - x2 (two chains of each for
     // independent MFMAs)
@@ -474,6 +482,7 @@ __device__ inline float2 tile_product(const float2* __restrict__ G, const float2
         xx[0] = make_float2(x01.x, x01.y); xx[1] = make_float2(x01.z, x01.w);
         xx[2] = make_float2(x23.x, x23.y); xx[3] = make_float2(x23.z, x23.w);
     };
+    const int nblk = Bp / 16;
     if (w < nblk) load(w, g, x);
     for (int b = w; b < nblk; b += NW3) {
         const int bn = b + NW3 < nblk ? b + NW3 : b;     // clamped: the last prefetch is a re-read
@@ -495,86 +504,115 @@ __device__ inline float2 tile_product(const float2* __restrict__ G, const float2
         const float p1 = x1a[j] + x1b[j], p2 = x2a[j] + x2b[j], p3 = x3a[j] + x3b[j];
         red[w][4 * q4 + j][n] = make_float2(p1 - p2, p3 - p1 - p2);
     }
-    __syncthreads();
-    float2 z = make_float2(0.f, 0.f);
-    if (t < 256) {
-        const int i = t >> 4, c = t & 15;
-#pragma unroll
-        for (int v = 0; v < NW3; ++v) { z.x += red[v][i][c].x; z.y += red[v][i][c].y; }
-    }
-    return z;
 }
 
-// complex128: FMA, each lane four rows (4 (l / 16) + j) of one column (l % 16)
-__device__ inline double2 tile_product(const double2* __restrict__ G, const double2* __restrict__ X, int Bp,
-                                       int RP, int i0, int r0, double2 (*red)[16][16]) {
+__device__ inline void tile_part(const double2* __restrict__ G, const double2* __restrict__ X, int Bp, int RP, int i0,
+                                 int r0, double2 (*red)[16][16]) {
     const int t = threadIdx.x, lane = t & 63, w = t >> 6, n = lane & 15, q4 = lane >> 4;
-    const int nblk = Bp / 16;
-    double2 acc[4];
+    md4 cr = {0.0, 0.0, 0.0, 0.0}, ci = cr;
+    // k-step u of block b: lane (n, q4) takes k = 16 b + 4 u + q4
+    const double2* gp = G + (size_t)q4 * Bp + i0 + n;
+    const double2* xp = X + (size_t)q4 * RP + r0 + n;
+    double2 g[4], x[4], gn[4], xn[4];
+    auto load = [&](int b, double2 (&gg)[4], double2 (&xx)[4]) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc[j] = make_double2(0.0, 0.0);
-    const double2* gp = G + i0 + 4 * q4;
-    const double2* xp = X + r0 + n;
-    for (int b = w; b < nblk; b += NW3) {
-#pragma unroll 4
-        for (int kk = 0; kk < 16; ++kk) {
-            const int k = 16 * b + kk;
-            const double2 xv = xp[(size_t)k * RP];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) cfma(acc[j], gp[(size_t)k * Bp + j], xv);
+        for (int u = 0; u < 4; ++u) {
+            gg[u] = gp[(size_t)(16 * b + 4 * u) * Bp];
+            xx[u] = xp[(size_t)(16 * b + 4 * u) * RP];
         }
+    };
+    const int nblk = Bp / 16;
+    if (w < nblk) load(w, g, x);
+    for (int b = w; b < nblk; b += NW3) {
+        load(b + NW3 < nblk ? b + NW3 : b, gn, xn);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            cr = __builtin_amdgcn_mfma_f64_16x16x4f64(g[u].x, x[u].x, cr, 0, 0, 0);
+            ci = __builtin_amdgcn_mfma_f64_16x16x4f64(g[u].x, x[u].y, ci, 0, 0, 0);
+            cr = __builtin_amdgcn_mfma_f64_16x16x4f64(-g[u].y, x[u].y, cr, 0, 0, 0);
+            ci = __builtin_amdgcn_mfma_f64_16x16x4f64(g[u].y, x[u].x, ci, 0, 0, 0);
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) { g[u] = gn[u]; x[u] = xn[u]; }
     }
 #pragma unroll
-    for (int j = 0; j < 4; ++j) red[w][4 * q4 + j][n] = acc[j];
-    __syncthreads();
-    double2 z = make_double2(0.0, 0.0);
-    if (t < 256) {
-        const int i = t >> 4, c = t & 15;
-#pragma unroll
-        for (int v = 0; v < NW3; ++v) { z.x += red[v][i][c].x; z.y += red[v][i][c].y; }
-    }
-    return z;
+    for (int j = 0; j < 4; ++j) red[w][q4 + 4 * j][n] = make_double2(cr[j], ci[j]);
 }
 
-// Forward plane l: y_l = G_l Tw_l, kept in Yw[l]; the tile's rows of the next right-hand
-// side Tn = r_{l+1} - c_{l+1} y_l are formed here (the last plane scatters x = y instead).
+// The tile's product in z (entry row t / 16, column t % 16) for threads t < 256; false for the
+// others.  Grid (tiles, right-hand-side groups, ends).
 template <typename T>
-__global__ void __launch_bounds__(NT3) k3_fwd(Solve3Args<T> a, int l, const cplx<T>* __restrict__ Tw,
-                                             cplx<T>* __restrict__ Tn) {
+__device__ inline bool tile_product(const Solve3Args<T>& a, const cplx<T>* __restrict__ G,
+                                    const cplx<T>* __restrict__ X, int i0, int r0, cplx<T>& z) {
+    __shared__ cplx<T> red[NW3][16][16];
+    const int t = threadIdx.x;
+    tile_part(G, X, a.Bp, a.RP, i0, r0, red);
+    __syncthreads();
+    if (t >= 256) return false;
+    const int i = t >> 4, c = t & 15;
+    z = cmk<cplx<T>>(0, 0);
+#pragma unroll
+    for (int v = 0; v < NW3; ++v) z = cadd(z, red[v][i][c]);
+    return true;
+}
+
+// Forward step k: plane k from below and, while the upper end has planes left (grid z), plane
+// Ny - 1 - k from above: y_l = G_l t_l, kept in Yw[l], with t_l the right-hand side less the
+// coupling to the plane before; the tile's rows of the next plane's t are formed here.  From
+// below t alternates between the two planes of Tw; from above t_l is in the slot of plane
+// l - 1, still unused.  The upper end is done a step or two before the lower one: it leaves
+// r_p - b_p y_{p+1} of the middle plane p in slot p - 1, where the lower end's last plane
+// picks it up before it stores its own y.
+template <typename T>
+__global__ void __launch_bounds__(NT3) k3_fwd(Solve3Args<T> a, int k, int p) {
     using V = cplx<T>;
-    __shared__ V red[NW3][16][16];
     const int i0 = blockIdx.x * 16, r0 = blockIdx.y * 16;
-    const V y = tile_product(a.F + (size_t)l * a.Bp * a.Bp, Tw, a.Bp, a.RP, i0, r0, red);
-    if (threadIdx.x >= 256) return;
+    const bool up = blockIdx.z == 1;                      // from above
+    const int l = up ? a.Ny - 1 - k : k;
+    const size_t plane = (size_t)a.Bp * a.RP;
+    const V* X = up ? a.Yw + (size_t)(l - 1) * plane : a.Tw + (k & 1) * plane;
+    V y;
+    if (!tile_product(a, a.F + (size_t)l * a.Bp * a.Bp, X, i0, r0, y)) return;
     const int i = i0 + (threadIdx.x >> 4), r = r0 + (threadIdx.x & 15);
     const size_t at = pidx<T>(i, r, a.RP);
-    a.Yw[(size_t)l * a.Bp * a.RP + at] = y;
     const bool live = i < a.B && r < a.nrhs;
-    if (l + 1 < a.Ny) {
-        V tn = cmk<V>(0, 0);
-        if (live) {
-            const double2 c = a.cy[l + 1];
-            tn = csub(gather3<T>(a, r, l + 1, i), cmul(ccast<V>(c), y));
-        }
-        Tn[at] = tn;
-    } else if (live) {
-        scatter3<T>(a, r, l, i, y);
-    }
+    V* yl = a.Yw + (size_t)l * plane + at;
+    const int ln = up ? l - 1 : l + 1;
+    V tn = cmk<V>(0, 0);
+    if (!up && ln == p) tn = *yl;
+    else if (live) tn = gather3<T>(a, r, ln, i);
+    if (live) tn = csub(tn, cmul(ccast<V>(up ? a.by[ln] : a.cy[ln]), y));
+    *yl = y;
+    (up ? a.Yw + (size_t)(l - 2) * plane : a.Tw + ((k + 1) & 1) * plane)[at] = tn;
 }
 
-// Backward plane l: x_l = y_l - b_l G_l x_{l+1}, kept in Yw[l] and scattered.
+// The middle plane: x_p = G_p t_p, kept and scattered.
 template <typename T>
-__global__ void __launch_bounds__(NT3) k3_bwd(Solve3Args<T> a, int l) {
-    using V = cplx<T>;
-    __shared__ V red[NW3][16][16];
+__global__ void __launch_bounds__(NT3) k3_mid(Solve3Args<T> a, int p) {
     const int i0 = blockIdx.x * 16, r0 = blockIdx.y * 16;
     const size_t plane = (size_t)a.Bp * a.RP;
-    const V z = tile_product(a.F + (size_t)l * a.Bp * a.Bp, a.Yw + (size_t)(l + 1) * plane, a.Bp, a.RP,
-                             i0, r0, red);
-    if (threadIdx.x >= 256) return;
+    cplx<T> x;
+    if (!tile_product(a, a.F + (size_t)p * a.Bp * a.Bp, a.Tw + (p & 1) * plane, i0, r0, x)) return;
+    const int i = i0 + (threadIdx.x >> 4), r = r0 + (threadIdx.x & 15);
+    a.Yw[(size_t)p * plane + pidx<T>(i, r, a.RP)] = x;
+    if (i < a.B && r < a.nrhs) scatter3<T>(a, r, p, i, x);
+}
+
+// Backward step k: x_l = y_l - b_l G_l x_{l+1} at plane l = p - 1 - k and, from above,
+// x_l = y_l - c_l G_l x_{l-1} at l = p + 1 + k, kept in Yw[l] and scattered.
+template <typename T>
+__global__ void __launch_bounds__(NT3) k3_bwd(Solve3Args<T> a, int k, int p) {
+    using V = cplx<T>;
+    const int i0 = blockIdx.x * 16, r0 = blockIdx.y * 16;
+    const bool up = blockIdx.z == 1;
+    const int l = up ? p + 1 + k : p - 1 - k;
+    const size_t plane = (size_t)a.Bp * a.RP;
+    V z;
+    if (!tile_product(a, a.F + (size_t)l * a.Bp * a.Bp, a.Yw + (size_t)(up ? l - 1 : l + 1) * plane, i0, r0, z))
+        return;
     const int i = i0 + (threadIdx.x >> 4), r = r0 + (threadIdx.x & 15);
     V* yl = a.Yw + (size_t)l * plane + pidx<T>(i, r, a.RP);
-    const V x = csub(*yl, cmul(ccast<V>(a.by[l]), z));
+    const V x = csub(*yl, cmul(ccast<V>(up ? a.cy[l] : a.by[l]), z));
     *yl = x;
     if (i < a.B && r < a.nrhs) scatter3<T>(a, r, l, i, x);
 }
@@ -615,13 +653,13 @@ hipError_t launch_factor3_panelize(float2* F, size_t stride, int J, int Ny, int 
     return hipGetLastError();
 }
 
-hipError_t launch_factor3_plane(const Fac3Args& a, int l, const double2* Gprev, double2* S,
+hipError_t launch_factor3_plane(const Fac3Args& a, int l, const double2* Glow, const double2* Gup, double2* S,
                                 double2* Tm, double2* Cm, int* perm, int* pi, int* err,
                                 double2* G64, void* out, bool out_single, size_t out_stride,
                                 hipStream_t st) {
     const size_t BB = (size_t)a.Bp * a.Bp;
     unsigned nb = (unsigned)std::min<size_t>((BB + 255) / 256, 4096);
-    hipLaunchKernelGGL(k3_build_S, dim3(nb, a.J), dim3(256), 0, st, a, l, Gprev, S);
+    hipLaunchKernelGGL(k3_build_S, dim3(nb, a.J), dim3(256), 0, st, a, l, Glow, Gup, S);
     for (int k0 = 0; k0 < a.Bp; k0 += NB) {
         if (a.Bp <= BPI_MAX)
             hipLaunchKernelGGL(k3_gj_panel_lds, dim3(a.J), dim3(NTI), 0, st, S, a.Bp, k0, perm, err);
@@ -642,13 +680,14 @@ hipError_t launch_factor3_plane(const Fac3Args& a, int l, const double2* Gprev, 
 
 template <typename T>
 hipError_t launch_strip_solve3(const Solve3Args<T>& a, hipStream_t st, KTimer* kt) {
-    dim3 grid(a.Bp / 16, a.RP / 16);
-    cplx<T>* Tw[2] = {a.Tw, a.Tw + (size_t)a.Bp * a.RP};
+    const int p = slab_mid(a.Ny), nu = a.Ny - 1 - p;      // the upper end has nu planes, fewer than p
+    if (nu < 1) return hipErrorInvalidValue;
+    const dim3 g1(a.Bp / 16, a.RP / 16, 1), g2(a.Bp / 16, a.RP / 16, 2);
     if (kt) kt->begin(K_PHASE_A, st);
-    hipLaunchKernelGGL(k3_rhs0<T>, dim3((unsigned)(((size_t)a.Bp * a.RP + 255) / 256)), dim3(256), 0, st, a, Tw[0]);
-    for (int l = 0; l < a.Ny; ++l)
-        hipLaunchKernelGGL(k3_fwd<T>, grid, dim3(NT3), 0, st, a, l, Tw[l & 1], Tw[(l + 1) & 1]);
-    for (int l = a.Ny - 2; l >= 0; --l) hipLaunchKernelGGL(k3_bwd<T>, grid, dim3(NT3), 0, st, a, l);
+    hipLaunchKernelGGL(k3_rhs0<T>, dim3((unsigned)(((size_t)a.Bp * a.RP + 255) / 256)), dim3(256), 0, st, a, a.Tw);
+    for (int k = 0; k < p; ++k) hipLaunchKernelGGL(k3_fwd<T>, k < nu ? g2 : g1, dim3(NT3), 0, st, a, k, p);
+    hipLaunchKernelGGL(k3_mid<T>, g1, dim3(NT3), 0, st, a, p);
+    for (int k = 0; k < p; ++k) hipLaunchKernelGGL(k3_bwd<T>, k < nu ? g2 : g1, dim3(NT3), 0, st, a, k, p);
     if (kt) kt->end(K_PHASE_A, st);
     return hipGetLastError();
 }

@@ -1,6 +1,7 @@
 // Complex64 slab factorisation of the mixed-precision 3-D path (the same block recursion
 // along y as the FP64 one, Sec. 2.2 with the 7-point stencil):
-//     S_0 = T_0,  S_l = T_l - c_l b_{l-1} G_{l-1},  G_l = S_l^{-1}.
+//     S_l = T_l - c_l b_{l-1} G_{l-1} - b_l c_{l+1} G_{l+1},  G_l = S_l^{-1},
+// with one of the two terms on the planes below and above the middle one, both on it.
 // Each S_l is built over its own slot of the stored factor and inverted in place by
 // blocked Gauss-Jordan elimination with pivoting only inside the 64 x 64 diagonal blocks:
 // for the column block K,
@@ -36,17 +37,18 @@ constexpr size_t WSTR = 8 * (size_t)BLK;   // FP64 scratch blocks
 constexpr size_t PSTR = 128 * 128;         // P
 __host__ __device__ inline size_t cstr(int Bp) { return (size_t)128 * Bp; }   // C and R
 
-// S_l = T_l - c_l b_{l-1} G_{l-1} into the plane-l slot of every slab (identity on the
-// padding); G_{l-1} is the previous plane's slot (already inverted).  T in FP64, rounded.
+// S_l = T_l - c_l b_{l-1} G_{l-1} (low) - b_l c_{l+1} G_{l+1} (up) into the plane-l slot of
+// every slab (identity on the padding); the neighbour planes' slots are already inverted.  T
+// in FP64, rounded.
 __global__ void __launch_bounds__(256) k3f_build_S(Fac3Args a, int l, float2* __restrict__ F, size_t stride,
-                                                  int s0) {
+                                                  int s0, int low, int up) {
     const int s = s0 + blockIdx.y;
     const size_t BB = (size_t)a.Bp * a.Bp;
     const int W = a.sW[s], B = W * a.Nz;
     float2* S = F + s * stride + (size_t)l * BB;
-    const float2* Gp = l > 0 ? S - BB : nullptr;
-    double2 cb = make_double2(0.0, 0.0);
-    if (l > 0) cb = cmul(a.cy[l], a.by[l - 1]);
+    double2 cb = make_double2(0.0, 0.0), bc = cb;
+    if (low) cb = cmul(a.cy[l], a.by[l - 1]);
+    if (up) bc = cmul(a.by[l], a.cy[l + 1]);
     const double2 ydiag = cmul(a.ay[l], cadd(a.ayh[l + 1], a.ayh[l]));
     const double2* sax = a.sax + (size_t)s * WP;
     const double2* saxh = a.saxh + (size_t)s * (WP + 1);
@@ -54,10 +56,8 @@ __global__ void __launch_bounds__(256) k3f_build_S(Fac3Args a, int l, float2* __
         const int col = (int)(e / a.Bp), row = (int)(e % a.Bp);
         double2 v = make_double2(0.0, 0.0);
         if (row < B && col < B) {
-            if (l > 0) {
-                const float2 gp = Gp[e];
-                v = cmk<double2>(-(cb.x * gp.x - cb.y * gp.y), -(cb.x * gp.y + cb.y * gp.x));
-            }
+            if (low) v = csub(v, cmul(cb, ccast<double2>((S - BB)[e])));
+            if (up) v = csub(v, cmul(bc, ccast<double2>((S + BB)[e])));
             const int xr = row % W, zr = row / W, xc = col % W, zc = col / W;
             double2 t = make_double2(0.0, 0.0);
             if (row == col) {
@@ -386,14 +386,14 @@ size_t factor3_f32_work_bytes(int J, int Bp) {
 // Bp is an odd multiple of 64).  A 128-wide block halves the passes of the update over the
 // matrices (the update is bound by HBM and MFMA about equally at 64).
 hipError_t launch_factor3_plane_f32(const Fac3Args& a, int l, float2* F, size_t stride, void* work, int* err,
-                                    hipStream_t st, int s0, int ns) {
+                                    hipStream_t st, int s0, int ns, bool low, bool up) {
     const size_t BB = (size_t)a.Bp * a.Bp;
     double2* Wd = static_cast<double2*>(work);
     float2* Pf = reinterpret_cast<float2*>(Wd + (size_t)a.J * WSTR);
     float2* Cb = Pf + (size_t)a.J * PSTR;
     float2* Rb = Cb + (size_t)a.J * cstr(a.Bp);
     const unsigned nbs = (unsigned)std::min<size_t>((BB + 255) / 256, 4096);
-    hipLaunchKernelGGL(k3f_build_S, dim3(nbs, ns), dim3(256), 0, st, a, l, F, stride, s0);
+    hipLaunchKernelGGL(k3f_build_S, dim3(nbs, ns), dim3(256), 0, st, a, l, F, stride, s0, low ? 1 : 0, up ? 1 : 0);
     const int nb = a.Bp / 64;
     const int total = ns * nb * nb, per = (total + 7) / 8;
     for (int k0 = 0; k0 < a.Bp;) {
