@@ -571,16 +571,19 @@ __global__ void __launch_bounds__(NT3) k3_fwd(Solve3Args<T> a, int k, int p) {
     const int l = up ? a.Ny - 1 - k : k;
     const size_t plane = (size_t)a.Bp * a.RP;
     const V* X = up ? a.Yw + (size_t)(l - 1) * plane : a.Tw + (k & 1) * plane;
-    V y;
-    if (!tile_product(a, a.F + (size_t)l * a.Bp * a.Bp, X, i0, r0, y)) return;
-    const int i = i0 + (threadIdx.x >> 4), r = r0 + (threadIdx.x & 15);
+    // the next plane's right-hand side, loaded before the product
+    const int i = i0 + ((threadIdx.x & 255) >> 4), r = r0 + (threadIdx.x & 15);
     const size_t at = pidx<T>(i, r, a.RP);
     const bool live = i < a.B && r < a.nrhs;
     V* yl = a.Yw + (size_t)l * plane + at;
     const int ln = up ? l - 1 : l + 1;
     V tn = cmk<V>(0, 0);
-    if (!up && ln == p) tn = *yl;
-    else if (live) tn = gather3<T>(a, r, ln, i);
+    if (threadIdx.x < 256) {
+        if (!up && ln == p) tn = *yl;
+        else if (live) tn = gather3<T>(a, r, ln, i);
+    }
+    V y;
+    if (!tile_product(a, a.F + (size_t)l * a.Bp * a.Bp, X, i0, r0, y)) return;
     if (live) tn = csub(tn, cmul(ccast<V>(up ? a.by[ln] : a.cy[ln]), y));
     *yl = y;
     (up ? a.Yw + (size_t)(l - 2) * plane : a.Tw + ((k + 1) & 1) * plane)[at] = tn;
@@ -607,12 +610,13 @@ __global__ void __launch_bounds__(NT3) k3_bwd(Solve3Args<T> a, int k, int p) {
     const bool up = blockIdx.z == 1;
     const int l = up ? p + 1 + k : p - 1 - k;
     const size_t plane = (size_t)a.Bp * a.RP;
+    const int i = i0 + ((threadIdx.x & 255) >> 4), r = r0 + (threadIdx.x & 15);
+    V* yl = a.Yw + (size_t)l * plane + pidx<T>(i, r, a.RP);
+    const V y = *yl;                                      // loaded before the product
     V z;
     if (!tile_product(a, a.F + (size_t)l * a.Bp * a.Bp, a.Yw + (size_t)(up ? l - 1 : l + 1) * plane, i0, r0, z))
         return;
-    const int i = i0 + (threadIdx.x >> 4), r = r0 + (threadIdx.x & 15);
-    V* yl = a.Yw + (size_t)l * plane + pidx<T>(i, r, a.RP);
-    const V x = csub(*yl, cmul(ccast<V>(up ? a.cy[l] : a.by[l]), z));
+    const V x = csub(y, cmul(ccast<V>(up ? a.cy[l] : a.by[l]), z));
     *yl = x;
     if (i < a.B && r < a.nrhs) scatter3<T>(a, r, l, i, x);
 }
