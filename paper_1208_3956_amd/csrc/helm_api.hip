@@ -853,7 +853,7 @@ helm_status red_sweep(helm_t H, int nrhs, bool up, const double2* psi, bool base
         else { a.oat[0] = right + 1; a.oat[1] = right + 2; a.oat[2] = left + 3; a.oat[3] = left + 4; }
         a.nout = 0;
         for (int o = 0; o < 5; ++o)
-            if (!last || o < 2) a.omap[a.nout++] = o;
+            if (!last || o < 2) a.omap |= (unsigned)o << 4 * a.nout++;
         a.p = panels + s * strip;
         a.pn = last ? nullptr : panels + (up ? s + 1 : s - 1) * strip;
         if (base) {

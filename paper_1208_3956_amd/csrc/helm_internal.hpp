@@ -374,7 +374,8 @@ struct RedArgs {
     // added to the outputs (null: nothing): base to dst, laid out alike; tc (trB - trA) of the
     // strip's own traces [rhs][row] to the next strip's entry 0
     const double2* base = nullptr; const double2* trA = nullptr; const double2* trB = nullptr; double tc = 0;
-    int omap[5] = {0, 0, 0, 0, 0}, nout = 0;   // active outputs (4: the next strip's entry 0)
+    unsigned omap = 0;            // active outputs, 4 bits each (4: the next strip's entry 0)
+    int nout = 0;
     int M = 0, Mp = 0, P = 0, ns = 0, Ny = 0, nrhs = 0, G = 0;
 };
 template <typename T>

@@ -37,16 +37,33 @@ constexpr int TI = 6;            // target columns / input columns per row of th
 typedef float mf4 __attribute__((ext_vector_type(4)));
 
 // ---------------------------------------------------------------- products of a strip solve
-template <typename T> struct Mfma;
-template <> struct Mfma<float> {
+// A product's tiles: 16 rows by W right-hand sides; element j of a lane's accumulator lies in
+// row row(lane, j), column lane % W.
+template <typename T> struct Wide;
+template <> struct Wide<float> {
     using acc = mf4;
+    static constexpr int W = 16, REGS = 4;
     static __device__ inline acc mul(float a, float b, acc c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
-    static __device__ inline int row(int q4, int j) { return 4 * q4 + j; }
+    static __device__ inline int row(int lane, int j) { return 4 * (lane >> 4) + j; }
+    static __device__ inline float get(const acc& c, int j) { return c[j]; }
 };
-template <> struct Mfma<double> {
+template <> struct Wide<double> {
     using acc = md4;
+    static constexpr int W = 16, REGS = 4;
     static __device__ inline acc mul(double a, double b, acc c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
-    static __device__ inline int row(int q4, int j) { return q4 + 4 * j; }
+    static __device__ inline int row(int lane, int j) { return (lane >> 4) + 4 * j; }
+    static __device__ inline double get(const acc& c, int j) { return c[j]; }
+};
+// four right-hand sides: the blocks of 4x4x4 are the tile's four groups of rows, so that the left
+// operand's layout is that of 16x16x4; sums over k in the same order (FP64 only: the FP32
+// form keeps a sum per k, so that a column's bits would depend on the panel's width)
+template <typename T> struct Quad;
+template <> struct Quad<double> {
+    using acc = double;
+    static constexpr int W = 4, REGS = 1;
+    static __device__ inline acc mul(double a, double b, acc c) { return __builtin_amdgcn_mfma_f64_4x4x4f64(a, b, c, 0, 0, 0); }
+    static __device__ inline int row(int lane, int) { return (lane & 12) + (lane >> 4); }
+    static __device__ inline double get(const acc& c, int) { return c; }
 };
 
 // the two k-steps of group gi in this lane
@@ -60,22 +77,28 @@ __device__ inline void load_group(const double2* p, int gi, int lane, double2 (&
     v[1] = p[((size_t)gi * 2 + 1) * 64 + lane];
 }
 
-// One 16-row tile of a product for NTR groups of 16 right-hand sides: the four waves take a
-// quarter of the k range each and add their tiles through LDS in a fixed order, so a
-// right-hand side's result depends neither on its neighbours nor on the panel's width.  Four
-// real products per complex one.  Operands come straight from memory, U k-groups (8 U values
-// of k) ahead of their products.
+// One 16-row tile of a product for NC column tiles of TL::W right-hand sides: the four waves
+// take a quarter of the k range each and add their tiles through LDS in a fixed order, so a
+// right-hand side's result does not depend on its neighbours.  Four real products per complex
+// one.  Operands come straight from memory, U k-groups (8 U values of k) ahead of their products.
 //   MODE 0  r^ = Rm p           tile = 4 separator + quarter
 //   MODE 1  x_s = Sm r^         tile = 4 separator + quarter
 //   MODE 2  outputs = Tm [p; x_s]   tile = (chunk, active output, 16-row group)
-template <typename T, int NTR, int MODE>
-__global__ void __launch_bounds__(NT) k_red_mul(RedArgs<T> a) {
+// The column tiles of a row tile follow each other on one XCD (blocks 8 apart), which reads
+// the matrix from memory once.
+template <typename T, typename TL, int NC, int MODE>
+__global__ void __launch_bounds__(NT) k_red_mul(RedArgs<T> a, int tiles, int nc) {
     using V = cplx<T>;
-    using MF = Mfma<T>;
-    constexpr int U = std::is_same<T, float>::value ? 4 : 2;
-    __shared__ V red[4][NTR][16][16];
-    const int t = threadIdx.x, lane = t & 63, w = t >> 6, n = lane & 15, q4 = lane >> 4;
-    const int tile = blockIdx.x, g0 = blockIdx.y * NTR;
+    constexpr int U = std::is_same<T, float>::value || (TL::W == 4 && NC == 1) ? 4 : 2, W = TL::W;
+    constexpr int CPG = 16 / W;                     // column tiles per group of right-hand sides
+    __shared__ V red[4][NC][16][W];
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+    const int tile = blockIdx.z * 8 + blockIdx.x, c0 = blockIdx.y * NC;
+    // all arguments at once: each is otherwise read where it is used, one scalar load's latency
+    // after the other (0.3 of 6 to 14 us a launch)
+    asm volatile("" ::"s"(a.A), "s"(a.p), "s"(a.pn), "s"(a.rh), "s"(a.xs), "s"(a.dst), "s"(a.dst_rs), "s"(a.dst_ls), "s"(a.base),
+                 "s"(a.trA), "s"(a.trB), "s"(a.omap), "s"(a.M), "s"(a.nrhs), "s"(tiles));
+    if (tile >= tiles) return;
     const int per = a.Mp / 16, KP = 3 * a.Mp;
     int c, o = 0, lg = 0, ng, nga;
     const V* A;
@@ -90,33 +113,35 @@ __global__ void __launch_bounds__(NT) k_red_mul(RedArgs<T> a) {
     } else {
         c = tile / (a.nout * per);
         const int rem = tile - c * a.nout * per;
-        o = a.omap[rem / per];
+        o = a.omap >> 4 * (rem / per) & 7;
         lg = rem % per;
         const int K = KP + (a.ns ? 2 * WP : 0);
         nga = KP / 8;
         ng = K / 8;
         A = a.A + ((size_t)(c * 5 + o) * per + lg) * 16 * K;
     }
-    const V* Bp[NTR];
-    const V* Bx[NTR];
+    const V* Bp[NC];
+    const V* Bx[NC];
+    int bl[NC];                                     // this lane's place in the panel's groups
 #pragma unroll
-    for (int u = 0; u < NTR; ++u) {
-        const int g = min(g0 + u, a.G - 1);
+    for (int u = 0; u < NC; ++u) {
+        const int ct = min(c0 + u, nc - 1), g = ct / CPG;
+        bl[u] = W == 16 ? lane : (lane & 48) + (ct % CPG) * W + lane % W;
         Bp[u] = MODE == 1 ? a.rh + (size_t)g * a.ns * WP * 16 : a.p + ((size_t)g * a.P + c) * KP * 16;
         Bx[u] = MODE == 2 ? a.xs + ((size_t)g * (a.ns + 2) + c) * WP * 16 - (size_t)nga * 128 : nullptr;
     }
     const int k0 = ng * w / 4, k1 = ng * (w + 1) / 4;
-    typename MF::acc cr[NTR], ci[NTR];
+    typename TL::acc cr[NC], ci[NC];
 #pragma unroll
-    for (int u = 0; u < NTR; ++u) { cr[u] = typename MF::acc{0, 0, 0, 0}; ci[u] = cr[u]; }
-    struct Stage { V a[U][2], b[U][NTR][2]; };
+    for (int u = 0; u < NC; ++u) { cr[u] = typename TL::acc{}; ci[u] = cr[u]; }
+    struct Stage { V a[U][2], b[U][NC][2]; };
     auto load = [&](Stage& s, int k) {
 #pragma unroll
         for (int i = 0; i < U; ++i) {
             const int gi = min(k + i, k1 - 1);
             load_group(A, gi, lane, s.a[i]);
 #pragma unroll
-            for (int u = 0; u < NTR; ++u) load_group(MODE == 2 && gi >= nga ? Bx[u] : Bp[u], gi, lane, s.b[i][u]);
+            for (int u = 0; u < NC; ++u) load_group(MODE == 2 && gi >= nga ? Bx[u] : Bp[u], gi, bl[u], s.b[i][u]);
         }
     };
     auto mul = [&](const Stage& s, int k) {
@@ -127,16 +152,16 @@ __global__ void __launch_bounds__(NT) k_red_mul(RedArgs<T> a) {
             for (int h = 0; h < 2; ++h) {
                 const V x = s.a[i][h];
 #pragma unroll
-                for (int u = 0; u < NTR; ++u) {
+                for (int u = 0; u < NC; ++u) {
                     const V y = s.b[i][u][h];
-                    cr[u] = MF::mul(x.x, y.x, cr[u]);
-                    ci[u] = MF::mul(x.x, y.y, ci[u]);
+                    cr[u] = TL::mul(x.x, y.x, cr[u]);
+                    ci[u] = TL::mul(x.x, y.y, ci[u]);
                 }
 #pragma unroll
-                for (int u = 0; u < NTR; ++u) {
+                for (int u = 0; u < NC; ++u) {
                     const V y = s.b[i][u][h];
-                    cr[u] = MF::mul(-x.y, y.y, cr[u]);
-                    ci[u] = MF::mul(x.y, y.x, ci[u]);
+                    cr[u] = TL::mul(-x.y, y.y, cr[u]);
+                    ci[u] = TL::mul(x.y, y.x, ci[u]);
                 }
             }
         }
@@ -152,16 +177,16 @@ __global__ void __launch_bounds__(NT) k_red_mul(RedArgs<T> a) {
         }
     }
 #pragma unroll
-    for (int u = 0; u < NTR; ++u)
+    for (int u = 0; u < NC; ++u)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) red[w][u][MF::row(q4, j)][n] = cmk<V>(cr[u][j], ci[u][j]);
+        for (int j = 0; j < TL::REGS; ++j)
+            red[w][u][TL::row(lane, j)][lane % W] = cmk<V>(TL::get(cr[u], j), TL::get(ci[u], j));
     __syncthreads();
-    const int row = t >> 4, rn = t & 15;
 #pragma unroll
-    for (int u = 0; u < NTR; ++u) {
-        const int g = g0 + u;
-        if (g >= a.G) break;
-        const V v = cadd(cadd(red[0][u][row][rn], red[1][u][row][rn]), cadd(red[2][u][row][rn], red[3][u][row][rn]));
+    for (int q = t; q < 16 * W * NC; q += NT) {
+        const int u = q / (16 * W), row = q / W % 16, ct = c0 + u, g = ct / CPG, rn = (ct % CPG) * W + q % W;
+        if (ct >= nc) break;
+        const V v = cadd(cadd(red[0][u][row][q % W], red[1][u][row][q % W]), cadd(red[2][u][row][q % W], red[3][u][row][q % W]));
         if (MODE == 0) {
             a.rh[(size_t)g * a.ns * WP * 16 + red_pos<T>(tile * 16 + row, rn)] = v;
         } else if (MODE == 1) {
@@ -739,10 +764,28 @@ __global__ void __launch_bounds__(NT) k_red_pack_r(RedBuild b, const double2* __
     }
 }
 
+template <typename T, typename TL, int NC, int MODE>
+void launch_mul_as(const RedArgs<T>& a, int tiles, int nc, hipStream_t st) {
+    hipLaunchKernelGGL((k_red_mul<T, TL, NC, MODE>), dim3(8, (nc + NC - 1) / NC, (tiles + 7) / 8), dim3(NT), 0, st, a, tiles,
+                       nc);
+}
+// Which tiles.  Up to 16 right-hand sides the 4 ns row tiles of Rm and Sm are fewer than the CUs
+// and bound by their waves' FP64 products (64 cycles each): tiles of four right-hand sides
+// make them 1/4 as long (1 right-hand side) or spread them over four times the CUs (16).  Sm
+// at 2032 rows, one right-hand side: 10.3 -> 7.4 us, Rm 8.9 -> 6.9; 1032 rows, 16: 12.1 -> 9.6 and
+// 6.4 -> 5.6.  Tm has tiles enough: four at a time only where there are no more (2032 rows: 19.7 ->
+// 15.9 us; with 8 right-hand sides at 532 rows 7.4 -> 10.8, with 16 at 1032 13.0 -> 22).  Beyond 16,
+// two groups of right-hand sides per workgroup read the matrix half as often, but not where the
+// groups are needed to fill the chip: Sm, Rm at 2032 rows and 64 right-hand sides 11.0, 10.1 us
+// with two, 7.2, 7.2 with one.
 template <typename T, int MODE>
 void launch_mul(const RedArgs<T>& a, int tiles, hipStream_t st) {
-    if (a.G > 1) hipLaunchKernelGGL((k_red_mul<T, 2, MODE>), dim3(tiles, (a.G + 1) / 2), dim3(NT), 0, st, a);
-    else hipLaunchKernelGGL((k_red_mul<T, 1, MODE>), dim3(tiles, 1), dim3(NT), 0, st, a);
+    if (a.G > 1 && (MODE == 2 || tiles * a.G > 512)) launch_mul_as<T, Wide<T>, 2, MODE>(a, tiles, a.G, st);
+    else if (a.G > 1) launch_mul_as<T, Wide<T>, 1, MODE>(a, tiles, a.G, st);
+    else if constexpr (std::is_same<T, double>::value) {
+        if (MODE != 2 || a.nrhs <= 4) launch_mul_as<T, Quad<T>, 1, MODE>(a, tiles, (a.nrhs + 3) / 4, st);
+        else launch_mul_as<T, Wide<T>, 1, MODE>(a, tiles, 1, st);
+    } else launch_mul_as<T, Wide<T>, 1, MODE>(a, tiles, 1, st);
 }
 
 }  // namespace

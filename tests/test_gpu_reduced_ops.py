@@ -79,6 +79,23 @@ def test_reduced_operator_keeps_right_hand_sides_apart(cases, prec):
     H.close()
 
 
+# panels of up to four, of up to 16 (tiles of four right-hand sides in FP64) and of several groups:
+# sums over fewer than 1000 products of FP64 (FP32) in any order
+@pytest.mark.parametrize("prec,tol", [("c128", 1e-12), ("mixed", 5e-4)])
+@pytest.mark.parametrize("n,J,chunk", [(30, 2, 9), (150, 5, 2), (150, 5, 9)])
+def test_reduced_operator_few_right_hand_sides(cases, prec, tol, n, J, chunk):
+    wl, g, A, S = cases[(n, J)]
+    H = _handle(wl, prec, "reduced", chunk)
+    rng = np.random.default_rng(chunk)
+    shape = (49, g.N_y, 2 * (g.J - 1))
+    psi = torch.from_numpy(rng.standard_normal(shape) + 1j * rng.standard_normal(shape)).to(DEV)
+    wide = H.apply_AP_reduced(psi)
+    for nrhs in (1, 2, 3, 4, 5, 8, 9, 13, 16, 17, 32):
+        got = H.apply_AP_reduced(psi[:nrhs].clone())
+        assert (got - wide[:nrhs]).abs().max() <= tol * wide.abs().max(), nrhs
+    H.close()
+
+
 # chunks of the strip solver: many (two-level separators), four (one separator chain), two, one
 @pytest.mark.parametrize("prec", ["c128", "mixed"])
 @pytest.mark.parametrize("mode", ["full", "reduced"])
