@@ -17,8 +17,17 @@ namespace gjr {
 // position step(i) (the step that pivoted on row i) and column j at position perm(j) (the row
 // pivoted at step j).  The columns cycle through the registers: after every four steps the
 // array is rotated by one register, so the column of the current step is always M[0].
+//
+// One workgroup and 64 dependent steps: a step is bound by its chain of the pivot row's lane reads
+// and products (about 750 clocks for 64 + 64 instructions), the search (270) and a barrier
+// with its round through LDS (280).  The wave that owns column k + 1 finds the pivot and forms
+// the multipliers for all waves after its update of step k, so there is one such round a step.
+// 53 -> 47 us for a 64 x 64 block (before: every wave's own multipliers with two divisions from a
+// second read of LDS, a 64-bit search, products waiting for the lane reads).  Deferring the
+// owner's update past the barrier took 56: the waves wait for it one step later.
 struct GJShared {
-    double2 fcol[2][WP];     // pivot column of the step (double-buffered: one barrier per step)
+    double2 f[2][WP];        // multipliers of the step (double-buffered: one barrier per step)
+    double2 inv[2];          // reciprocal pivot
     int piv[2];
     int perm[WP];
     double nrm[2][4];        // per wave: largest column 1-norm of the block, of its inverse
@@ -46,8 +55,25 @@ __device__ inline double wave_colnorm_max(const double2 (&M)[16]) {
     return best;
 }
 
-// wavefront maximum (device library; declared by the HIP headers only on request)
-extern "C" __device__ __attribute__((const)) unsigned long long __ockl_wfred_max_u64(unsigned long long);
+// wavefront maximum of 32-bit keys (row shifts, then broadcasts: lane 63 holds it)
+__device__ inline unsigned wave_max_u32(unsigned v) {
+#define HELM_DPP_MAX(ctrl) v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, ctrl, 0xf, 0xf, false))
+    HELM_DPP_MAX(0x111);
+    HELM_DPP_MAX(0x112);
+    HELM_DPP_MAX(0x114);
+    HELM_DPP_MAX(0x118);
+    HELM_DPP_MAX(0x142);
+    HELM_DPP_MAX(0x143);
+#undef HELM_DPP_MAX
+    return (unsigned)__builtin_amdgcn_readlane((int)v, 63);
+}
+
+// 1 / d of a normal d: the hardware's estimate and two Newton steps
+__device__ inline double recip(double d) {
+    double r = __builtin_amdgcn_rcp(d);
+    r = fma(fma(-d, r, 1.0), r, r);
+    return fma(fma(-d, r, 1.0), r, r);
+}
 
 // component-wise select (a select of whole double2 values goes through scratch memory)
 __device__ inline double2 sel(bool c, double2 a, double2 b) {
@@ -67,60 +93,74 @@ __device__ inline double readlane_f64(double v, int lane) {
 // finite, bit 2 when the 1-norm condition estimate exceeds cond_max.
 __device__ inline void gj_invert_store(double2 (&M)[16], int W, GJShared& sh, double2* __restrict__ dst,
                                 float2* __restrict__ dst32, int* err, double cond_max = GJ_COND_MAX) {
-    const int i = threadIdx.x & (WP - 1), g = threadIdx.x >> 6;
+    const int i = threadIdx.x & (WP - 1), g = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     bool used = i >= W;
     int my_step = i;                               // rows beyond W keep their position
     double2 my_inv = cmk<double2>(1.0, 0.0);
     int rot = 0;                                   // rotations done: M[r] holds column g + 4 (r + rot)
     {
         const double cn = wave_colnorm_max(M);
-        if ((threadIdx.x & 63) == 0) sh.nrm[0][g] = cn;
+        if (i == 0) sh.nrm[0][g] = cn;
     }
+    // pivot of column k (v: this lane's entry) among the unused rows and the step's multipliers.
+    // The key orders by the upper half of |v|^2, its low 6 bits replaced by 63 - row, so that
+    // near ties (6e-5) go to the lower row.
+    auto publish = [&](int k, double2 v) {
+        const int buf = k & 1;
+        const double mag = v.x * v.x + v.y * v.y;
+        const unsigned key = used ? 0u : ((unsigned)__double2hiint(mag) & ~63u) | (unsigned)(63 - i);
+        const int p = 63 - (int)(wave_max_u32(key) & 63u);
+        const double2 pv = cmk<double2>(readlane_f64(v.x, p), readlane_f64(v.y, p));
+        const double den = pv.x * pv.x + pv.y * pv.y;
+        const double rd = den > 0.0 ? recip(den) : 0.0;
+        const double2 inv = cmk<double2>(pv.x * rd, -pv.y * rd);
+        sh.f[buf][i] = sel(i == p, cmk<double2>(0.0, 0.0), cmul(v, inv));
+        if (i == 0) {
+            sh.piv[buf] = p;
+            sh.inv[buf] = inv;
+            sh.perm[k] = p;
+            if (!(den > 0.0 && isfinite(den))) atomicOr(err, 1);
+        }
+    };
+    if (g == 0) publish(0, M[0]);
+    __syncthreads();
     for (int kk = 0; 4 * kk < W; ++kk) {
 #pragma unroll
         for (int gg = 0; gg < 4; ++gg) {
             const int k = 4 * kk + gg;
             if (k < W) {
-                const int buf = k & 1;
-                if (g == gg) {
-                    // pivot search over the unused rows: the key orders by |m|^2 (its low 6
-                    // mantissa bits replaced by 63 - row, so ties go to the lower row)
-                    const double2 v = M[0];
-                    const double mag = v.x * v.x + v.y * v.y;
-                    const unsigned long long key =
-                        used ? 0ull : (((unsigned long long)__double_as_longlong(mag) & ~63ull) |
-                                       (unsigned long long)(63 - i));
-                    const unsigned long long best = __ockl_wfred_max_u64(key);
-                    sh.fcol[buf][i] = v;
-                    if (i == 0) {
-                        const int p = 63 - (int)(best & 63ull);
-                        sh.piv[buf] = p;
-                        sh.perm[k] = p;
-                    }
-                }
-                __syncthreads();
-                const int p = sh.piv[buf];
-                const double2 pv = sh.fcol[buf][p];
-                const double2 fk = sh.fcol[buf][i];
-                const double den = pv.x * pv.x + pv.y * pv.y;
-                if (threadIdx.x == 0 && !(den > 0.0 && isfinite(den))) atomicOr(err, 1);
-                const double2 inv = sel(den > 0.0, cmk<double2>(pv.x / den, -pv.y / den),
-                                        cmk<double2>(0.0, 0.0));
-                const double2 f = sel(i == p, cmk<double2>(0.0, 0.0), cmul(fk, inv));
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const double Rx = readlane_f64(M[r].x, p), Ry = readlane_f64(M[r].y, p);
-                    M[r].x = fma(-f.x, Rx, fma(f.y, Ry, M[r].x));
-                    M[r].y = fma(-f.x, Ry, fma(-f.y, Rx, M[r].y));
-                }
-                if (g == gg) {
-                    M[0] = sel(i == p, cmk<double2>(1.0, 0.0), cmk<double2>(-f.x, -f.y));
-                }
+                constexpr int next_reg[4] = {0, 0, 0, 1};
+                const int nr = next_reg[gg], buf = k & 1;     // column k + 1: wave (gg + 1) % 4, M[nr]
+                const int p = __builtin_amdgcn_readfirstlane(sh.piv[buf]);
+                const double2 f = sh.f[buf][i], inv = sh.inv[buf];
                 if (i == p) {
                     used = true;
                     my_step = k;
                     my_inv = inv;
                 }
+                // a column's lane reads two columns ahead of its last products, in this order
+                // (left to itself each product waits for the lane read before it)
+                double Rx[3], Ry[3], u[2][2];
+                auto column = [&](int r) {
+                    if (r < 16) {
+                        Rx[r % 3] = readlane_f64(M[r].x, p);
+                        Ry[r % 3] = readlane_f64(M[r].y, p);
+                    }
+                    if (r > 0 && r < 17) {
+                        u[r & 1][0] = fma(f.y, Ry[(r + 2) % 3], M[r - 1].x);
+                        u[r & 1][1] = fma(-f.y, Rx[(r + 2) % 3], M[r - 1].y);
+                    }
+                    if (r > 1) {
+                        M[r - 2].x = fma(-f.x, Rx[(r + 1) % 3], u[(r + 1) & 1][0]);
+                        M[r - 2].y = fma(-f.x, Ry[(r + 1) % 3], u[(r + 1) & 1][1]);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                };
+#pragma unroll
+                for (int r = 0; r < 18; ++r) column(r);
+                if (g == gg) M[0] = sel(i == p, cmk<double2>(1.0, 0.0), cmk<double2>(-f.x, -f.y));
+                if (g == ((gg + 1) & 3) && k + 1 < W) publish(k + 1, M[nr]);
+                __syncthreads();
             }
         }
         // rotate: the next four columns come to M[0]
