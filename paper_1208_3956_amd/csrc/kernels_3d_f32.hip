@@ -139,7 +139,7 @@ __global__ void __launch_bounds__(256) k3f_diag_inv128(const float2* __restrict_
                                                       int k0, double2* __restrict__ Wd, float2* __restrict__ Pf,
                                                       int* __restrict__ err, int s0) {
     __shared__ GJShared sh;
-    __shared__ double na[2][128], np[2][128];
+    __shared__ double na[4], np[4];
     const int s = s0 + blockIdx.x, t = threadIdx.x;
     const float2* A = F + s * stride + (size_t)l * Bp * Bp;
     double2* W = Wd + (size_t)s * WSTR;
@@ -149,6 +149,7 @@ __global__ void __launch_bounds__(256) k3f_diag_inv128(const float2* __restrict_
         const float2 v = A[(size_t)(k0 + c) * Bp + k0 + r];
         return make_double2(v.x, v.y);
     };
+#pragma unroll 8
     for (int e = t; e < BLK; e += 256) {
         const int r = e % WP, c = e / WP;
         A12[e] = at(r, 64 + c);
@@ -171,6 +172,7 @@ __global__ void __launch_bounds__(256) k3f_diag_inv128(const float2* __restrict_
     gemm64_mfma(A21, WP, P22, WP, T2, WP, mone, nullptr, 0);       // P21 = -P22 T2 (over A21)
     gemm64_mfma(P11, WP, P12, WP, T2, WP, mone, P11, WP);          // P11 = P11 - P12 T2
     float2* P = Pf + (size_t)s * PSTR;
+#pragma unroll 8
     for (int e = t; e < 128 * 128; e += 256) {
         const int r = e % 128, c = e / 128;
         const double2* src = r < 64 ? (c < 64 ? P11 : P12) : (c < 64 ? A21 : P22);
@@ -178,112 +180,140 @@ __global__ void __launch_bounds__(256) k3f_diag_inv128(const float2* __restrict_
         P[e] = make_float2((float)v.x, (float)v.y);
     }
     __syncthreads();
-    {
-        // column sums of |A_KK| and |P|: thread (column c, half h) sums 64 rows
-        const int c = t & 127, h = t >> 7;
-        double sa = 0.0, sp = 0.0;
+    // column 1-norms of A_KK and P, a column per wave at a time (a thread per column reads 128 lines
+    // at once: 30 us)
+    double ma = 0.0, mp = 0.0;
 #pragma unroll 4
-        for (int r = 64 * h; r < 64 * h + 64; ++r) {
+    for (int c = 32 * g; c < 32 * g + 32; ++c) {
+        double sa = 0.0, sp = 0.0;
+#pragma unroll
+        for (int r = i; r < 128; r += 64) {
             const double2 v = at(r, c);
-            sa += sqrt(v.x * v.x + v.y * v.y);
             const float2 q = P[(size_t)c * 128 + r];
+            sa += sqrt(v.x * v.x + v.y * v.y);
             sp += sqrt((double)q.x * q.x + (double)q.y * q.y);
         }
-        na[h][c] = sa;
-        np[h][c] = sp;
+        ma = fmax(ma, wave_sum(sa));
+        mp = fmax(mp, wave_sum(sp));
     }
+    if (i == 0) { na[g] = ma; np[g] = mp; }
     __syncthreads();
-    if (t < 64) {
-        double ma = fmax(na[0][t] + na[1][t], na[0][t + 64] + na[1][t + 64]);
-        double mp = fmax(np[0][t] + np[1][t], np[0][t + 64] + np[1][t + 64]);
-        for (int off = 32; off > 0; off >>= 1) {
-            ma = fmax(ma, __shfl_xor(ma, off));
-            mp = fmax(mp, __shfl_xor(mp, off));
-        }
-        if (t == 0 && !(ma * mp <= COND_MAX)) atomicOr(err, 2);
+    if (t == 0) {
+        for (int q = 1; q < 4; ++q) { ma = fmax(ma, na[q]); mp = fmax(mp, np[q]); }
+        if (!(ma * mp <= COND_MAX)) atomicOr(err, 2);
     }
 }
 
-// The operands of the update for the column block K = k0 .. k0 + NB - 1 (grid: 64-column
+// The operands of the update for the column block K = k0 .. k0 + NB - 1 (grid: RCW-column
 // tiles x slabs):
 //   C(i, k) = A(i, k0 + k) - [i = k0 + k]     rows of tile jt,  stored Cb[s][k][Bp]
 //   R(k, j) = sum_m P(k, m) A(k0 + m, j)      columns of tile jt, R(:, K) = P, Rb[s][k][Bp]
-// P is NB x NB, column-major (leading dimension NB).  The NB x 64 x NB product runs on
-// v_mfma_f32_16x16x4f32: wave w computes rows NB/4 w .. of R for the tile's 64 columns, P
-// read in lane layout from global memory, the A block from LDS (staged column by column).
+// P is NB x NB, column-major (leading dimension NB).  The NB x RCW x NB product runs on
+// v_mfma_f32_16x16x4f32: wave w computes NB/4 rows of R from NB/4 w on, P read in lane layout from
+// global memory eight k-steps ahead, the A block from LDS.  The two tiles of a pair hold the
+// even and the odd rows (columns), so that a lane's two operands (results) are one 16-byte access.
+// Bound by latency, one short round of workgroups: 32 columns, 2 to 3 workgroups a CU (15 slabs of
+// 1344 unknowns, 128 columns eliminated: 61 us with 64 columns and loads where they are
+// used, 38 us).
+constexpr int RCW = 32;                // columns of a workgroup of k3f_rc
 template <int NB>
 __global__ void __launch_bounds__(256) k3f_rc(const float2* __restrict__ F, size_t stride, int l, int Bp, int k0,
                                              const float2* __restrict__ Pf, float2* __restrict__ Cb,
                                              float2* __restrict__ Rb, int s0) {
-    constexpr int RW = NB / 64;        // 16-row MFMA tiles per wave
-    __shared__ float2 As[64][NB + 1];  // As[j][m] = A(k0 + m, J0 + j)
-    const int s = s0 + blockIdx.y, J0 = blockIdx.x * 64, t = threadIdx.x;
+    constexpr int NK = NB / 4, D = 8, CL = NB / 16, AL = RCW * NB / 512;
+    __shared__ float2 As[RCW][NB + 1];  // As[j][m] = A(k0 + m, J0 + j)
+    const int s = s0 + blockIdx.y, J0 = blockIdx.x * RCW, t = threadIdx.x;
     const float2* A = F + s * stride + (size_t)l * Bp * Bp;
     float2* cb = Cb + (size_t)s * cstr(Bp);
     float2* rb = Rb + (size_t)s * cstr(Bp);
     const float2* P = Pf + (size_t)s * PSTR;
-    // C rows of this tile
-    for (int e = t; e < NB * 64; e += 256) {
-        const int k = e / 64, ii = e % 64, i = J0 + ii;
-        float2 v = A[(size_t)(k0 + k) * Bp + i];
-        if (i == k0 + k) v.x -= 1.0f;
-        cb[(size_t)k * Bp + i] = v;
+    const bool own = J0 >= k0 && J0 < k0 + NB;
+    // C rows of this tile and the A block, two values a load, all loads before the first use
+    const int ci = J0 + 2 * (t & 15), ck = t >> 4, am = 2 * (t % (NB / 2)), aj = t / (NB / 2);
+    float4 cv[CL], xv[AL];
+#pragma unroll
+    for (int q = 0; q < AL; ++q)
+        xv[q] = *reinterpret_cast<const float4*>(A + (size_t)(J0 + aj + q * (512 / NB)) * Bp + k0 + am);
+#pragma unroll
+    for (int q = 0; q < CL; ++q) cv[q] = *reinterpret_cast<const float4*>(A + (size_t)(k0 + ck + 16 * q) * Bp + ci);
+#pragma unroll
+    for (int q = 0; q < AL; ++q) {
+        As[aj + q * (512 / NB)][am] = make_float2(xv[q].x, xv[q].y);
+        As[aj + q * (512 / NB)][am + 1] = make_float2(xv[q].z, xv[q].w);
     }
-    if (J0 >= k0 && J0 < k0 + NB) {
-        for (int e = t; e < NB * 64; e += 256) {
-            const int k = e / 64, jj = e % 64;
+#pragma unroll
+    for (int q = 0; q < CL; ++q) {
+        const int k = ck + 16 * q;
+        if (ci == k0 + k) cv[q].x -= 1.0f;
+        if (ci + 1 == k0 + k) cv[q].z -= 1.0f;
+        *reinterpret_cast<float4*>(cb + (size_t)k * Bp + ci) = cv[q];
+    }
+    if (own) {
+        for (int e = t; e < NB * RCW; e += 256) {
+            const int k = e / RCW, jj = e % RCW;
             rb[(size_t)k * Bp + J0 + jj] = P[(size_t)(J0 - k0 + jj) * NB + k];
         }
         return;
     }
-    for (int e = t; e < NB * 64; e += 256) {
-        const int jj = e / NB, mm = e % NB;
-        As[jj][mm] = A[(size_t)(J0 + jj) * Bp + k0 + mm];
-    }
     __syncthreads();
+    // wave w: NB / 4 rows, as pairs of 16-row tiles of even and odd rows where there are two
+    constexpr int RW = NB / 64;
     const int lane = t & 63, w = t >> 6, n = lane & 15, q4 = lane >> 4;
-    mf4 re[RW][4], im[RW][4];
+    mf4 re[RW][2], im[RW][2];
 #pragma unroll
     for (int ra = 0; ra < RW; ++ra)
 #pragma unroll
-        for (int jb = 0; jb < 4; ++jb) { re[ra][jb] = mf4{0.f, 0.f, 0.f, 0.f}; im[ra][jb] = re[ra][jb]; }
-    const float2* pp = P + (size_t)q4 * NB + 16 * RW * w + n;     // P(16 (RW w + ra) + n, 4 ks + q4)
-#pragma unroll 2
-    for (int ks = 0; ks < NB / 4; ++ks) {
-        float2 a[RW];
+        for (int jb = 0; jb < 2; ++jb) { re[ra][jb] = mf4{0.f, 0.f, 0.f, 0.f}; im[ra][jb] = re[ra][jb]; }
+    const float2* pp = P + (size_t)q4 * NB + 16 * RW * w + RW * n;     // P(RW (16 w + n) + ra, 4 ks + q4)
+    float2 a[D][RW];
+    auto load = [&](int d, int ks) {
+        const float2* q = pp + (size_t)4 * (ks < NK ? ks : NK - 1) * NB;
+        if constexpr (RW == 2) {
+            const float4 x = *reinterpret_cast<const float4*>(q);
+            a[d][0] = make_float2(x.x, x.y);
+            a[d][1] = make_float2(x.z, x.w);
+        } else {
+            a[d][0] = *q;
+        }
+    };
 #pragma unroll
-        for (int ra = 0; ra < RW; ++ra) a[ra] = pp[(size_t)4 * ks * NB + 16 * ra];
+    for (int d = 0; d < D - 1; ++d) load(d, d);
+    for (int kb = 0; kb < NK; kb += D)
 #pragma unroll
-        for (int jb = 0; jb < 4; ++jb) {
-            const float2 b = As[16 * jb + n][4 * ks + q4];
+        for (int d = 0; d < D; ++d) {
+            load((d + D - 1) % D, kb + d + D - 1);
 #pragma unroll
-            for (int ra = 0; ra < RW; ++ra) {
-                re[ra][jb] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[ra].x, b.x, re[ra][jb], 0, 0, 0);
-                im[ra][jb] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[ra].x, b.y, im[ra][jb], 0, 0, 0);
-                re[ra][jb] = __builtin_amdgcn_mfma_f32_16x16x4f32(-a[ra].y, b.y, re[ra][jb], 0, 0, 0);
-                im[ra][jb] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[ra].y, b.x, im[ra][jb], 0, 0, 0);
+            for (int jb = 0; jb < 2; ++jb) {
+                const float2 b = As[2 * n + jb][4 * (kb + d) + q4];
+#pragma unroll
+                for (int ra = 0; ra < RW; ++ra) {
+                    re[ra][jb] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[d][ra].x, b.x, re[ra][jb], 0, 0, 0);
+                    im[ra][jb] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[d][ra].x, b.y, im[ra][jb], 0, 0, 0);
+                    re[ra][jb] = __builtin_amdgcn_mfma_f32_16x16x4f32(-a[d][ra].y, b.y, re[ra][jb], 0, 0, 0);
+                    im[ra][jb] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[d][ra].y, b.x, im[ra][jb], 0, 0, 0);
+                }
             }
         }
-    }
 #pragma unroll
     for (int ra = 0; ra < RW; ++ra)
 #pragma unroll
-        for (int jb = 0; jb < 4; ++jb)
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-                rb[(size_t)(16 * (RW * w + ra) + 4 * q4 + j) * Bp + J0 + 16 * jb + n] =
-                    make_float2(re[ra][jb][j], im[ra][jb][j]);
+        for (int j = 0; j < 4; ++j)
+            *reinterpret_cast<float4*>(rb + (size_t)(16 * RW * w + RW * (4 * q4 + j) + ra) * Bp + J0 + 2 * n) =
+                make_float4(re[ra][0][j], im[ra][0][j], re[ra][1][j], im[ra][1][j]);
 }
 
 // A := A_mod - C R on every 64 x 64 tile of every slab.  The tiles are spread over the
 // eight XCDs in contiguous runs of the slab-major, column-major tile order (a run covers
 // whole columns of one or two slabs, so the C panel and the R columns a run reads stay in
 // that XCD's L2).  Wave w computes the 32 x 32 quadrant (w & 1, w >> 1) as 2 x 2 MFMA
-// tiles; operands are read straight from global memory in the MFMA lane layout (A operand
-// C(l % 16, l / 16), B operand R(l / 16, l % 16), accumulator rows 4 (l / 16) + j, column
-// l % 16), one k-step ahead.
+// tiles, the even and the odd rows and columns: a lane's operands of both tiles are one
+// 16-byte load straight from global memory, its results four rows of a column each way.
+// Bound by the CU's loads of operands beside the matrix cores (15 slabs of 1344 unknowns, 128
+// columns: 242 us with 8-byte loads and A read first behind eight waits, 195 us; 153 us without
+// any operand loads, 91 us the memory traffic alone).  128 registers, so that four
+// waves share a SIMD (with three: 205 us); 64 x 32 per wave: 204 us.
 template <int NB>
-__global__ void __launch_bounds__(256) k3f_update(float2* __restrict__ F, size_t stride, int l, int Bp, int k0,
+__global__ void __launch_bounds__(256, 4) k3f_update(float2* __restrict__ F, size_t stride, int l, int Bp, int k0,
                                                  int ns, const float2* __restrict__ Cb,
                                                  const float2* __restrict__ Rb, int s0) {
     const int nb = Bp / 64, nt = nb * nb;
@@ -294,8 +324,8 @@ __global__ void __launch_bounds__(256) k3f_update(float2* __restrict__ F, size_t
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, n = lane & 15, q4 = lane >> 4;
     const int I0 = it * 64 + 32 * (w & 1), J0 = jt * 64 + 32 * (w >> 1);
     float2* A = F + s * stride + (size_t)l * Bp * Bp;
-    const float2* cp = Cb + (size_t)s * cstr(Bp) + (size_t)q4 * Bp + I0 + n;
-    const float2* rp = Rb + (size_t)s * cstr(Bp) + (size_t)q4 * Bp + J0 + n;
+    const float2* cp = Cb + (size_t)s * cstr(Bp) + (size_t)q4 * Bp + I0 + 2 * n;
+    const float2* rp = Rb + (size_t)s * cstr(Bp) + (size_t)q4 * Bp + J0 + 2 * n;
     const bool kcol = jt * 64 >= k0 && jt * 64 < k0 + NB;
     if (it * 64 >= k0 && it * 64 < k0 + NB) {
         // the rows of block K become R(:, J) = P A(K, J): written directly, since forming
@@ -317,18 +347,6 @@ __global__ void __launch_bounds__(256) k3f_update(float2* __restrict__ F, size_t
     }
     // complex products by three real ones (x1 = -sum Cr Rr, x2 = sum Ci Ri,
     // x3 = -sum (Cr + Ci)(Rr + Ri)):  Re = A.r + x1 + x2,  Im = A.i + x3 - x1 + x2
-    float2 av[2][2][4];
-#pragma unroll
-    for (int ia = 0; ia < 2; ++ia)
-#pragma unroll
-        for (int jb = 0; jb < 2; ++jb) {
-            const int col = J0 + 16 * jb + n;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int row = I0 + 16 * ia + 4 * q4 + j;
-                av[ia][jb][j] = kcol ? make_float2(row == col ? 1.f : 0.f, 0.f) : A[(size_t)col * Bp + row];
-            }
-        }
     mf4 x1[2][2], x2[2][2], x3[2][2];
 #pragma unroll
     for (int ia = 0; ia < 2; ++ia)
@@ -338,39 +356,58 @@ __global__ void __launch_bounds__(256) k3f_update(float2* __restrict__ F, size_t
             x2[ia][jb] = x1[ia][jb];
             x3[ia][jb] = x1[ia][jb];
         }
-    float2 c[2], r[2], cn[2], rn[2];
+    constexpr int D = 4, NK = NB / 4;                   // ring of k-steps, D - 1 ahead
+    float2 c[D][2], r[D][2];
+    auto load = [&](int d, int kb) {
+        const size_t o = (size_t)(kb < NK ? kb : NK - 1) * 4 * Bp;
+        const float4 x = *reinterpret_cast<const float4*>(cp + o), y = *reinterpret_cast<const float4*>(rp + o);
+        c[d][0] = make_float2(x.x, x.y);
+        c[d][1] = make_float2(x.z, x.w);
+        r[d][0] = make_float2(y.x, y.y);
+        r[d][1] = make_float2(y.z, y.w);
+    };
+    auto steps = [&](int from, int to) {
+        for (int kb = from; kb < to; kb += D)
 #pragma unroll
-    for (int u = 0; u < 2; ++u) { c[u] = cp[16 * u]; r[u] = rp[16 * u]; }
-    for (int kb = 0; kb < NB / 4; ++kb) {
-        const size_t nx = (size_t)(kb + 1 < NB / 4 ? kb + 1 : kb) * 4 * Bp;
+            for (int d = 0; d < D; ++d) {
+                load((d + D - 1) % D, kb + d + D - 1);
+                float cs[2], rs[2];
 #pragma unroll
-        for (int u = 0; u < 2; ++u) { cn[u] = cp[nx + 16 * u]; rn[u] = rp[nx + 16 * u]; }
-        float cs[2], rs[2];
+                for (int u = 0; u < 2; ++u) { cs[u] = c[d][u].x + c[d][u].y; rs[u] = r[d][u].x + r[d][u].y; }
 #pragma unroll
-        for (int u = 0; u < 2; ++u) { cs[u] = c[u].x + c[u].y; rs[u] = r[u].x + r[u].y; }
+                for (int ia = 0; ia < 2; ++ia)
 #pragma unroll
-        for (int ia = 0; ia < 2; ++ia)
-#pragma unroll
-            for (int jb = 0; jb < 2; ++jb) {
-                x1[ia][jb] = __builtin_amdgcn_mfma_f32_16x16x4f32(-c[ia].x, r[jb].x, x1[ia][jb], 0, 0, 0);
-                x2[ia][jb] = __builtin_amdgcn_mfma_f32_16x16x4f32(c[ia].y, r[jb].y, x2[ia][jb], 0, 0, 0);
-                x3[ia][jb] = __builtin_amdgcn_mfma_f32_16x16x4f32(-cs[ia], rs[jb], x3[ia][jb], 0, 0, 0);
+                    for (int jb = 0; jb < 2; ++jb) {
+                        x1[ia][jb] = __builtin_amdgcn_mfma_f32_16x16x4f32(c[d][ia].x, r[d][jb].x, x1[ia][jb], 0, 0, 0);
+                        x2[ia][jb] = __builtin_amdgcn_mfma_f32_16x16x4f32(c[d][ia].y, r[d][jb].y, x2[ia][jb], 0, 0, 0);
+                        x3[ia][jb] = __builtin_amdgcn_mfma_f32_16x16x4f32(cs[ia], rs[jb], x3[ia][jb], 0, 0, 0);
+                    }
             }
+    };
 #pragma unroll
-        for (int u = 0; u < 2; ++u) { c[u] = cn[u]; r[u] = rn[u]; }
+    for (int d = 0; d < D - 1; ++d) load(d, d);
+    steps(0, NK - 8);
+    // A's entries are read eight steps before they are needed: earlier, the first steps wait for memory
+    float4 av[2][4];                                    // column J0 + 2 n + jb, rows I0 + 8 q4 + 2 j, + 1
+    float4* at[2];
+#pragma unroll
+    for (int jb = 0; jb < 2; ++jb) {
+        at[jb] = reinterpret_cast<float4*>(A + (size_t)(J0 + 2 * n + jb) * Bp + I0 + 8 * q4);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) av[jb][j] = at[jb][j];
     }
+    steps(NK - 8, NK);
 #pragma unroll
-    for (int ia = 0; ia < 2; ++ia)
+    for (int jb = 0; jb < 2; ++jb)
 #pragma unroll
-        for (int jb = 0; jb < 2; ++jb) {
-            const int col = J0 + 16 * jb + n;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int row = I0 + 16 * ia + 4 * q4 + j;
-                const float2 a0 = av[ia][jb][j];
-                const float p1 = x1[ia][jb][j], p2 = x2[ia][jb][j], p3 = x3[ia][jb][j];
-                A[(size_t)col * Bp + row] = make_float2(a0.x + p1 + p2, a0.y + p3 - p1 + p2);
+        for (int j = 0; j < 4; ++j) {
+            float4 a0 = av[jb][j];
+            if (kcol) {
+                const int d = J0 + 2 * n + jb - (I0 + 8 * q4 + 2 * j);
+                a0 = make_float4(d == 0 ? 1.f : 0.f, 0.f, d == 1 ? 1.f : 0.f, 0.f);
             }
+            at[jb][j] = make_float4(a0.x - x1[0][jb][j] + x2[0][jb][j], a0.y - x3[0][jb][j] + x1[0][jb][j] + x2[0][jb][j],
+                                    a0.z - x1[1][jb][j] + x2[1][jb][j], a0.w - x3[1][jb][j] + x1[1][jb][j] + x2[1][jb][j]);
         }
 }
 
@@ -399,13 +436,13 @@ hipError_t launch_factor3_plane_f32(const Fac3Args& a, int l, float2* F, size_t 
     for (int k0 = 0; k0 < a.Bp;) {
         if (k0 + 128 <= a.Bp) {
             hipLaunchKernelGGL(k3f_diag_inv128, dim3(ns), dim3(256), 0, st, F, stride, l, a.Bp, k0, Wd, Pf, err, s0);
-            hipLaunchKernelGGL(k3f_rc<128>, dim3(nb, ns), dim3(256), 0, st, F, stride, l, a.Bp, k0, Pf, Cb, Rb, s0);
+            hipLaunchKernelGGL(k3f_rc<128>, dim3(a.Bp / RCW, ns), dim3(256), 0, st, F, stride, l, a.Bp, k0, Pf, Cb, Rb, s0);
             hipLaunchKernelGGL(k3f_update<128>, dim3(8 * per), dim3(256), 0, st, F, stride, l, a.Bp, k0, ns, Cb, Rb,
                                s0);
             k0 += 128;
         } else {
             hipLaunchKernelGGL(k3f_diag_inv, dim3(ns), dim3(256), 0, st, F, stride, l, a.Bp, k0, Wd, Pf, err, s0);
-            hipLaunchKernelGGL(k3f_rc<64>, dim3(nb, ns), dim3(256), 0, st, F, stride, l, a.Bp, k0, Pf, Cb, Rb, s0);
+            hipLaunchKernelGGL(k3f_rc<64>, dim3(a.Bp / RCW, ns), dim3(256), 0, st, F, stride, l, a.Bp, k0, Pf, Cb, Rb, s0);
             hipLaunchKernelGGL(k3f_update<64>, dim3(8 * per), dim3(256), 0, st, F, stride, l, a.Bp, k0, ns, Cb, Rb,
                                s0);
             k0 += 64;
