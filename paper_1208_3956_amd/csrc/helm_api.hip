@@ -198,7 +198,7 @@ struct helm_problem {
     int batch_fuse = 0;         // join fused strip-solve launches in helm_solve_batch
     hipStream_t st_c[2] = {};   // concurrent sweep: streams of the downward chain and the z solves
     hipEvent_t ev_c[3] = {};    // fork / join events of the concurrent sweep
-    hipStream_t st_fac = nullptr;   // 3-D factorisation: stream of the upper end
+    hipStream_t st_fac = nullptr;   // 3-D factorisation: second stream
     hipStream_t cap_st = nullptr;  // private stream the graph is captured on (capture is not
                                    // allowed on the legacy default stream); replays go to st
     long ws_epoch = 0;          // workspace generation (graphs captured before it are stale)
@@ -2512,23 +2512,22 @@ helm_status factor3(helm_t H) {
         // complex64 blocked Gauss-Jordan in place in the stored factor; a diagonal block
         // that is singular or ill-conditioned sends the whole factorisation to the FP64
         // Gauss-Jordan with partial pivoting over the whole column below
-        const size_t wb = helm::factor3_f32_work_bytes(nf, g.Bp);
-        if ((st = alloc(&work32, 2 * wb)) != HELM_OK) return st;
+        if ((st = alloc(&work32, helm::factor3_f32_work_bytes(2 * nf, g.Bp))) != HELM_OK) return st;
         HIPCHK(hipMemsetAsync(H->d_err, 0, sizeof(int), H->st));
         float2* F32 = static_cast<float2*>(F);
         const size_t stride = (size_t)g.Ny * BB;
-        // the planes below the middle one on the handle's stream, those above on a second one,
-        // all slabs of a plane together, so that one end's latency-bound diagonal inverses
-        // overlap the other end's update GEMMs; the middle plane in two halves of the slabs
-        hipError_t e = TIMED(H, helm::K_FACTOR_CHUNKS, two_ends([&](int l, int end, hipStream_t q) {
-            void* wk = static_cast<char*>(work32) + end * wb;
-            if (l != p)
-                return helm::launch_factor3_plane_f32(a, l, F32, stride, wk, H->d_err, q, 0, nf, end == 0 && l > 0,
-                                                      end == 1 && l < g.Ny - 1);
-            const int s0 = end == 0 ? 0 : (nf + 1) / 2, s1 = end == 0 ? (nf + 1) / 2 : nf;
-            return s1 > s0 ? helm::launch_factor3_plane_f32(a, l, F32, stride, wk, H->d_err, q, s0, s1 - s0, true, true)
-                           : hipSuccess;
-        }));
+        // a plane from each end at a time; the updates on the second stream
+        auto planes = [&]() -> hipError_t {
+            hipError_t r = hipSuccess;
+            for (int k = 0; k <= p && r == hipSuccess; ++k) {
+                const int u = k < p && g.Ny - 1 - k > p ? g.Ny - 1 - k : -1;
+                const int below = k > 0 ? 1 : 0, above = (k == p && p < g.Ny - 1 ? 1 : 0) | (u >= 0 && u < g.Ny - 1 ? 2 : 0);
+                r = helm::launch_factor3_plane_f32(a, k, u, F32, stride, work32, H->d_err, below, above, H->st, H->st_fac, evs);
+            }
+            if (r != hipSuccess) (void)hipStreamSynchronize(H->st_fac);   // its buffers are about to be freed
+            return r;
+        };
+        hipError_t e = TIMED(H, helm::K_FACTOR_CHUNKS, planes());
         HIPCHK(e);
         HIPCHK(hipMemcpyAsync(&herr, H->d_err, sizeof(int), hipMemcpyDeviceToHost, H->st));
         HIPCHK(hipStreamSynchronize(H->st));

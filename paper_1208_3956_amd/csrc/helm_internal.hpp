@@ -333,16 +333,17 @@ hipError_t launch_factor3_plane(const Fac3Args& a, int l, const double2* Glow, c
                                 hipStream_t st);
 size_t factor3_panel_width();
 // complex64 slab factorisation (mixed precision): blocked Gauss-Jordan in place in the
-// stored factor F ([slab][plane][Bp*Bp], slab stride `stride`), one plane of the slabs
-// s0 .. s0 + ns - 1 per call (disjoint slab sets, or planes with work of their own, may run on
-// different streams); low, up: the neighbour planes already inverted
+// stored factor F ([slab][plane][Bp*Bp], slab stride `stride`), plane l0 and (l1 >= 0) plane l1 of
+// every slab per call; below, above: the neighbour planes already inverted (bit 0 of l0, bit 1
+// of l1); st2 and two events: the updates beside the diagonal inverses on st, joined before
+// the call's last kernel; work: factor3_f32_work_bytes(matrices, Bp)
 size_t factor3_f32_work_bytes(int J, int Bp);
 // stored complex64 slab inverses (J slots of Ny planes, slot stride `stride`) rewritten,
 // plane by plane, from column-major into the 16-row panels the sweeps read; work holds
 // J Bp^2 complex64 entries
 hipError_t launch_factor3_panelize(float2* F, size_t stride, int J, int Ny, int Bp, float2* work, hipStream_t st);
-hipError_t launch_factor3_plane_f32(const Fac3Args& a, int l, float2* F, size_t stride, void* work, int* err,
-                                    hipStream_t st, int s0, int ns, bool low, bool up);
+hipError_t launch_factor3_plane_f32(const Fac3Args& a, int l0, int l1, float2* F, size_t stride, void* work, int* err,
+                                    int below, int above, hipStream_t st, hipStream_t st2, const hipEvent_t* ev);
 template <typename T>
 hipError_t launch_strip_solve3(const Solve3Args<T>& a, hipStream_t st, KTimer* kt);
 

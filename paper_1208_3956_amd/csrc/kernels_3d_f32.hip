@@ -37,15 +37,26 @@ constexpr size_t WSTR = 8 * (size_t)BLK;   // FP64 scratch blocks
 constexpr size_t PSTR = 128 * 128;         // P
 __host__ __device__ inline size_t cstr(int Bp) { return (size_t)128 * Bp; }   // C and R
 
+// The matrices of a call: plane l0 of the ns slabs, then plane l1 of the ns slabs (the
+// elimination's two ends), slabs `stride` entries apart
+struct Planes {
+    float2* F;
+    size_t stride;
+    int ns, l0, l1;
+    __device__ int slab(int u) const { return u < ns ? u : u - ns; }
+    __device__ int plane(int u) const { return u < ns ? l0 : l1; }
+    __device__ float2* at(int u, int Bp) const { return F + slab(u) * stride + (size_t)plane(u) * Bp * Bp; }
+};
+
 // S_l = T_l - c_l b_{l-1} G_{l-1} (low) - b_l c_{l+1} G_{l+1} (up) into the plane-l slot of
-// every slab (identity on the padding); the neighbour planes' slots are already inverted.  T
+// every slab (below, above: bit 0 for plane l0, bit 1 for l1) (identity on the padding); the neighbour planes' slots are already inverted.  T
 // in FP64, rounded.
-__global__ void __launch_bounds__(256) k3f_build_S(Fac3Args a, int l, float2* __restrict__ F, size_t stride,
-                                                  int s0, int low, int up) {
-    const int s = s0 + blockIdx.y;
+__global__ void __launch_bounds__(256) k3f_build_S(Fac3Args a, Planes F, int below, int above) {
+    const int u = blockIdx.y, s = F.slab(u), l = F.plane(u);
+    const bool low = below >> (u >= F.ns) & 1, up = above >> (u >= F.ns) & 1;
     const size_t BB = (size_t)a.Bp * a.Bp;
     const int W = a.sW[s], B = W * a.Nz;
-    float2* S = F + s * stride + (size_t)l * BB;
+    float2* S = F.at(u, a.Bp);
     double2 cb = make_double2(0.0, 0.0), bc = cb;
     if (low) cb = cmul(a.cy[l], a.by[l - 1]);
     if (up) bc = cmul(a.by[l], a.cy[l + 1]);
@@ -82,16 +93,106 @@ __global__ void __launch_bounds__(256) k3f_build_S(Fac3Args a, int l, float2* __
     }
 }
 
+// The 32 x 32 quadrant at (I0, J0) of A - C R (the block column K, kcol: I - C R) by one wave, the
+// even and the odd rows and columns as MFMA tiles.
+template <int NB>
+__device__ __attribute__((always_inline)) inline void update_quadrant(float2* A, const float2* cb, const float2* rb, int Bp, int I0,
+                                                                      int J0, bool kcol) {
+    const int lane = threadIdx.x & 63, n = lane & 15, q4 = lane >> 4;
+    const float2* cp = cb + (size_t)q4 * Bp + I0 + 2 * n;
+    const float2* rp = rb + (size_t)q4 * Bp + J0 + 2 * n;
+    // complex products by three real ones (x1 = -sum Cr Rr, x2 = sum Ci Ri,
+    // x3 = -sum (Cr + Ci)(Rr + Ri)):  Re = A.r + x1 + x2,  Im = A.i + x3 - x1 + x2
+    mf4 x1[2][2], x2[2][2], x3[2][2];
+#pragma unroll
+    for (int ia = 0; ia < 2; ++ia)
+#pragma unroll
+        for (int jb = 0; jb < 2; ++jb) {
+            x1[ia][jb] = mf4{0.f, 0.f, 0.f, 0.f};
+            x2[ia][jb] = x1[ia][jb];
+            x3[ia][jb] = x1[ia][jb];
+        }
+    constexpr int D = 4, NK = NB / 4;                   // ring of k-steps, D - 1 ahead
+    float2 c[D][2], r[D][2];
+    auto load = [&](int d, int kb) {
+        const size_t o = (size_t)(kb < NK ? kb : NK - 1) * 4 * Bp;
+        const float4 x = *reinterpret_cast<const float4*>(cp + o), y = *reinterpret_cast<const float4*>(rp + o);
+        c[d][0] = make_float2(x.x, x.y);
+        c[d][1] = make_float2(x.z, x.w);
+        r[d][0] = make_float2(y.x, y.y);
+        r[d][1] = make_float2(y.z, y.w);
+    };
+    auto steps = [&](int from, int to) {
+        for (int kb = from; kb < to; kb += D)
+#pragma unroll
+            for (int d = 0; d < D; ++d) {
+                load((d + D - 1) % D, kb + d + D - 1);
+                float cs[2], rs[2];
+#pragma unroll
+                for (int u = 0; u < 2; ++u) { cs[u] = c[d][u].x + c[d][u].y; rs[u] = r[d][u].x + r[d][u].y; }
+#pragma unroll
+                for (int ia = 0; ia < 2; ++ia)
+#pragma unroll
+                    for (int jb = 0; jb < 2; ++jb) {
+                        x1[ia][jb] = __builtin_amdgcn_mfma_f32_16x16x4f32(c[d][ia].x, r[d][jb].x, x1[ia][jb], 0, 0, 0);
+                        x2[ia][jb] = __builtin_amdgcn_mfma_f32_16x16x4f32(c[d][ia].y, r[d][jb].y, x2[ia][jb], 0, 0, 0);
+                        x3[ia][jb] = __builtin_amdgcn_mfma_f32_16x16x4f32(cs[ia], rs[jb], x3[ia][jb], 0, 0, 0);
+                    }
+            }
+    };
+#pragma unroll
+    for (int d = 0; d < D - 1; ++d) load(d, d);
+    steps(0, NK - 8);
+    // A's entries are read eight steps before they are needed: earlier, the first steps wait for memory
+    float4 av[2][4];                                    // column J0 + 2 n + jb, rows I0 + 8 q4 + 2 j, + 1
+    float4* at[2];
+#pragma unroll
+    for (int jb = 0; jb < 2; ++jb) {
+        at[jb] = reinterpret_cast<float4*>(A + (size_t)(J0 + 2 * n + jb) * Bp + I0 + 8 * q4);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) av[jb][j] = at[jb][j];
+    }
+    steps(NK - 8, NK);
+#pragma unroll
+    for (int jb = 0; jb < 2; ++jb)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            float4 a0 = av[jb][j];
+            if (kcol) {
+                const int d = J0 + 2 * n + jb - (I0 + 8 * q4 + 2 * j);
+                a0 = make_float4(d == 0 ? 1.f : 0.f, 0.f, d == 1 ? 1.f : 0.f, 0.f);
+            }
+            at[jb][j] = make_float4(a0.x - x1[0][jb][j] + x2[0][jb][j], a0.y - x3[0][jb][j] + x1[0][jb][j] + x2[0][jb][j],
+                                    a0.z - x1[1][jb][j] + x2[1][jb][j], a0.w - x3[1][jb][j] + x1[1][jb][j] + x2[1][jb][j]);
+        }
+}
+
+// The diagonal block at k0 (NB wide) of slab s brought up to date with the elimination of the 128
+// columns before it: its tiles of that update (Cb null: nothing to do)
+template <int NB>
+__device__ __attribute__((always_inline)) inline void update_diag(float2* A, const float2* Cb, const float2* Rb, int Bp, int k0,
+                                                                  int s) {
+    if (!Cb) return;
+    const int w = threadIdx.x >> 6;
+    for (int q = 0; q < (NB / 64) * (NB / 64); ++q)
+        update_quadrant<128>(A, Cb + (size_t)s * cstr(Bp), Rb + (size_t)s * cstr(Bp), Bp, k0 + 64 * (q & 1) + 32 * (w & 1),
+                             k0 + 64 * (q >> 1) + 32 * (w >> 1), false);
+    __syncthreads();
+}
+
 // P = A_KK^{-1} for the diagonal block at k0 of every slab (one workgroup per slab, the
 // block in registers, FP64), stored column-major (leading dimension 64) in FP64 and
 // complex64.  err bit 1: zero or non-finite pivot; bit 2: 1-norm condition above COND_MAX.
-__global__ void __launch_bounds__(256) k3f_diag_inv(const float2* __restrict__ F, size_t stride, int l, int Bp,
-                                                   int k0, double2* __restrict__ Pd, float2* __restrict__ Pf,
-                                                   int* __restrict__ err, int s0) {
+__global__ void __launch_bounds__(256) k3f_diag_inv(Planes F, int Bp, int k0,
+                                                   const float2* __restrict__ Cb, const float2* __restrict__ Rb,
+                                                   double2* __restrict__ Pd, float2* __restrict__ Pf,
+                                                   int* __restrict__ err) {
     __shared__ GJShared sh;
     __shared__ double na[4][64], np[4][64];
-    const int s = s0 + blockIdx.x;
-    const float2* A = F + s * stride + (size_t)l * Bp * Bp;
+    __builtin_amdgcn_s_setprio(3);
+    const int s = blockIdx.x;
+    float2* A = F.at(s, Bp);
+    update_diag<64>(A, Cb, Rb, Bp, k0, s);
     const int i = threadIdx.x & 63, g = threadIdx.x >> 6;
     double2 M[16];
 #pragma unroll
@@ -135,13 +236,16 @@ __global__ void __launch_bounds__(256) k3f_diag_inv(const float2* __restrict__ F
 // (pivoting inside the two 64 x 64 inverses), in FP64, one workgroup per slab, with eight
 // 64 x 64 scratch blocks per slab in global memory; P is stored complex64, column-major
 // (leading dimension 128).  err bits as in the 64-wide kernel.
-__global__ void __launch_bounds__(256) k3f_diag_inv128(const float2* __restrict__ F, size_t stride, int l, int Bp,
-                                                      int k0, double2* __restrict__ Wd, float2* __restrict__ Pf,
-                                                      int* __restrict__ err, int s0) {
+__global__ void __launch_bounds__(256) k3f_diag_inv128(Planes F, int Bp, int k0,
+                                                      const float2* __restrict__ Cb, const float2* __restrict__ Rb,
+                                                      double2* __restrict__ Wd, float2* __restrict__ Pf,
+                                                      int* __restrict__ err) {
     __shared__ GJShared sh;
     __shared__ double na[4], np[4];
-    const int s = s0 + blockIdx.x, t = threadIdx.x;
-    const float2* A = F + s * stride + (size_t)l * Bp * Bp;
+    __builtin_amdgcn_s_setprio(3);                       // beside the update's waves
+    const int s = blockIdx.x, t = threadIdx.x;
+    float2* A = F.at(s, Bp);
+    update_diag<128>(A, Cb, Rb, Bp, k0, s);
     double2* W = Wd + (size_t)s * WSTR;
     double2 *A12 = W, *A21 = W + BLK, *A22 = W + 2 * BLK, *P11 = W + 3 * BLK;
     double2 *T1 = W + 4 * BLK, *P22 = W + 5 * BLK, *T2 = W + 6 * BLK, *P12 = W + 7 * BLK;
@@ -217,13 +321,12 @@ __global__ void __launch_bounds__(256) k3f_diag_inv128(const float2* __restrict_
 // used, 38 us).
 constexpr int RCW = 32;                // columns of a workgroup of k3f_rc
 template <int NB>
-__global__ void __launch_bounds__(256) k3f_rc(const float2* __restrict__ F, size_t stride, int l, int Bp, int k0,
-                                             const float2* __restrict__ Pf, float2* __restrict__ Cb,
-                                             float2* __restrict__ Rb, int s0) {
+__global__ void __launch_bounds__(256) k3f_rc(Planes F, int Bp, int k0, const float2* __restrict__ Pf,
+                                             float2* __restrict__ Cb, float2* __restrict__ Rb) {
     constexpr int NK = NB / 4, D = 8, CL = NB / 16, AL = RCW * NB / 512;
     __shared__ float2 As[RCW][NB + 1];  // As[j][m] = A(k0 + m, J0 + j)
-    const int s = s0 + blockIdx.y, J0 = blockIdx.x * RCW, t = threadIdx.x;
-    const float2* A = F + s * stride + (size_t)l * Bp * Bp;
+    const int s = blockIdx.y, J0 = blockIdx.x * RCW, t = threadIdx.x;
+    const float2* A = F.at(s, Bp);
     float2* cb = Cb + (size_t)s * cstr(Bp);
     float2* rb = Rb + (size_t)s * cstr(Bp);
     const float2* P = Pf + (size_t)s * PSTR;
@@ -313,19 +416,18 @@ __global__ void __launch_bounds__(256) k3f_rc(const float2* __restrict__ F, size
 // any operand loads, 91 us the memory traffic alone).  128 registers, so that four
 // waves share a SIMD (with three: 205 us); 64 x 32 per wave: 204 us.
 template <int NB>
-__global__ void __launch_bounds__(256, 4) k3f_update(float2* __restrict__ F, size_t stride, int l, int Bp, int k0,
-                                                 int ns, const float2* __restrict__ Cb,
-                                                 const float2* __restrict__ Rb, int s0) {
+__global__ void __launch_bounds__(256, 4) k3f_update(Planes F, int Bp, int k0, int ns, const float2* __restrict__ Cb,
+                                                 const float2* __restrict__ Rb, int kn, int nbn) {
     const int nb = Bp / 64, nt = nb * nb;
     const int total = ns * nt, per = (total + 7) / 8;
     const int gi = (int)(blockIdx.x % 8) * per + (int)(blockIdx.x / 8);
     if (gi >= total) return;
-    const int s = s0 + gi / nt, tt = gi % nt, it = tt % nb, jt = tt / nb;
+    const int s = gi / nt, tt = gi % nt, it = tt % nb, jt = tt / nb;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, n = lane & 15, q4 = lane >> 4;
     const int I0 = it * 64 + 32 * (w & 1), J0 = jt * 64 + 32 * (w >> 1);
-    float2* A = F + s * stride + (size_t)l * Bp * Bp;
-    const float2* cp = Cb + (size_t)s * cstr(Bp) + (size_t)q4 * Bp + I0 + 2 * n;
-    const float2* rp = Rb + (size_t)s * cstr(Bp) + (size_t)q4 * Bp + J0 + 2 * n;
+    float2* A = F.at(s, Bp);
+    auto next = [&](int x) { return x * 64 >= kn && x * 64 < kn + nbn; };
+    if (next(it) && next(jt)) return;                   // the next diagonal block's own
     const bool kcol = jt * 64 >= k0 && jt * 64 < k0 + NB;
     if (it * 64 >= k0 && it * 64 < k0 + NB) {
         // the rows of block K become R(:, J) = P A(K, J): written directly, since forming
@@ -345,70 +447,7 @@ __global__ void __launch_bounds__(256, 4) k3f_update(float2* __restrict__ F, siz
             }
         return;
     }
-    // complex products by three real ones (x1 = -sum Cr Rr, x2 = sum Ci Ri,
-    // x3 = -sum (Cr + Ci)(Rr + Ri)):  Re = A.r + x1 + x2,  Im = A.i + x3 - x1 + x2
-    mf4 x1[2][2], x2[2][2], x3[2][2];
-#pragma unroll
-    for (int ia = 0; ia < 2; ++ia)
-#pragma unroll
-        for (int jb = 0; jb < 2; ++jb) {
-            x1[ia][jb] = mf4{0.f, 0.f, 0.f, 0.f};
-            x2[ia][jb] = x1[ia][jb];
-            x3[ia][jb] = x1[ia][jb];
-        }
-    constexpr int D = 4, NK = NB / 4;                   // ring of k-steps, D - 1 ahead
-    float2 c[D][2], r[D][2];
-    auto load = [&](int d, int kb) {
-        const size_t o = (size_t)(kb < NK ? kb : NK - 1) * 4 * Bp;
-        const float4 x = *reinterpret_cast<const float4*>(cp + o), y = *reinterpret_cast<const float4*>(rp + o);
-        c[d][0] = make_float2(x.x, x.y);
-        c[d][1] = make_float2(x.z, x.w);
-        r[d][0] = make_float2(y.x, y.y);
-        r[d][1] = make_float2(y.z, y.w);
-    };
-    auto steps = [&](int from, int to) {
-        for (int kb = from; kb < to; kb += D)
-#pragma unroll
-            for (int d = 0; d < D; ++d) {
-                load((d + D - 1) % D, kb + d + D - 1);
-                float cs[2], rs[2];
-#pragma unroll
-                for (int u = 0; u < 2; ++u) { cs[u] = c[d][u].x + c[d][u].y; rs[u] = r[d][u].x + r[d][u].y; }
-#pragma unroll
-                for (int ia = 0; ia < 2; ++ia)
-#pragma unroll
-                    for (int jb = 0; jb < 2; ++jb) {
-                        x1[ia][jb] = __builtin_amdgcn_mfma_f32_16x16x4f32(c[d][ia].x, r[d][jb].x, x1[ia][jb], 0, 0, 0);
-                        x2[ia][jb] = __builtin_amdgcn_mfma_f32_16x16x4f32(c[d][ia].y, r[d][jb].y, x2[ia][jb], 0, 0, 0);
-                        x3[ia][jb] = __builtin_amdgcn_mfma_f32_16x16x4f32(cs[ia], rs[jb], x3[ia][jb], 0, 0, 0);
-                    }
-            }
-    };
-#pragma unroll
-    for (int d = 0; d < D - 1; ++d) load(d, d);
-    steps(0, NK - 8);
-    // A's entries are read eight steps before they are needed: earlier, the first steps wait for memory
-    float4 av[2][4];                                    // column J0 + 2 n + jb, rows I0 + 8 q4 + 2 j, + 1
-    float4* at[2];
-#pragma unroll
-    for (int jb = 0; jb < 2; ++jb) {
-        at[jb] = reinterpret_cast<float4*>(A + (size_t)(J0 + 2 * n + jb) * Bp + I0 + 8 * q4);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) av[jb][j] = at[jb][j];
-    }
-    steps(NK - 8, NK);
-#pragma unroll
-    for (int jb = 0; jb < 2; ++jb)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            float4 a0 = av[jb][j];
-            if (kcol) {
-                const int d = J0 + 2 * n + jb - (I0 + 8 * q4 + 2 * j);
-                a0 = make_float4(d == 0 ? 1.f : 0.f, 0.f, d == 1 ? 1.f : 0.f, 0.f);
-            }
-            at[jb][j] = make_float4(a0.x - x1[0][jb][j] + x2[0][jb][j], a0.y - x3[0][jb][j] + x1[0][jb][j] + x2[0][jb][j],
-                                    a0.z - x1[1][jb][j] + x2[1][jb][j], a0.w - x3[1][jb][j] + x1[1][jb][j] + x2[1][jb][j]);
-        }
+    update_quadrant<NB>(A, Cb + (size_t)s * cstr(Bp), Rb + (size_t)s * cstr(Bp), Bp, I0, J0, kcol);
 }
 
 }  // namespace
@@ -419,34 +458,55 @@ size_t factor3_f32_work_bytes(int J, int Bp) {
     return (size_t)J * (WSTR * sizeof(double2) + PSTR * sizeof(float2) + 2 * cstr(Bp) * sizeof(float2));
 }
 
-// One plane of the slabs s0 .. s0 + ns - 1: column blocks of 128 (a last block of 64 when
+// Plane l0 and (l1 >= 0) plane l1 of every slab: column blocks of 128 (a last block of 64 when
 // Bp is an odd multiple of 64).  A 128-wide block halves the passes of the update over the
-// matrices (the update is bound by HBM and MFMA about equally at 64).
-hipError_t launch_factor3_plane_f32(const Fac3Args& a, int l, float2* F, size_t stride, void* work, int* err,
-                                    hipStream_t st, int s0, int ns, bool low, bool up) {
+// matrices (the update is bound by HBM and MFMA about equally at 64).  The inverse of a
+// diagonal block, one workgroup per matrix, needs no more of the update before it than the
+// block's own tiles: it makes these itself, on st, beside the update of the rest on st2 (ev: two
+// events).  It is launched first: its workgroups find no room on a CU that the update has
+// filled, and would wait for the update's end.  Both ends in one launch, so that the update
+// of 30 matrices of 1344 (408 us alone) covers the inverse (192 alone, 366 beside it): 75 planes
+// of 15 slabs in 271 ms; 273 to 298 with the ends' chains on a stream each, 360 with the update
+// launched first.
+hipError_t launch_factor3_plane_f32(const Fac3Args& a, int l0, int l1, float2* Ff, size_t stride, void* work, int* err,
+                                    int below, int above, hipStream_t st, hipStream_t st2, const hipEvent_t* ev) {
+    const Planes F{Ff, stride, a.J, l0, l1};
+    const int ns = l1 < 0 ? a.J : 2 * a.J;
     const size_t BB = (size_t)a.Bp * a.Bp;
     double2* Wd = static_cast<double2*>(work);
-    float2* Pf = reinterpret_cast<float2*>(Wd + (size_t)a.J * WSTR);
-    float2* Cb = Pf + (size_t)a.J * PSTR;
-    float2* Rb = Cb + (size_t)a.J * cstr(a.Bp);
+    float2* Pf = reinterpret_cast<float2*>(Wd + (size_t)ns * WSTR);
+    float2* Cb = Pf + (size_t)ns * PSTR;
+    float2* Rb = Cb + (size_t)ns * cstr(a.Bp);
     const unsigned nbs = (unsigned)std::min<size_t>((BB + 255) / 256, 4096);
-    hipLaunchKernelGGL(k3f_build_S, dim3(nbs, ns), dim3(256), 0, st, a, l, F, stride, s0, low ? 1 : 0, up ? 1 : 0);
+    hipLaunchKernelGGL(k3f_build_S, dim3(nbs, ns), dim3(256), 0, st, a, F, below, above);
     const int nb = a.Bp / 64;
     const int total = ns * nb * nb, per = (total + 7) / 8;
+    auto width = [&](int k0) { return k0 + 128 <= a.Bp ? 128 : a.Bp - k0; };
+    auto diag = [&](int k0, const float2* C, hipStream_t q) {
+        if (width(k0) == 128)
+            hipLaunchKernelGGL(k3f_diag_inv128, dim3(ns), dim3(256), 0, q, F, a.Bp, k0, C, Rb, Wd, Pf, err);
+        else hipLaunchKernelGGL(k3f_diag_inv, dim3(ns), dim3(256), 0, q, F, a.Bp, k0, C, Rb, Wd, Pf, err);
+    };
+    auto after = [&](hipStream_t from, hipStream_t to, hipEvent_t e) {
+        const hipError_t r = hipEventRecord(e, from);
+        return r == hipSuccess ? hipStreamWaitEvent(to, e, 0) : r;
+    };
+    diag(0, nullptr, st);
     for (int k0 = 0; k0 < a.Bp;) {
-        if (k0 + 128 <= a.Bp) {
-            hipLaunchKernelGGL(k3f_diag_inv128, dim3(ns), dim3(256), 0, st, F, stride, l, a.Bp, k0, Wd, Pf, err, s0);
-            hipLaunchKernelGGL(k3f_rc<128>, dim3(a.Bp / RCW, ns), dim3(256), 0, st, F, stride, l, a.Bp, k0, Pf, Cb, Rb, s0);
-            hipLaunchKernelGGL(k3f_update<128>, dim3(8 * per), dim3(256), 0, st, F, stride, l, a.Bp, k0, ns, Cb, Rb,
-                               s0);
-            k0 += 128;
-        } else {
-            hipLaunchKernelGGL(k3f_diag_inv, dim3(ns), dim3(256), 0, st, F, stride, l, a.Bp, k0, Wd, Pf, err, s0);
-            hipLaunchKernelGGL(k3f_rc<64>, dim3(a.Bp / RCW, ns), dim3(256), 0, st, F, stride, l, a.Bp, k0, Pf, Cb, Rb, s0);
-            hipLaunchKernelGGL(k3f_update<64>, dim3(8 * per), dim3(256), 0, st, F, stride, l, a.Bp, k0, ns, Cb, Rb,
-                               s0);
-            k0 += 64;
+        const int w = width(k0), kn = k0 + w, nbn = width(kn);
+        const dim3 grc(a.Bp / RCW, ns), gup(8 * per);
+        hipError_t r;
+        if (w == 128) hipLaunchKernelGGL(k3f_rc<128>, grc, dim3(256), 0, st, F, a.Bp, k0, Pf, Cb, Rb);
+        else hipLaunchKernelGGL(k3f_rc<64>, grc, dim3(256), 0, st, F, a.Bp, k0, Pf, Cb, Rb);
+        const hipStream_t q = nbn > 0 ? st2 : st;
+        if (nbn > 0) {
+            if ((r = after(st, st2, ev[0])) != hipSuccess) return r;
+            diag(kn, Cb, st);
         }
+        if (w == 128) hipLaunchKernelGGL(k3f_update<128>, gup, dim3(256), 0, q, F, a.Bp, k0, ns, Cb, Rb, kn, nbn);
+        else hipLaunchKernelGGL(k3f_update<64>, gup, dim3(256), 0, q, F, a.Bp, k0, ns, Cb, Rb, kn, nbn);
+        if (nbn > 0 && (r = after(st2, st, ev[1])) != hipSuccess) return r;
+        k0 = kn;
     }
     return hipGetLastError();
 }
