@@ -380,6 +380,8 @@ helm_status helm_get_fusion_stats(helm_t H, long long* fused, long long* unfused
  *   2 phase C (spike correction + scatter)        3 factor, chunks
  *   4 factor, separators                          5 FP64 stencil
  *   6 GMRES vector kernels                        7 other
+ * A launch over a batch of strips counts once per strip; the dense products of the reduced
+ * form and their build are in class 7 (a reduced iteration then has none in 0 to 2).
  * launches, total_ms: host arrays of nclass entries.  At most 65536 launches are
  * recorded per enable; later ones are counted but not timed (ms stays a lower bound).
  * enable is a bit mask of the classes to time (bit c = class c, 0xFF = all); launches of
@@ -392,6 +394,8 @@ helm_status helm_set_kernel_timing(helm_t H, int enable);
 helm_status helm_get_kernel_times(helm_t H, int nclass, int* launches, double* total_ms);
 
 const char* helm_last_error(helm_t H);
+/* Up to 8 GB per device of the memory of destroyed handles stay allocated in the process, for
+ * later handles; an allocation of the library that fails gives all of it back first. */
 void helm_destroy(helm_t H);
 
 #ifdef __cplusplus
