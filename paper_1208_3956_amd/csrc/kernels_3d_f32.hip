@@ -12,7 +12,7 @@
 // A(I, J) -= A(I, K) P A(K, J): one step of block Gauss-Jordan.  After the last block A
 // holds S^{-1} with no permutation to undo.  The rows of block K are written as R
 // directly rather than through the product (in FP32 that form would cancel to an error of
-// order eps cond(A_KK)).  The update is a rank-64 complex GEMM on
+// order eps cond(A_KK)).  The update is a rank-128 (64) complex GEMM on
 // v_mfma_f32_16x16x4f32 with three real products per complex one (Gauss's form),
 // accumulated in FP32.
 // Without a search over the whole column the elimination relies on well-conditioned
@@ -31,8 +31,7 @@ using namespace gjr;
 typedef float mf4 __attribute__((ext_vector_type(4)));
 
 constexpr double COND_MAX = 1e6;   // largest accepted 1-norm condition of a diagonal block
-// per-slab strides of the work arrays (the same for 64- and 128-wide blocks, so that slab
-// groups on different streams never share a region)
+// strides of the work arrays, one set per matrix of a call (the same for 64- and 128-wide blocks)
 constexpr size_t WSTR = 8 * (size_t)BLK;   // FP64 scratch blocks
 constexpr size_t PSTR = 128 * 128;         // P
 __host__ __device__ inline size_t cstr(int Bp) { return (size_t)128 * Bp; }   // C and R

@@ -85,7 +85,10 @@ __device__ inline void load_group(const double2* p, int gi, int lane, double2 (&
 //   MODE 1  x_s = Sm r^         tile = 4 separator + quarter
 //   MODE 2  outputs = Tm [p; x_s]   tile = (chunk, active output, 16-row group)
 // The column tiles of a row tile follow each other on one XCD (blocks 8 apart), which reads
-// the matrix from memory once.
+// the matrix from memory once.  Bound by the launch (4 to 5 us of any dependent one) and, at
+// 2032 rows, by reading Tm (42 MB in FP32, 8.6 us; 13.5 us a launch with 16 right-hand sides)
+// or by the products (64: 2.7 GFLOP, 32 us).  Not faster: eight waves with 2 x 2 tiles each
+// (64 -> 90 us a strip solve), registers for five workgroups a CU instead of three (56 -> 56).
 template <typename T, typename TL, int NC, int MODE>
 __global__ void __launch_bounds__(NT) k_red_mul(RedArgs<T> a, int tiles, int nc) {
     using V = cplx<T>;
