@@ -446,10 +446,30 @@ helm_status dmalloc(helm_t H, P** p, size_t bytes) {
     return HELM_OK;
 }
 
+// The handle's device made current for a scope, the caller's again after it: handles are closed
+// (and collected) from code that has another device current
+struct OnDevice {
+    int prev = -1;
+    explicit OnDevice(helm_t H) {
+        int cur = H->dev;
+        if (hipGetDevice(&cur) == hipSuccess && cur != H->dev && hipSetDevice(H->dev) == hipSuccess) prev = cur;
+    }
+    ~OnDevice() { if (prev >= 0) (void)hipSetDevice(prev); }
+    OnDevice(const OnDevice&) = delete;
+    OnDevice& operator=(const OnDevice&) = delete;
+};
+
+// waits for the work queued on the handle's stream; the default stream's counterpart is the
+// handle's device, which need not be the current one
+hipError_t quiesce(helm_t H) {
+    OnDevice on(H);
+    return H->st ? hipStreamSynchronize(H->st) : hipDeviceSynchronize();
+}
+
 // memory of handle H, which only work ordered on its stream uses
 void dfree(helm_t H, void* p) {
     if (!p) return;
-    (void)(H->st ? hipStreamSynchronize(H->st) : hipDeviceSynchronize());
+    (void)quiesce(H);
     Pool::get().put(p);
 }
 
@@ -1516,7 +1536,7 @@ helm_status drop_graph(helm_t H, int slot = -1) {
     bool any = false;
     for (int i = 0; i < helm_problem::NGRAPH; ++i) any = any || ((slot < 0 || i == slot) && H->apg[i].exec);
     if (!any) return HELM_OK;
-    HIPCHK(H->st ? hipStreamSynchronize(H->st) : hipDeviceSynchronize());
+    HIPCHK(quiesce(H));
     for (int i = 0; i < helm_problem::NGRAPH; ++i) {
         if ((slot >= 0 && i != slot) || !H->apg[i].exec) continue;
         HIPCHK(hipGraphExecDestroy(H->apg[i].exec));
@@ -3025,11 +3045,11 @@ helm_status helm_set_kernel_timing(helm_t H, int enable) {
     if (!H) return HELM_EINVAL;
     if (enable) {
         if (!H->timer) H->timer = new EventTimer();
-        HIPCHK(H->st ? hipStreamSynchronize(H->st) : hipDeviceSynchronize());
+        HIPCHK(quiesce(H));
         H->timer->reset();
         H->timer->mask = (unsigned)enable & 0xFFu;
     } else if (H->timer) {
-        HIPCHK(H->st ? hipStreamSynchronize(H->st) : hipDeviceSynchronize());
+        HIPCHK(quiesce(H));
         delete H->timer;
         H->timer = nullptr;
     }
@@ -3039,7 +3059,7 @@ helm_status helm_set_kernel_timing(helm_t H, int enable) {
 helm_status helm_get_kernel_times(helm_t H, int nclass, int* launches, double* total_ms) {
     if (!H || nclass < 0) return HELM_EINVAL;
     if (!H->timer) return fail(H, HELM_ESTATE, "kernel timing is not enabled");
-    HIPCHK(H->st ? hipStreamSynchronize(H->st) : hipDeviceSynchronize());
+    HIPCHK(quiesce(H));
     H->timer->collect();
     for (int c = 0; c < nclass; ++c) {
         const bool ok = c < helm::K_NCLASS;
@@ -3053,8 +3073,8 @@ const char* helm_last_error(helm_t H) { return H ? H->err.c_str() : g_setup_err.
 
 void helm_destroy(helm_t H) {
     if (!H) return;
-    if (H->st) (void)hipStreamSynchronize(H->st);
-    else (void)hipDeviceSynchronize();
+    OnDevice on(H);
+    (void)quiesce(H);
     for (auto& e : H->apg)
         if (e.exec) (void)hipGraphExecDestroy(e.exec);
     if (H->fuse_ev) (void)hipEventDestroy(H->fuse_ev);

@@ -1,0 +1,129 @@
+"""Host side of device memory, streams and errors, without a GPU: libhelm.so on a HIP runtime
+that only keeps a record (hip_recorder.cpp).  Every scenario runs in a process of its own."""
+import json
+import os
+import subprocess
+import sys
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+
+PRELUDE = """
+import ctypes, json, sys
+import numpy as np
+R = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
+sz, vp = ctypes.c_size_t, ctypes.c_void_p
+R.rec_budget.argtypes = [ctypes.c_int, sz]
+R.rec_room.restype = R.rec_live.restype = R.rec_log_size.restype = sz
+R.rec_kill_stream.argtypes = [vp]
+R.rec_fail_launch.argtypes = R.rec_fail_malloc.argtypes = [ctypes.c_long]
+R.rec_log_text.argtypes = [ctypes.c_char_p, sz]
+from paper_1208_3956_amd import _lib as L
+GB = 1 << 30
+C128, MIXED, FULL, REDUCED = L.HELM_C128, L.HELM_MIXED_C64, L.HELM_FULL, L.HELM_REDUCED
+
+def device(d=None):
+    if d is not None:
+        assert R.hipSetDevice(d) == 0
+    v = ctypes.c_int()
+    R.hipGetDevice(ctypes.byref(v))
+    return v.value
+
+def log():
+    n = R.rec_log_size()
+    b = ctypes.create_string_buffer(n + 1)
+    R.rec_log_text(b, n)
+    out = []
+    for ln in b.value.decode().split("\\n"):
+        if ln:
+            what, p, n, dev = ln.split()
+            out.append((what, int(p, 16), int(n), int(dev)))
+    return out
+
+def setup(n=40, J=3, prec=C128, mode=REDUCED, stream=0, chunk=9, dim=2, **kw):
+    o = L.helm_default_opts(n, n)
+    o.pml_outer, o.pml_iface, o.prec, o.mode, o.chunk, o.dim = 8, 6, prec, mode, chunk, dim
+    o.stream = vp(stream)
+    if dim == 3:
+        o.n[2] = n
+        o.pml_outer, o.pml_iface = 4, 3
+    for k, v in kw.items():
+        setattr(o, k, v)
+    c = 1.0 + 0.3 * np.random.default_rng(1).random((n,) * dim)
+    c = np.ascontiguousarray(c)
+    return L.helm_setup(c.ctypes.data_as(ctypes.POINTER(ctypes.c_double)), 2 * np.pi * n / 13, 1.0 / n, o, J)
+
+def field(H, nrhs):
+    nx, ny, nz, J = L.helm_get_dims3(H)
+    return np.zeros((nrhs, nz * ny * nx), np.complex128)
+
+def status(f, *a):
+    try:
+        f(*a)
+        return 0
+    except L.HelmError as e:
+        return e.status
+"""
+
+
+@pytest.fixture(scope="module")
+def recorder(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("rec") / "hip_recorder.so")
+    subprocess.run(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", "-o", so,
+                    os.path.join(HERE, "hip_recorder.cpp")], check=True)
+    return so
+
+
+def run(recorder, body):
+    p = subprocess.run([sys.executable, "-c", PRELUDE + body, recorder], cwd=ROOT, capture_output=True, text=True,
+                       timeout=300)
+    assert p.returncode == 0, p.stderr[-3000:]
+    return json.loads(p.stdout.splitlines()[-1])
+
+
+def test_destroy_waits_for_the_handles_own_device(recorder):
+    """Memory of a handle on device 1's default stream, closed while device 0 is current, may go to
+    the next handle only after device 1 has been waited for; device 0 stays current."""
+    got = run(recorder, """
+device(1)
+H = setup()
+L.helm_factor(H)
+f = field(H, 2)
+L.helm_apply_P(H, 2, f.ctypes.data, f.copy().ctypes.data)
+device(0)
+R.rec_log(1)
+L.helm_destroy(H)
+print(json.dumps({"syncs": [d for w, p, n, d in log() if w == "devsync"], "frees": [d for w, *_, d in log() if w == "free"],
+                  "now": device()}))
+""")
+    assert got["syncs"] and all(d == 1 for d in got["syncs"]), got
+    assert got["now"] == 0
+
+
+def test_pool_is_bounded_and_given_back(recorder):
+    """At most 8 GB of closed handles' memory stay; a later handle takes from it; an allocation
+    that does not fit otherwise gets all of it back."""
+    got = run(recorder, """
+def one(n, J):
+    H = setup(n=n, J=J)
+    L.helm_factor(H)
+    f = field(H, 1)
+    L.helm_apply_P(H, 1, f.ctypes.data, f.copy().ctypes.data)
+    L.helm_destroy(H)
+one(200, 8)
+small = R.rec_live(0)
+R.rec_log(1)
+one(200, 8)
+again = [n for w, p, n, d in log() if w == "malloc"]
+for n, J in ((400, 16), (500, 20), (600, 24)):
+    one(n, J)
+big = R.rec_live(0)
+R.rec_budget(0, 0)                 # nothing left but what the pool holds
+H = setup(n=100, J=4)
+L.helm_factor(H)
+print(json.dumps({"small": small, "again": again, "big": big}))
+""")
+    assert 0 < got["small"] <= 8 << 30 and got["again"] == []
+    assert 0 < got["big"] <= 8 << 30
