@@ -459,14 +459,21 @@ struct OnDevice {
     OnDevice& operator=(const OnDevice&) = delete;
 };
 
-// waits for the work queued on the handle's stream; the default stream's counterpart is the
-// handle's device, which need not be the current one
+// Waits for the work of the handle: what is queued on its stream (the default stream's counterpart
+// is the handle's device, which need not be the current one) and on the streams it forks work to,
+// which a call that failed half way has not joined
 hipError_t quiesce(helm_t H) {
     OnDevice on(H);
-    return H->st ? hipStreamSynchronize(H->st) : hipDeviceSynchronize();
+    hipError_t r = H->st ? hipStreamSynchronize(H->st) : hipDeviceSynchronize();
+    for (hipStream_t q : {H->st_c[0], H->st_c[1], H->st_fac}) {
+        if (!q) continue;
+        const hipError_t e = hipStreamSynchronize(q);
+        if (r == hipSuccess) r = e;
+    }
+    return r;
 }
 
-// memory of handle H, which only work ordered on its stream uses
+// memory of handle H, which only work ordered on its streams uses
 void dfree(helm_t H, void* p) {
     if (!p) return;
     (void)quiesce(H);
@@ -1145,6 +1152,28 @@ helm_status conc_streams(helm_t H) {
     return HELM_OK;
 }
 
+// Work forked to the streams of conc_streams: a scope left before join() waits for them, so that
+// nothing of a failed call still writes the handle's fields
+struct ConcFork {
+    helm_t H;
+    bool joined = false;
+    explicit ConcFork(helm_t h) : H(h) {}
+    helm_status join() {
+        HIPCHK(hipEventRecord(H->ev_c[1], H->st_c[0]));
+        HIPCHK(hipEventRecord(H->ev_c[2], H->st_c[1]));
+        HIPCHK(hipStreamWaitEvent(H->st, H->ev_c[1], 0));
+        HIPCHK(hipStreamWaitEvent(H->st, H->ev_c[2], 0));
+        joined = true;
+        return HELM_OK;
+    }
+    ~ConcFork() {
+        if (joined) return;
+        for (hipStream_t q : H->st_c) (void)hipStreamSynchronize(q);
+    }
+    ConcFork(const ConcFork&) = delete;
+    ConcFork& operator=(const ConcFork&) = delete;
+};
+
 // Window outputs of a strip: its first two core columns into the window of interface s
 // (s >= 1), its last two into that of interface s + 1 (s <= J - 2).
 helm_status conc_windows(helm_t H, int s, helm::IOSpec& io) {
@@ -1179,6 +1208,7 @@ helm_status sweep_concurrent(helm_t H, int nrhs, const double2* src, bool full, 
     const double ih2 = 1.0 / (g.h * g.h);
     CHK(conc_streams(H));
     const hipStream_t qa = H->st, qb = H->st_c[0], qc = H->st_c[1];
+    ConcFork forked(H);
     HIPCHK(hipEventRecord(H->ev_c[0], qa));
     HIPCHK(hipStreamWaitEvent(qb, H->ev_c[0], 0));
     HIPCHK(hipStreamWaitEvent(qc, H->ev_c[0], 0));
@@ -1252,11 +1282,7 @@ helm_status sweep_concurrent(helm_t H, int nrhs, const double2* src, bool full, 
             CHK(solve_on(H, qc, s, nrhs, io, w.Yw3));
         }
     }
-    HIPCHK(hipEventRecord(H->ev_c[1], qb));
-    HIPCHK(hipEventRecord(H->ev_c[2], qc));
-    HIPCHK(hipStreamWaitEvent(qa, H->ev_c[1], 0));
-    HIPCHK(hipStreamWaitEvent(qa, H->ev_c[2], 0));
-    return HELM_OK;
+    return forked.join();
 }
 
 // out = P_c f on the whole grid
@@ -1289,6 +1315,7 @@ helm_status conc_setup(helm_t H, int nrhs, const double2* f, double2* ut) {
     CHK(conc_streams(H));
     const hipStream_t qs[3] = {H->st, H->st_c[0], H->st_c[1]};
     void* yws[3] = {w.Yw, w.Yw2, w.Yw3};
+    ConcFork forked(H);
     HIPCHK(hipEventRecord(H->ev_c[0], H->st));
     HIPCHK(hipStreamWaitEvent(qs[1], H->ev_c[0], 0));
     HIPCHK(hipStreamWaitEvent(qs[2], H->ev_c[0], 0));
@@ -1301,11 +1328,7 @@ helm_status conc_setup(helm_t H, int nrhs, const double2* f, double2* ut) {
         io.o_lo[0] = io.src_lo; io.o_hi[0] = io.src_hi;
         CHK(solve_on(H, qs[s % 3], s, nrhs, io, yws[s % 3]));
     }
-    HIPCHK(hipEventRecord(H->ev_c[1], qs[1]));
-    HIPCHK(hipEventRecord(H->ev_c[2], qs[2]));
-    HIPCHK(hipStreamWaitEvent(H->st, H->ev_c[1], 0));
-    HIPCHK(hipStreamWaitEvent(H->st, H->ev_c[2], 0));
-    return HELM_OK;
+    return forked.join();
 }
 
 // the preconditioner of the handle's sweep on whole fields
@@ -3079,11 +3102,12 @@ void helm_destroy(helm_t H) {
         if (e.exec) (void)hipGraphExecDestroy(e.exec);
     if (H->fuse_ev) (void)hipEventDestroy(H->fuse_ev);
     if (H->cap_st) (void)hipStreamDestroy(H->cap_st);
-    for (hipStream_t q : H->st_c)
-        if (q) (void)hipStreamDestroy(q);
+    for (hipStream_t* q : {&H->st_c[0], &H->st_c[1], &H->st_fac}) {
+        if (*q) (void)hipStreamDestroy(*q);
+        *q = nullptr;
+    }
     for (hipEvent_t e : H->ev_c)
         if (e) (void)hipEventDestroy(e);
-    if (H->st_fac) (void)hipStreamDestroy(H->st_fac);
     free_work(H);
     delete H->timer;
     if (H->F != H->F64) dfree(H, H->F);

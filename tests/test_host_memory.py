@@ -102,6 +102,36 @@ print(json.dumps({"syncs": [d for w, p, n, d in log() if w == "devsync"], "frees
     assert got["now"] == 0
 
 
+@pytest.mark.parametrize("dim,kw", [(2, "sweep=1, mode=FULL"), (2, "sweep=1"), (3, "mode=FULL, prec=MIXED"), (3, "mode=FULL")])
+def test_forked_streams_are_waited_for_after_an_error(recorder, dim, kw):
+    """A launch that fails while work runs on streams the handle forked to: every stream that got
+    work is waited for before the handle's memory can go to another one."""
+    got = run(recorder, f"""
+bad = []
+for after in range(1, 60, 7):
+    H = setup(n=10 if {dim} == 3 else 40, dim={dim}, stream=0x10, {kw})
+    R.rec_log(1)
+    if {dim} == 3:
+        R.rec_fail_launch(after)
+        st = status(L.helm_factor, H)
+    else:
+        L.helm_factor(H)
+        f = field(H, 2)
+        R.rec_log(1)
+        R.rec_fail_launch(after)
+        st = status(L.helm_apply_P, H, 2, f.ctypes.data, f.copy().ctypes.data)
+    R.rec_fail_launch(-1)
+    L.helm_destroy(H)
+    last = {{}}
+    for i, (w, p, n, d) in enumerate(log()):
+        if w in ("launch", "sync"):
+            last.setdefault(p, [-1, -1])[w == "sync"] = i
+    bad += [(after, st, s) for s, (a, b) in last.items() if a > b]
+print(json.dumps({{"bad": bad}}))
+""")
+    assert got["bad"] == [], got
+
+
 def test_pool_is_bounded_and_given_back(recorder):
     """At most 8 GB of closed handles' memory stay; a later handle takes from it; an allocation
     that does not fit otherwise gets all of it back."""
