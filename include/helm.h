@@ -79,7 +79,8 @@ typedef struct {
     int max_iter;       /* GMRES iteration cap; <= 0 selects 200                          */
     int chunk;          /* rows per chunk of the y-partitioned strip solver; 0 = auto
                            (2-D only: a 3-D slab is one chunk)                           */
-    void* stream;       /* hipStream_t for all device work; NULL = default stream        */
+    void* stream;       /* hipStream_t for all device work; NULL = default stream.  It has to
+                           outlive the handle                                             */
     int graph;          /* 1 (default): in REDUCED mode, capture one application of
                            Algorithm 3 per right-hand-side count into a HIP graph and replay
                            it in every GMRES iteration (its input is first copied into a

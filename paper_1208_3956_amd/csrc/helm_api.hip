@@ -427,6 +427,12 @@ struct Pool {
         idle[{b.dev, b.size}].push_back({++tick, p});
         cached[b.dev] += b.size;
     }
+    // a block that some work may still use (its stream could not be waited for) is not kept:
+    // hipFree waits for the device
+    void drop(void* p) {
+        std::lock_guard<std::mutex> lk(mu);
+        if (live.erase(p)) (void)hipFree(p);
+    }
     size_t idle_bytes() {
         int dev = 0;
         (void)hipGetDevice(&dev);
@@ -476,8 +482,8 @@ hipError_t quiesce(helm_t H) {
 // memory of handle H, which only work ordered on its streams uses
 void dfree(helm_t H, void* p) {
     if (!p) return;
-    (void)quiesce(H);
-    Pool::get().put(p);
+    if (quiesce(H) == hipSuccess) Pool::get().put(p);
+    else Pool::get().drop(p);
 }
 
 // free device memory, the pool's idle blocks included (an allocation that needs them gets them)

@@ -132,6 +132,20 @@ print(json.dumps({{"bad": bad}}))
     assert got["bad"] == [], got
 
 
+def test_memory_of_a_stream_that_cannot_be_waited_for_is_freed(recorder):
+    """The caller destroyed its stream before the handle: nothing may be kept for later handles."""
+    got = run(recorder, """
+H = setup(stream=0x10)
+L.helm_factor(H)
+f = field(H, 2)
+L.helm_apply_P(H, 2, f.ctypes.data, f.copy().ctypes.data)
+R.rec_kill_stream(vp(0x10))
+L.helm_destroy(H)
+print(json.dumps({"live": R.rec_live(0)}))
+""")
+    assert got["live"] == 0, got
+
+
 def test_pool_is_bounded_and_given_back(recorder):
     """At most 8 GB of closed handles' memory stay; a later handle takes from it; an allocation
     that does not fit otherwise gets all of it back."""
