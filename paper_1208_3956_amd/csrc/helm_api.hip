@@ -360,11 +360,12 @@ helm_status fail(helm_t H, helm_status code, const std::string& msg) {
 // used it has been synchronised, so that any thread may take it for any stream.
 struct Pool {
     static constexpr size_t POOL_BYTES = (size_t)8 << 30;
-    struct Block { size_t size; int dev; unsigned long tick; };
+    static constexpr int MAX_DEV = 64;
+    struct Block { size_t size; int dev; };
     std::mutex mu;
     std::unordered_map<void*, Block> live;                              // every block handed out
     std::map<std::pair<int, size_t>, std::vector<std::pair<unsigned long, void*>>> idle;   // by device and size
-    std::unordered_map<int, size_t> cached;
+    size_t cached[MAX_DEV] = {};
     unsigned long tick = 0;
 
     static Pool& get() {
@@ -381,10 +382,10 @@ struct Pool {
         if (it == idle.end() || it->first.first != dev || it->first.second > n + n / 4) return nullptr;
         void* p = it->second.back().second;
         const size_t sz = it->first.second;
+        live[p] = Block{sz, dev};                    // may throw: nothing has changed yet
         it->second.pop_back();
         if (it->second.empty()) idle.erase(it);
         cached[dev] -= sz;
-        live[p] = Block{sz, dev, 0};
         return p;
     }
     // with mu held: frees idle blocks of dev, oldest first, until at most `keep` bytes stay
@@ -404,17 +405,29 @@ struct Pool {
         const size_t n = round(bytes);
         int dev = 0;
         (void)hipGetDevice(&dev);
+        *p = nullptr;
+        if (dev < 0 || dev >= MAX_DEV) return hipErrorInvalidDevice;
         std::lock_guard<std::mutex> lk(mu);
-        if ((*p = take(dev, n))) return hipSuccess;
-        hipError_t e = hipMalloc(p, n);
-        if (e != hipSuccess && cached[dev] > 0) {
-            (void)hipGetLastError();
-            trim(dev, 0);
-            e = hipMalloc(p, n);
+        try {
+            if ((*p = take(dev, n))) return hipSuccess;
+            hipError_t e = hipMalloc(p, n);
+            if (e != hipSuccess && cached[dev] > 0) {
+                (void)hipGetLastError();
+                trim(dev, 0);
+                e = hipMalloc(p, n);
+            }
+            if (e != hipSuccess) {
+                *p = nullptr;
+                (void)hipGetLastError();
+                return e;
+            }
+            live[*p] = Block{n, dev};
+            return hipSuccess;
+        } catch (const std::bad_alloc&) {            // no host memory for the record of the block
+            if (*p) (void)hipFree(*p);
+            *p = nullptr;
+            return hipErrorOutOfMemory;
         }
-        if (e == hipSuccess) live[*p] = Block{n, dev, 0};
-        else { *p = nullptr; (void)hipGetLastError(); }
-        return e;
     }
     void put(void* p) {
         std::lock_guard<std::mutex> lk(mu);
@@ -424,8 +437,15 @@ struct Pool {
         live.erase(it);
         if (b.size > POOL_BYTES) { (void)hipFree(p); return; }
         trim(b.dev, POOL_BYTES - b.size);
-        idle[{b.dev, b.size}].push_back({++tick, p});
-        cached[b.dev] += b.size;
+        auto at = idle.end();
+        try {                                        // called from destructors
+            at = idle.try_emplace({b.dev, b.size}).first;
+            at->second.push_back({++tick, p});
+            cached[b.dev] += b.size;
+        } catch (const std::bad_alloc&) {
+            if (at != idle.end() && at->second.empty()) idle.erase(at);
+            (void)hipFree(p);
+        }
     }
     // a block that some work may still use (its stream could not be waited for) is not kept:
     // hipFree waits for the device
@@ -437,7 +457,7 @@ struct Pool {
         int dev = 0;
         (void)hipGetDevice(&dev);
         std::lock_guard<std::mutex> lk(mu);
-        return cached[dev];
+        return dev >= 0 && dev < MAX_DEV ? cached[dev] : 0;
     }
 };
 

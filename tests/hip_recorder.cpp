@@ -8,6 +8,7 @@
 #include <cstring>
 #include <map>
 #include <mutex>
+#include <new>
 #include <set>
 #include <string>
 #include <sys/mman.h>
@@ -22,6 +23,7 @@ std::set<void*> dead_streams;
 size_t room[NDEV] = {(size_t)64 << 30, (size_t)64 << 30};
 long fail_launch = -1;        // launches until hipGetLastError reports one failed
 long fail_malloc = -1;        // allocations until one fails (the budget apart)
+thread_local long fail_new = 0;   // host allocations of this thread that fail from here on
 int last_error = 0;
 std::string log_text;
 bool logging = false;
@@ -39,8 +41,17 @@ void note(const char* what, const void* p, size_t n = 0) {
 void* fresh() { return (void*)(handles += 16); }
 }  // namespace
 
+void* operator new(size_t n) {
+    if (fail_new > 0) { --fail_new; throw std::bad_alloc(); }
+    if (void* p = std::malloc(n ? n : 1)) return p;
+    throw std::bad_alloc();
+}
+void operator delete(void* p) noexcept { std::free(p); }
+void operator delete(void* p, size_t) noexcept { std::free(p); }
+
 extern "C" {
 // ---- the test's side
+void rec_fail_new(long n) { fail_new = n; }
 void rec_budget(int dev, size_t bytes) { LOCK; room[dev] = bytes; }
 size_t rec_room(int dev) { LOCK; return room[dev]; }
 size_t rec_live(int dev) {

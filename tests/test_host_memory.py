@@ -18,7 +18,7 @@ sz, vp = ctypes.c_size_t, ctypes.c_void_p
 R.rec_budget.argtypes = [ctypes.c_int, sz]
 R.rec_room.restype = R.rec_live.restype = R.rec_log_size.restype = sz
 R.rec_kill_stream.argtypes = [vp]
-R.rec_fail_launch.argtypes = R.rec_fail_malloc.argtypes = [ctypes.c_long]
+R.rec_fail_launch.argtypes = R.rec_fail_malloc.argtypes = R.rec_fail_new.argtypes = [ctypes.c_long]
 R.rec_log_text.argtypes = [ctypes.c_char_p, sz]
 from paper_1208_3956_amd import _lib as L
 GB = 1 << 30
@@ -171,3 +171,27 @@ print(json.dumps({"small": small, "again": again, "big": big}))
 """)
     assert 0 < got["small"] <= 8 << 30 and got["again"] == []
     assert 0 < got["big"] <= 8 << 30
+
+
+def test_no_host_memory_for_the_pools_records(recorder):
+    """Host allocations that fail in the pool neither end the process (blocks are given back from
+    destructors) nor leave the C ABI as an exception, and lose no device memory."""
+    got = run(recorder, """
+f = np.zeros(1 << 20)
+out = []
+for many in (1, 2, 3, 1 << 30):
+    H = setup(n=30, J=2, stream=0x10)
+    L.helm_factor(H)
+    R.rec_fail_new(1)              # the record of the next block
+    st = status(L.helm_strip_solve, H, 0, 1, f.ctypes.data, f.ctypes.data)
+    again = status(L.helm_strip_solve, H, 0, 1, f.ctypes.data, f.ctypes.data)
+    R.rec_fail_new(many)
+    L.helm_destroy(H)
+    R.rec_fail_new(0)
+    out.append((st, again))
+live = R.rec_live(0)               # of the last: nothing could be kept
+R.rec_budget(0, 64 << 20)
+H = setup(n=100, J=4)              # takes what the pool still holds
+print(json.dumps({"out": out, "live": live, "ok": status(L.helm_factor, H) in (0, 2)}))
+""")
+    assert all(st == 2 and again == 0 for st, again in got["out"]) and got["ok"], got
