@@ -395,9 +395,14 @@ helm_status helm_set_kernel_timing(helm_t H, int enable);
 helm_status helm_get_kernel_times(helm_t H, int nclass, int* launches, double* total_ms);
 
 const char* helm_last_error(helm_t H);
-/* Up to 8 GB per device of the memory of destroyed handles stay allocated in the process, for
- * later handles; an allocation of the library that fails gives all of it back first. */
+/* Up to 8 GB per device of the memory of destroyed handles (and of work arrays that live handles
+ * have given up) stay allocated in the process, for later handles; an allocation of the library
+ * that fails gives all of it back first. */
 void helm_destroy(helm_t H);
+
+/* Gives that memory back to the driver, on every device, for other allocators of the process.
+ * Live handles keep theirs.  Any thread may call it at any time. */
+void helm_empty_cache(void);
 
 #ifdef __cplusplus
 }

@@ -24,7 +24,7 @@ EXPORTS = ["helm_default_opts", "helm_setup", "helm_factor", "helm_solve", "helm
            "helm_get_kernel_times", "helm_last_error", "helm_destroy", "helm_grad",
            "helm_solve_batch", "helm_get_dims3", "helm_autotune", "helm_get_factor_path",
            "helm_get_factor_slots", "helm_strip_solve_noalloc", "helm_get_panel_stats",
-           "helm_get_fusion_stats"]
+           "helm_get_fusion_stats", "helm_empty_cache"]
 KERNEL_CLASSES = ["phase_a", "phase_b", "phase_c", "factor_chunks", "factor_separators",
                   "stencil", "gmres_vectors", "other"]
 
@@ -105,9 +105,11 @@ def lib() -> ctypes.CDLL:
     L.helm_last_error.restype = ctypes.c_char_p
     L.helm_destroy.argtypes = [vp]
     L.helm_destroy.restype = None
+    L.helm_empty_cache.argtypes = []
+    L.helm_empty_cache.restype = None
     for name in EXPORTS:
         fn = getattr(L, name)
-        if name not in ("helm_default_opts", "helm_last_error", "helm_destroy"):
+        if name not in ("helm_default_opts", "helm_last_error", "helm_destroy", "helm_empty_cache"):
             fn.restype = ctypes.c_int
     _lib = L
     return L
@@ -300,3 +302,7 @@ def helm_last_error(hdl) -> str:
 
 def helm_destroy(hdl) -> None:
     lib().helm_destroy(hdl)
+
+
+def helm_empty_cache() -> None:
+    lib().helm_empty_cache()

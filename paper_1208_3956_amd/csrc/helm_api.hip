@@ -453,6 +453,10 @@ struct Pool {
         std::lock_guard<std::mutex> lk(mu);
         if (live.erase(p)) (void)hipFree(p);
     }
+    void give_back() {
+        std::lock_guard<std::mutex> lk(mu);
+        for (int dev = 0; dev < MAX_DEV; ++dev) trim(dev, 0);
+    }
     size_t idle_bytes() {
         int dev = 0;
         (void)hipGetDevice(&dev);
@@ -3119,6 +3123,8 @@ helm_status helm_get_kernel_times(helm_t H, int nclass, int* launches, double* t
 }
 
 const char* helm_last_error(helm_t H) { return H ? H->err.c_str() : g_setup_err.c_str(); }
+
+void helm_empty_cache(void) { Pool::get().give_back(); }
 
 void helm_destroy(helm_t H) {
     if (!H) return;

@@ -195,3 +195,22 @@ H = setup(n=100, J=4)              # takes what the pool still holds
 print(json.dumps({"out": out, "live": live, "ok": status(L.helm_factor, H) in (0, 2)}))
 """)
     assert all(st == 2 and again == 0 for st, again in got["out"]) and got["ok"], got
+
+
+def test_kept_memory_is_given_back_on_request(recorder):
+    """Other allocators of the process can have what closed handles left; a live handle keeps its own."""
+    got = run(recorder, """
+from paper_1208_3956_amd import empty_cache
+A = setup(n=40, J=3)
+L.helm_factor(A)
+own = R.rec_live(0)
+device(1)
+B = setup(n=60, J=3)
+L.helm_factor(B)
+L.helm_destroy(B)
+device(0)
+kept = R.rec_live(1)
+empty_cache()
+print(json.dumps({"own": own, "kept": kept, "after": [R.rec_live(0), R.rec_live(1)]}))
+""")
+    assert got["kept"] > 0 and got["after"] == [got["own"], 0], got
