@@ -267,7 +267,7 @@ helm_status helm_grad(helm_t H, int nsrc, const void* src, int nrec, const int64
 /*
  * The preconditioner alone (Sec. 2.1, end): out = P f = v + w for nrhs fields, computed
  * in the handle's precision (opts.sweep = 1: P_c f = v + w' - z).  f, out: device,
- * nrhs * N_y * N_x complex128.
+ * nrhs * N_y * N_x complex128; they may overlap.
  */
 helm_status helm_apply_P(helm_t H, int nrhs, const void* f, void* out);
 

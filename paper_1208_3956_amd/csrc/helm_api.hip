@@ -10,6 +10,7 @@
 #include <complex>
 #include <cstdio>
 #include <cstdlib>
+#include <cstdint>
 #include <cstring>
 #include <string>
 #include <condition_variable>
@@ -1103,6 +1104,14 @@ helm_status apply_P_full(helm_t H, int nrhs, const double2* f, double2* out) {
     // complex64 solves three batches instead of 2 J - 1 single strips: worth it while a
     // single strip fills at most half of the 256 CUs
     if (batched(H) && (H->prec == HELM_C128 || H->ch.P * ((nrhs + 15) / 16) <= 128)) {
+        // f is read after parts of out are written: where the two overlap the batches read a copy
+        // (V is the sequential sweeps')
+        const std::uintptr_t fa = reinterpret_cast<std::uintptr_t>(f), oa = reinterpret_cast<std::uintptr_t>(out);
+        const size_t fb = field_bytes(H, nrhs);
+        if (fa < oa + fb && oa < fa + fb) {
+            HIPCHK(hipMemcpyAsync(w.V, f, fb, hipMemcpyDeviceToDevice, H->st));
+            f = w.V;
+        }
         CHK(strip_batch_any(H, nrhs, 1, f, nullptr));
         return field_of_P(H, nrhs, f, nullptr, true, out);
     }

@@ -1,0 +1,61 @@
+"""What one call leaves for the next in the batches of strips and the dense reduced operators:
+fields in place, panels of another width, values that are not finite."""
+import numpy as np
+import pytest
+
+import workloads as W
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+
+
+def _handle(prec, mode, n=150, J=5, chunk=9, **kw):
+    from paper_1208_3956_amd import Helmholtz
+    c = 1.0 + 0.4 * np.random.default_rng(n).random((n, n))
+    wl = W.small(n=n, J=J, w_out=6, w=5, c=c, nsrc=1, seed=n + 1)
+    return Helmholtz(wl.c, wl.omega, wl.h, wl.J, wl.w_out, wl.w, prec=prec, mode=mode, chunk=chunk, device=DEV,
+                     **kw).factor()
+
+
+def _field(H, nrhs, seed=0, cols=None):
+    r = np.random.default_rng(seed)
+    shape = (nrhs, H.N_y, H.N_x if cols is None else cols)
+    return torch.from_numpy(r.standard_normal(shape) + 1j * r.standard_normal(shape)).to(DEV)
+
+
+@pytest.mark.parametrize("prec", ["c128", "mixed"])
+@pytest.mark.parametrize("nrhs,shift", [(1, 0), (5, 0), (5, 1), (17, 0)])
+def test_P_in_place(prec, nrhs, shift):
+    """out may be f itself, or lie over a part of it (shifted by one right-hand side)."""
+    from paper_1208_3956_amd import _lib as L
+    H = _handle(prec, "full")
+    buf = _field(H, nrhs + shift)
+    want = H.apply_P(buf[shift:].clone())
+    with torch.cuda.device(H.device):
+        L.helm_apply_P(H.h, nrhs, buf[shift:].data_ptr(), buf.data_ptr())
+    H.stream.synchronize()
+    assert torch.equal(buf[:nrhs], want)
+    H.close()
+
+
+# 162 padded rows: chunks joined to 72 (tiles of 16 rows padded, a ragged last chunk), 64, 128 rows
+@pytest.mark.parametrize("prec", ["c128", "mixed"])
+@pytest.mark.parametrize("chunk", [9, 16, 32])
+def test_narrower_panel_after_infinities(prec, chunk):
+    """The panels of a call lie where those of a wider one were: bit for bit what a fresh handle gives."""
+    A, B = _handle(prec, "full", chunk=chunk), _handle(prec, "full", chunk=chunk)
+    f, psi = _field(A, 33, 1), _field(A, 33, 2, 2 * (A.J - 1))
+    calls = [(A.apply_P, B.apply_P, f), (A.apply_AP_reduced, B.apply_AP_reduced, psi),
+             (A.restart_rhs_reduced, B.restart_rhs_reduced, f)]
+    for a, _, x in calls:
+        bad = x.clone()
+        bad[::2] = complex(float("inf"), 0.0)
+        bad[1::2] = complex(float("nan"), float("nan"))
+        a(bad)
+    for nrhs in (17, 16, 3, 33):
+        for a, b, x in calls:
+            assert torch.equal(a(x[:nrhs]), b(x[:nrhs])), (a.__name__, nrhs)
+    A.close()
+    B.close()
