@@ -490,6 +490,9 @@ struct OnDevice {
     OnDevice& operator=(const OnDevice&) = delete;
 };
 
+// memory that something can do without: false, and no error, where there is none
+bool try_alloc(void** p, size_t bytes) { return Pool::get().alloc(p, std::max<size_t>(bytes, 16)) == hipSuccess; }
+
 // Waits for the work of the handle: what is queued on its stream (the default stream's counterpart
 // is the handle's device, which need not be the current one) and on the streams it forks work to,
 // which a call that failed half way has not joined
@@ -1436,10 +1439,20 @@ helm_status apply_P_any(helm_t H, int nrhs, const double2* f, double2* out) {
     return H->sweep == 1 ? apply_Pc_full(H, nrhs, f, out) : apply_P_full(H, nrhs, f, out);
 }
 
+void free_reduced(helm_t H) {
+    for (void** p : {&H->red_T, &H->red_R, &H->red_S, &H->red_ws}) {
+        dfree(H, *p);
+        *p = nullptr;
+    }
+    H->red_m = 0;
+    H->red = helm::RedPlan();
+    H->red_gen += 1;
+}
+
 // The dense strip operators of the reduced sweeps, after the factorisation (2-D, double sweep
 // with PML transmission).  Their memory and the build's workspace are kept for the handle's
-// life; where they would take more than half of what is free the sweeps keep the block
-// substitutions.
+// life; where they would take more than half of what is free, or cannot be had, the sweeps keep
+// the block substitutions.
 helm_status build_reduced(helm_t H) {
     const auto& g = H->g;
     // a full-form handle uses them for the sweeps of P (see batched)
@@ -1451,18 +1464,15 @@ helm_status build_reduced(helm_t H) {
     const size_t nf = (size_t)H->nfac;
     if (!p.kappa) { H->red = p; return HELM_OK; }
     if (H->red_m != H->ch.m) {
-        dfree(H, H->red_T); dfree(H, H->red_R); dfree(H, H->red_S); dfree(H, H->red_ws);
-        H->red_T = H->red_R = H->red_S = H->red_ws = nullptr;
-        H->red_m = 0;
-        H->red = helm::RedPlan();
-        H->red_gen += 1;
+        free_reduced(H);
         size_t freeb = 0;
         HIPCHK(free_bytes(&freeb));
         if (nf * (2 * p.tsz + 2 * p.rsz + p.ssz) * esz + bs.bytes > freeb / 2) return HELM_OK;
-        CHK(dmalloc(H, &H->red_T, nf * 2 * p.tsz * esz));
-        CHK(dmalloc(H, &H->red_R, nf * 2 * p.rsz * esz));
-        CHK(dmalloc(H, &H->red_S, nf * p.ssz * esz));
-        CHK(dmalloc(H, &H->red_ws, bs.bytes));
+        if (!try_alloc(&H->red_T, nf * 2 * p.tsz * esz) || !try_alloc(&H->red_R, nf * 2 * p.rsz * esz) ||
+            !try_alloc(&H->red_S, nf * p.ssz * esz) || !try_alloc(&H->red_ws, bs.bytes)) {
+            free_reduced(H);
+            return HELM_OK;
+        }
         H->red_m = H->ch.m;
     }
     if (!H->red_T) return HELM_OK;

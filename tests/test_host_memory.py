@@ -214,3 +214,52 @@ empty_cache()
 print(json.dumps({"own": own, "kept": kept, "after": [R.rec_live(0), R.rec_live(1)]}))
 """)
     assert got["kept"] > 0 and got["after"] == [got["own"], 0], got
+
+
+@pytest.mark.parametrize("prec", ["C128", "MIXED"])
+@pytest.mark.parametrize("mode", ["REDUCED", "FULL"])
+def test_dense_operators_that_cannot_be_allocated(recorder, prec, mode):
+    """The block factors alone serve a handle: whichever allocation of the dense strip operators
+    fails, P, the reduced operator and a solve run."""
+    got = run(recorder, f"""
+from paper_1208_3956_amd import empty_cache
+def mallocs(f):
+    R.rec_log(1)
+    st = f()
+    n = sum(w == "malloc" for w, *_ in log())
+    R.rec_log(0)
+    return st, n
+def use(H):
+    f, psi = field(H, 2), np.zeros((2, 56 * 4), np.complex128)
+    return [status(L.helm_apply_P, H, 2, f.ctypes.data, f.copy().ctypes.data),
+            status(L.helm_apply_AP_reduced, H, 2, psi.ctypes.data, psi.copy().ctypes.data),
+            status(L.helm_solve, H, 2, f.ctypes.data, f.copy().ctypes.data, 1e-6)]
+A, B = setup(prec={prec}, mode=FULL, batch_fuse=1), setup(prec={prec}, mode={mode})
+_, blocks = mallocs(lambda: L.helm_factor(A))        # a handle that never has dense operators
+def all_of_it():
+    L.helm_factor(B)
+    return use(B)
+st, every = mallocs(all_of_it)
+assert st == [0, 0, 0]
+bad = []
+for k in range(blocks, blocks + 6):
+    empty_cache()
+    H = setup(prec={prec}, mode={mode})
+    R.rec_fail_malloc(k)
+    st = [status(L.helm_factor, H)]
+    R.rec_fail_malloc(-1)
+    st += use(H) if st == [0] else []
+    L.helm_destroy(H)
+    if st != [0, 0, 0, 0]:
+        bad.append((k, st))
+empty_cache()
+H = setup(prec={prec}, mode={mode}, n=200, J=8)
+L.helm_factor(H)
+own = R.rec_live(0)
+L.helm_destroy(H)
+empty_cache()
+R.rec_budget(0, own * 2 // 3)                         # they would take more than half of what is free
+H = setup(prec={prec}, mode={mode}, n=200, J=8)
+print(json.dumps({{"bad": bad, "blocks": blocks, "every": every, "tight": status(L.helm_factor, H)}}))
+""")
+    assert got["bad"] == [] and got["tight"] == 0 and got["every"] > got["blocks"] > 0, got
