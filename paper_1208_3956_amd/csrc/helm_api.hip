@@ -153,8 +153,6 @@ struct helm_problem {
     // dense strip operators of the reduced form (kernels_reduced.hip): in use when red.kappa > 0
     helm::RedPlan red;
     void *red_T = nullptr, *red_R = nullptr, *red_S = nullptr;
-    void* red_ws = nullptr;     // build workspace
-    size_t red_ws_bytes = 0;
     long red_gen = 0;           // generation of the plan and its buffers
     int red_m = 0;              // rows per fine chunk they were laid out for
     // per-strip tables of the batches of strips, J entries each (kinds of strip_batch)
@@ -1440,7 +1438,7 @@ helm_status apply_P_any(helm_t H, int nrhs, const double2* f, double2* out) {
 }
 
 void free_reduced(helm_t H) {
-    for (void** p : {&H->red_T, &H->red_R, &H->red_S, &H->red_ws}) {
+    for (void** p : {&H->red_T, &H->red_R, &H->red_S}) {
         dfree(H, *p);
         *p = nullptr;
     }
@@ -1450,8 +1448,9 @@ void free_reduced(helm_t H) {
 }
 
 // The dense strip operators of the reduced sweeps, after the factorisation (2-D, double sweep
-// with PML transmission).  Their memory and the build's workspace are kept for the handle's
-// life; where they would take more than half of what is free, or cannot be had, the sweeps keep
+// with PML transmission).  Their memory is kept for the handle's life, the build's workspace (2 GB
+// where there are many strips) goes back to the pool, which has it for the next factorisation of
+// any handle; where they would take more than half of what is free, or cannot be had, the sweeps keep
 // the block substitutions.
 helm_status build_reduced(helm_t H) {
     const auto& g = H->g;
@@ -1469,15 +1468,22 @@ helm_status build_reduced(helm_t H) {
         HIPCHK(free_bytes(&freeb));
         if (nf * (2 * p.tsz + 2 * p.rsz + p.ssz) * esz + bs.bytes > freeb / 2) return HELM_OK;
         if (!try_alloc(&H->red_T, nf * 2 * p.tsz * esz) || !try_alloc(&H->red_R, nf * 2 * p.rsz * esz) ||
-            !try_alloc(&H->red_S, nf * p.ssz * esz) || !try_alloc(&H->red_ws, bs.bytes)) {
+            !try_alloc(&H->red_S, nf * p.ssz * esz)) {
             free_reduced(H);
             return HELM_OK;
         }
         H->red_m = H->ch.m;
     }
     if (!H->red_T) return HELM_OK;
+    struct Ws {
+        helm_t H;
+        void* p = nullptr;
+        ~Ws() { dfree(H, p); }
+    } w{H};
+    H->red = helm::RedPlan();
+    if (!try_alloc(&w.p, bs.bytes)) return HELM_OK;
     H->red = p;
-    double2* ws = static_cast<double2*>(H->red_ws);
+    double2* ws = static_cast<double2*>(w.p);
     if (H->prec == HELM_C128)
         HIPCHK(TIMED(H, helm::K_OTHER,
                      helm::launch_red_build<double>(p, bs, H->tf, H->gf, H->ch, H->nfac, H->F64, ws, H->d_err + 1,
@@ -3171,7 +3177,6 @@ void helm_destroy(helm_t H) {
     dfree(H, H->red_T);
     dfree(H, H->red_R);
     dfree(H, H->red_S);
-    dfree(H, H->red_ws);
     dfree(H, H->d_err);
     for (void* p : H->owned) dfree(H, p);
     delete H;

@@ -139,6 +139,7 @@ H = setup(stream=0x10)
 L.helm_factor(H)
 f = field(H, 2)
 L.helm_apply_P(H, 2, f.ctypes.data, f.copy().ctypes.data)
+L.helm_empty_cache()
 R.rec_kill_stream(vp(0x10))
 L.helm_destroy(H)
 print(json.dumps({"live": R.rec_live(0)}))
@@ -203,6 +204,7 @@ def test_kept_memory_is_given_back_on_request(recorder):
 from paper_1208_3956_amd import empty_cache
 A = setup(n=40, J=3)
 L.helm_factor(A)
+empty_cache()
 own = R.rec_live(0)
 device(1)
 B = setup(n=60, J=3)
@@ -263,3 +265,28 @@ H = setup(prec={prec}, mode={mode}, n=200, J=8)
 print(json.dumps({{"bad": bad, "blocks": blocks, "every": every, "tight": status(L.helm_factor, H)}}))
 """)
     assert got["bad"] == [] and got["tight"] == 0 and got["every"] > got["blocks"] > 0, got
+
+
+def test_build_workspace_is_shared(recorder):
+    """The workspace in which the dense operators are built is nobody's afterwards: a second handle's
+    factorisation takes it from the pool, and it can be given back while both live."""
+    got = run(recorder, """
+from paper_1208_3956_amd import empty_cache
+def mallocs(f):
+    R.rec_log(1)
+    f()
+    return sorted(n for w, p, n, d in log() if w == "malloc")
+A, B = setup(n=200, J=8), setup(n=200, J=8)
+a, b = mallocs(lambda: L.helm_factor(A)), mallocs(lambda: L.helm_factor(B))
+again = mallocs(lambda: L.helm_factor(A))
+R.rec_log(1)
+empty_cache()
+freed = [n for w, p, n, d in log() if w == "free"]
+f = field(B, 1)
+print(json.dumps({"a": a, "b": b, "again": again, "freed": freed,
+                  "st": status(L.helm_solve, B, 1, f.ctypes.data, f.copy().ctypes.data, 1e-6)}))
+""")
+    left = list(got["a"])
+    for n in got["b"]:
+        left.remove(n)
+    assert len(left) == 1 and got["freed"] == left and got["again"] == [] and got["st"] == 0, got
