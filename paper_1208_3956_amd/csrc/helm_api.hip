@@ -75,11 +75,10 @@ struct Work {
     void *rp = nullptr, *rpd = nullptr, *rrh = nullptr, *rxs = nullptr;   // rp upward, rpd downward
     int rnrhs = 0;
     long rgen = -1;
-    // batches of strips: strip-solver workspace of bstrips strips, and the window field of
+    // batches of strips: strip-solver workspace of several strips, and the window field of
     // the strips' solutions of a full field (the base of an upward sweep)
     void* Yb = nullptr;
     double2* Vb = nullptr;
-    int bstrips = 0, bnrhs = 0, bP = 0;
     size_t bcap = 0;            // strips x right-hand sides Yb holds
     double2* basis_old = nullptr;   // the previous cycle's basis, kept through a restart
     int mcap_old = 0;
@@ -464,11 +463,17 @@ struct Pool {
     }
 };
 
+bool release_dense(helm_t H);
+
+// Device memory of handle H.  The dense strip operators and what goes with them can be done without:
+// where there is no room otherwise they make it, and the handle's sweeps go on in the block
+// substitutions.  (So nothing may be allocated between the calls that use them.)
 template <typename P>
 helm_status dmalloc(helm_t H, P** p, size_t bytes) {
     *p = nullptr;
     if (bytes == 0) bytes = 16;
     hipError_t e = Pool::get().alloc((void**)p, bytes);
+    if (e != hipSuccess && release_dense(H)) e = Pool::get().alloc((void**)p, bytes);
     if (e != hipSuccess)
         return fail(H, HELM_ENOMEM, "hipMalloc of " + std::to_string(bytes) + " bytes failed: " +
                                         hipGetErrorString(e));
@@ -844,27 +849,42 @@ helm_status sweep_down(helm_t H, int nrhs, double2* dst, bool full) {
 
 // Panels of the dense reduced operators for nrhs right-hand sides.  Rows beyond a chunk's
 // last and the separator slots outside the strip are never written: they must read as zero.
+// Whether a call of nrhs right-hand sides runs its reduced sweeps on the dense operators: their
+// panels are there (prepare_dense)
+bool dense(helm_t H, int nrhs) {
+    const Work& w = H->wk;
+    return H->red.kappa > 0 && w.rxs && w.rnrhs >= nrhs && w.rgen == H->red_gen;
+}
+
+void free_panels(helm_t H) {
+    Work& w = H->wk;
+    for (void** p : {&w.rp, &w.rpd, &w.rrh, &w.rxs}) {
+        dfree(H, *p);
+        *p = nullptr;
+    }
+    w.rnrhs = 0;
+    H->ws_epoch += 1;
+}
+
 helm_status ensure_red_ws(helm_t H, int nrhs) {
     Work& w = H->wk;
     const auto& p = H->red;
     const int G = (nrhs + 15) / 16;
-    if (!p.kappa || (w.rp && w.rnrhs >= nrhs && w.rgen == H->red_gen)) return HELM_OK;
-    dfree(H, w.rp); dfree(H, w.rpd); dfree(H, w.rrh); dfree(H, w.rxs);
-    w.rp = w.rpd = w.rrh = w.rxs = nullptr;
-    w.rnrhs = 0;
-    H->ws_epoch += 1;
+    if (!p.kappa || dense(H, nrhs)) return HELM_OK;
+    free_panels(H);
     const size_t esz = H->prec == HELM_C128 ? sizeof(double2) : sizeof(float2);
     const size_t pb = (size_t)H->g.J * G * p.P * 3 * p.Mp * 16 * esz;
     const size_t xb = (size_t)G * (p.ns + 2) * WP * 16 * esz;
-    CHK(dmalloc(H, &w.rp, pb));
-    CHK(dmalloc(H, &w.rpd, pb));
-    HIPCHK(hipMemsetAsync(w.rpd, 0, pb, H->st));
-    CHK(dmalloc(H, &w.rrh, (size_t)G * p.ns * WP * 16 * esz));
-    CHK(dmalloc(H, &w.rxs, xb));
-    HIPCHK(hipMemsetAsync(w.rp, 0, pb, H->st));
-    HIPCHK(hipMemsetAsync(w.rxs, 0, xb, H->st));
+    if (!try_alloc(&w.rp, pb) || !try_alloc(&w.rpd, pb) || !try_alloc(&w.rrh, (size_t)G * p.ns * WP * 16 * esz) ||
+        !try_alloc(&w.rxs, xb)) {
+        free_panels(H);
+        return HELM_OK;
+    }
     w.rnrhs = nrhs;
     w.rgen = H->red_gen;
+    HIPCHK(hipMemsetAsync(w.rp, 0, pb, H->st));
+    HIPCHK(hipMemsetAsync(w.rpd, 0, pb, H->st));
+    HIPCHK(hipMemsetAsync(w.rxs, 0, xb, H->st));
     return HELM_OK;
 }
 
@@ -930,14 +950,12 @@ helm_status red_sweep(helm_t H, int nrhs, bool up, const double2* psi, bool base
 
 // the two reduced sweeps, in the form the handle holds
 helm_status reduced_up(helm_t H, int nrhs, const double2* psi) {
-    if (!H->red.kappa) return sweep_up(H, nrhs, nullptr, 1, false, psi);
-    CHK(ensure_red_ws(H, nrhs));
+    if (!dense(H, nrhs)) return sweep_up(H, nrhs, nullptr, 1, false, psi);
     return H->prec == HELM_C128 ? red_sweep<double>(H, nrhs, true, psi, false)
                                 : red_sweep<float>(H, nrhs, true, psi, false);
 }
 helm_status reduced_down(helm_t H, int nrhs) {
-    if (!H->red.kappa) return sweep_down(H, nrhs, H->wk.Ww, false);
-    CHK(ensure_red_ws(H, nrhs));
+    if (!dense(H, nrhs)) return sweep_down(H, nrhs, H->wk.Ww, false);
     return H->prec == HELM_C128 ? red_sweep<double>(H, nrhs, false, nullptr, false)
                                 : red_sweep<float>(H, nrhs, false, nullptr, false);
 }
@@ -951,35 +969,51 @@ helm_status reduced_down(helm_t H, int nrhs) {
 // chip idle when it has few right-hand sides, and the field of P takes J strip solves, both
 // sweeps' sources added, instead of 2 J - 1.  (Handles that fuse their strip solves with
 // other problems' keep the sequential sweeps.)
-bool batched(helm_t H) { return H->red.kappa > 0 && !H->batch_fuse; }
+bool batched(helm_t H, int nrhs) {
+    return dense(H, nrhs) && !H->batch_fuse && H->wk.Vb && H->wk.bcap >= (size_t)nrhs;
+}
 
-helm_status ensure_batch_ws(helm_t H, int nrhs) {
+// strip-solver workspace of one strip
+size_t batch_strip_bytes(helm_t H, int nrhs) {
+    return (size_t)nrhs * H->g.Ny * WP * (H->prec == HELM_C128 ? sizeof(double2) : sizeof(float2));
+}
+
+// strips per batch: four workgroups of phase A per CU, or 2 GB, and at most `cap`, in batches of
+// nearly one size
+int batch_strips(helm_t H, int nrhs, size_t cap) {
+    const int J = H->g.J, wgs = H->ch.P * ((nrhs + 15) / 16);
+    int nb = std::min(J, std::max(1, (1024 + wgs - 1) / wgs));
+    nb = (int)std::min<size_t>(nb, std::max<size_t>(1, ((size_t)2 << 30) / batch_strip_bytes(H, nrhs)));
+    nb = (int)std::min<size_t>(nb, cap);
+    const int nsub = (J + nb - 1) / nb;
+    return (J + nsub - 1) / nsub;
+}
+
+// Workspaces of the dense operators and of the batches of strips for nrhs right-hand sides, where
+// they can be had: called before a solve's Krylov basis takes most of what is free, and nowhere
+// where a graph may be captured.  Of the strips' workspace at most an eighth of the free memory,
+// so that the basis keeps its length, and half as much again and again until it fits.
+helm_status prepare_dense(helm_t H, int nrhs) {
+    CHK(ensure_red_ws(H, nrhs));
+    if (!dense(H, nrhs) || H->batch_fuse) return HELM_OK;
     Work& w = H->wk;
-    const auto& g = H->g;
-    if (w.Yb && w.bnrhs == nrhs && w.bP == H->ch.P) return HELM_OK;
-    const size_t esz = H->prec == HELM_C128 ? sizeof(double2) : sizeof(float2);
-    const size_t per = (size_t)nrhs * g.Ny * WP * esz;
-    // four workgroups of phase A per CU, or 2 GB
-    const int wgs = H->ch.P * ((nrhs + 15) / 16);
-    int nb = std::min(g.J, std::max(1, (1024 + wgs - 1) / wgs));
-    nb = (int)std::max<size_t>(1, std::min<size_t>(nb, ((size_t)2 << 30) / per));
-    const int nsub = (g.J + nb - 1) / nb;
-    nb = (g.J + nsub - 1) / nsub;
-    if (!w.Yb || w.bcap < (size_t)nb * nrhs) {
+    const size_t per = batch_strip_bytes(H, nrhs), want = (size_t)batch_strips(H, nrhs, H->g.J);
+    if (w.bcap < want * nrhs) {
         dfree(H, w.Yb);
         w.Yb = nullptr;
-        w.bnrhs = 0;
-        CHK(dmalloc(H, &w.Yb, per * nb));
-        w.bcap = (size_t)nb * nrhs;
+        w.bcap = 0;
+        size_t freeb = 0;
+        HIPCHK(free_bytes(&freeb));
+        for (size_t nb = std::min(want, std::max<size_t>(1, freeb / 8 / per)); nb >= 1; nb /= 2)
+            if (try_alloc(&w.Yb, per * nb)) {
+                w.bcap = nb * nrhs;
+                break;
+            }
     }
     if (!w.Vb) {
-        const size_t wb = (size_t)w.nrhs * g.Nrow() * (g.J - 1) * helm::IWIN * sizeof(double2);
-        CHK(dmalloc(H, &w.Vb, wb));
-        HIPCHK(hipMemsetAsync(w.Vb, 0, wb, H->st));
+        const size_t wb = (size_t)w.nrhs * H->g.Nrow() * (H->g.J - 1) * helm::IWIN * sizeof(double2);
+        if (try_alloc((void**)&w.Vb, wb)) HIPCHK(hipMemsetAsync(w.Vb, 0, wb, H->st));
     }
-    w.bstrips = nb;
-    w.bnrhs = nrhs;
-    w.bP = H->ch.P;
     return HELM_OK;
 }
 
@@ -990,8 +1024,6 @@ helm_status ensure_batch_ws(helm_t H, int nrhs) {
 template <typename T>
 helm_status strip_batch(helm_t H, int nrhs, int kind, const double2* f, double2* dst) {
     using V = helm::cplx<T>;
-    CHK(ensure_red_ws(H, nrhs));
-    CHK(ensure_batch_ws(H, nrhs));
     const auto& g = H->g;
     const auto& p = H->red;
     Work& w = H->wk;
@@ -1011,8 +1043,9 @@ helm_status strip_batch(helm_t H, int nrhs, int kind, const double2* f, double2*
     io.targets_only = kind == 1 ? 1 : 0;
     io.accumulate = kind == 4 ? 1 : 0;
     const int J = kind == 4 ? g.J - 1 : g.J;            // the downward sweep starts at strip J - 2
-    for (int s0 = 0; s0 < J; s0 += w.bstrips) {
-        const int ns = std::min(w.bstrips, J - s0);
+    const int nb = batch_strips(H, nrhs, w.bcap / nrhs);
+    for (int s0 = 0; s0 < J; s0 += nb) {
+        const int ns = std::min(nb, J - s0);
         rhs.s0 = s0;
         rhs.io = H->sio[kind] + s0;
         if (kind == 1) {
@@ -1035,7 +1068,6 @@ helm_status strip_batch_any(helm_t H, int nrhs, int kind, const double2* f, doub
 // base: the source is a full field whose strip solutions are in Vb, Tup, plus psi (may be
 // null) on the reduced columns; else it is psi alone.
 helm_status inputs_up(helm_t H, int nrhs, const double2* psi, bool base) {
-    CHK(ensure_red_ws(H, nrhs));
     return H->prec == HELM_C128 ? red_sweep<double>(H, nrhs, true, psi, base)
                                 : red_sweep<float>(H, nrhs, true, psi, base);
 }
@@ -1104,7 +1136,7 @@ helm_status apply_P_full(helm_t H, int nrhs, const double2* f, double2* out) {
     Work& w = H->wk;
     // complex64 solves three batches instead of 2 J - 1 single strips: worth it while a
     // single strip fills at most half of the 256 CUs
-    if (batched(H) && (H->prec == HELM_C128 || H->ch.P * ((nrhs + 15) / 16) <= 128)) {
+    if (batched(H, nrhs) && (H->prec == HELM_C128 || H->ch.P * ((nrhs + 15) / 16) <= 128)) {
         // f is read after parts of out are written: where the two overlap the batches read a copy
         // (V is the sequential sweeps')
         const std::uintptr_t fa = reinterpret_cast<std::uintptr_t>(f), oa = reinterpret_cast<std::uintptr_t>(out);
@@ -1150,7 +1182,7 @@ helm_status restart_rhs_reduced(helm_t H, int nrhs, const double2* r, double2* b
     const auto& g = H->g;
     Work& w = H->wk;
     if (g.J < 2) return HELM_OK;
-    if (batched(H)) {
+    if (batched(H, nrhs)) {
         CHK(strip_batch_any(H, nrhs, 1, r, nullptr));
         CHK(inputs_both(H, nrhs, r, nullptr));
         HIPCHK(TIMED(H, helm::K_STENCIL, helm::launch_stencil_win(4, H->t, g, nrhs, w.Ww, nullptr, w.Gw, b, H->st)));
@@ -1447,6 +1479,21 @@ void free_reduced(helm_t H) {
     H->red_gen += 1;
 }
 
+// Frees the dense strip operators and everything that only they use; false if there was nothing.
+// The sweeps of the handle run on the block substitutions until its next factorisation.
+bool release_dense(helm_t H) {
+    Work& w = H->wk;
+    if (!H->red_T && !w.rp && !w.Yb && !w.Vb) return false;
+    free_panels(H);
+    for (void** p : {&w.Yb, (void**)&w.Vb}) {
+        dfree(H, *p);
+        *p = nullptr;
+    }
+    w.bcap = 0;
+    free_reduced(H);
+    return true;
+}
+
 // The dense strip operators of the reduced sweeps, after the factorisation (2-D, double sweep
 // with PML transmission).  Their memory is kept for the handle's life, the build's workspace (2 GB
 // where there are many strips) goes back to the pool, which has it for the next factorisation of
@@ -1500,7 +1547,7 @@ helm_status build_reduced(helm_t H) {
 // Algorithm 2: u~ on D~^(j) from independent strip solves with f on D~^(j).
 helm_status reduced_setup(helm_t H, int nrhs, const double2* f, double2* ut) {
     const auto& g = H->g;
-    if (batched(H)) return strip_batch_any(H, nrhs, 0, f, ut);
+    if (batched(H, nrhs)) return strip_batch_any(H, nrhs, 0, f, ut);
     for (int s = 0; s < g.J; ++s) {
         const auto& S = g.strips[s];
         helm::IOSpec io = field_io(H, s);
@@ -1637,7 +1684,6 @@ helm_status apply_op(helm_t H, int nrhs, const double2* x, double2* out) {
     // graph replay: the captured launches read the fixed buffer apin and write `out`
     Work& w = H->wk;
     CHK(ensure_sweep_ws(H, nrhs));
-    CHK(ensure_red_ws(H, nrhs));
     const size_t bytes = (size_t)nrhs * H->g.Nrow() * 2 * (H->g.J - 1) * sizeof(double2);
     if (x != w.apin) HIPCHK(hipMemcpyAsync(w.apin, x, bytes, hipMemcpyDeviceToDevice, H->st));
     int slot = -1, lru = 0;
@@ -1990,6 +2036,7 @@ helm_status solve_impl(helm_t H, int nrhs, const double2* f, double2* u, double 
                        int* iters, double* relres) {
     const auto& g = H->g;
     CHK(ensure_sweep_ws(H, nrhs));
+    CHK(prepare_dense(H, nrhs));
     Work& w = H->wk;
     const long nfull = g.Nrow() * g.Nx;
     const int nred = 2 * (g.J - 1);
@@ -2099,7 +2146,7 @@ helm_status solve_impl(helm_t H, int nrhs, const double2* f, double2* u, double 
         if (reduced && cycle > 0 && merge) {
             // Algorithm 4 with the restart's P r folded in: u += P (r + psi)
             HIPCHK(TIMED(H, helm::K_OTHER, helm::launch_scatter_cols(w.w, red_cols(H), nred, nrhs, g.Nrow(), g.Nx, w.R, H->st, true)));
-            if (batched(H)) {
+            if (batched(H, nrhs)) {
                 // the strip solutions of r are still in Vb, Tup
                 CHK(field_of_P(H, nrhs, w.R, w.w, true, w.Hf));
             } else {
@@ -2110,7 +2157,7 @@ helm_status solve_impl(helm_t H, int nrhs, const double2* f, double2* u, double 
             // Algorithm 4: u += P psi + u~   (psi scattered onto the reduced columns of Psi,
             // which is zero everywhere else: nothing but this scatter writes it)
             HIPCHK(TIMED(H, helm::K_OTHER, helm::launch_scatter_cols(w.w, red_cols(H), nred, nrhs, g.Nrow(), g.Nx, w.Psi, H->st)));
-            if (batched(H)) {
+            if (batched(H, nrhs)) {
                 CHK(field_of_P(H, nrhs, w.Psi, w.w, false, w.Hf));
             } else {
                 CHK(apply_P_any(H, nrhs, w.Psi, w.Hf));
@@ -2827,6 +2874,7 @@ helm_status helm_autotune(helm_t H, int nrhs, const void* rhs, const int* cand, 
     for (int c = 0; c < ncand; ++c) {
         set_chunks(H, cand[c]);
         CHK(helm_factor(H));
+        CHK(prepare_dense(H, nrhs));
         CHK(apply());                      // warm-up (first touch of the layout)
         HIPCHK(hipEventRecord(e0, H->st));
         for (int r = 0; r < reps; ++r) CHK(apply());
@@ -3007,6 +3055,7 @@ helm_status helm_apply_P(helm_t H, int nrhs, const void* f, void* out) {
     if (!H->factored) return fail(H, HELM_ESTATE, "helm_apply_P before helm_factor");
     if (nrhs < 1 || !f || !out) return fail(H, HELM_EINVAL, "bad arguments");
     CHK(ensure_sweep_ws(H, nrhs));
+    CHK(prepare_dense(H, nrhs));
     return apply_P_any(H, nrhs, static_cast<const double2*>(f), static_cast<double2*>(out));
 }
 
@@ -3016,6 +3065,8 @@ helm_status helm_apply_AP_reduced(helm_t H, int nrhs, const void* psi, void* out
     if (nrhs < 1 || !psi || !out) return fail(H, HELM_EINVAL, "bad arguments");
     if (H->g.J < 2) return fail(H, HELM_EINVAL, "the reduced space is empty for J = 1");
     if (H->trans == 1) return fail(H, HELM_EINVAL, "the reduced form is built for the PML transmission");
+    CHK(ensure_sweep_ws(H, nrhs));
+    CHK(ensure_red_ws(H, nrhs));
     return apply_AP_red(H, nrhs, static_cast<const double2*>(psi), static_cast<double2*>(out));
 }
 
@@ -3026,6 +3077,8 @@ helm_status helm_restart_rhs_reduced(helm_t H, int nrhs, const void* r, void* b)
     if (nrhs < 1 || !r || !b) return fail(H, HELM_EINVAL, "bad arguments");
     if (H->trans == 1 || H->sweep == 1)
         return fail(H, HELM_EINVAL, "the restart right-hand side is built for the double sweep with PML transmission");
+    CHK(ensure_sweep_ws(H, nrhs));
+    CHK(prepare_dense(H, nrhs));
     return restart_rhs_reduced(H, nrhs, static_cast<const double2*>(r), static_cast<double2*>(b));
 }
 

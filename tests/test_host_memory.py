@@ -195,7 +195,7 @@ R.rec_budget(0, 64 << 20)
 H = setup(n=100, J=4)              # takes what the pool still holds
 print(json.dumps({"out": out, "live": live, "ok": status(L.helm_factor, H) in (0, 2)}))
 """)
-    assert all(st == 2 and again == 0 for st, again in got["out"]) and got["ok"], got
+    assert all(st in (0, 2) and again == 0 for st, again in got["out"]) and got["ok"], got
 
 
 def test_kept_memory_is_given_back_on_request(recorder):
@@ -290,3 +290,58 @@ print(json.dumps({"a": a, "b": b, "again": again, "freed": freed,
     for n in got["b"]:
         left.remove(n)
     assert len(left) == 1 and got["freed"] == left and got["again"] == [] and got["st"] == 0, got
+
+
+@pytest.mark.parametrize("prec", ["C128", "MIXED"])
+def test_solve_in_little_memory(recorder, prec):
+    """Whatever memory is enough for a handle without the dense operators and the batches of strips is
+    enough for one with them; with more, the batches take at most an eighth of what is free."""
+    got = run(recorder, f"""
+from paper_1208_3956_amd import empty_cache
+nrhs = 64
+def solve(room, **kw):
+    empty_cache()
+    R.rec_budget(0, int(room))
+    H = setup(n=100, J=6, prec={prec}, mode=FULL, **kw)
+    st = status(L.helm_factor, H)
+    f = field(H, nrhs)
+    if st == 0:
+        st = status(L.helm_solve, H, nrhs, f.ctypes.data, f.copy().ctypes.data, 1e-6)
+    L.helm_destroy(H)
+    return st
+rooms = [int(m * 1e6) for m in range(60, 1500, 10)]
+plain = [r for r in rooms if solve(r, batch_fuse=1) == 0]
+both = [r for r in rooms if solve(r) == 0]
+print(json.dumps({{"least": plain[0], "lost": [r for r in plain if r not in both], "n": len(plain)}}))
+""")
+    assert got["n"] > 50 and got["least"] > 60e6 and got["lost"] == [], got
+
+
+@pytest.mark.parametrize("prec", ["C128", "MIXED"])
+@pytest.mark.parametrize("call", ["solve", "P", "rhs", "AP"])
+def test_any_one_allocation_of_a_call_may_fail(recorder, prec, call):
+    """Whichever allocation of a first call fails, the dense operators, panels or batches make room
+    and the call runs."""
+    got = run(recorder, f"""
+from paper_1208_3956_amd import empty_cache
+def go(H):
+    f, psi = field(H, 3), np.zeros((3, 56 * 4), np.complex128)
+    return {{"solve": lambda: status(L.helm_solve, H, 3, f.ctypes.data, f.copy().ctypes.data, 1e-6),
+            "P": lambda: status(L.helm_apply_P, H, 3, f.ctypes.data, f.copy().ctypes.data),
+            "rhs": lambda: status(L.helm_restart_rhs_reduced, H, 3, f.ctypes.data, f.copy().ctypes.data),
+            "AP": lambda: status(L.helm_apply_AP_reduced, H, 3, psi.ctypes.data, psi.copy().ctypes.data)}}["{call}"]()
+bad, n = [], 0
+for k in range(60):
+    H = setup(prec={prec})
+    L.helm_factor(H)
+    empty_cache()
+    R.rec_fail_malloc(k)
+    st = go(H)
+    R.rec_fail_malloc(-1)
+    again = go(H)
+    L.helm_destroy(H)
+    if st or again:
+        bad.append((k, st, again))
+print(json.dumps({{"bad": bad}}))
+""")
+    assert got["bad"] == [], got
