@@ -153,7 +153,9 @@ helm_status helm_setup(const double* c, double omega, double h, const helm_opts*
  * of their Schur complement.  In 3-D a slab is block tridiagonal along y with dense
  * (W N_z) x (W N_z) blocks (the (x, z) planes); each is inverted by blocked Gauss-Jordan
  * elimination, plane after plane (the blocks of all slabs of one plane together).  2-D:
- * computed in FP64, stored in FP64 (HELM_C128) or rounded to complex64.  3-D HELM_C128:
+ * computed in FP64, stored in FP64 (HELM_C128) or rounded to complex64; what the double sweep
+ * needs beyond the strips' own factors is formed from them by the first call that sweeps
+ * (helm_solve, helm_grad, helm_apply_P, ...; not helm_strip_solve).  3-D HELM_C128:
  * FP64 with partial pivoting over the whole column.  3-D HELM_MIXED_C64: complex64 with
  * FP32 accumulation over column blocks of 128, each diagonal block inverted in FP64 from
  * its 64 x 64 sub-blocks with pivoting inside those only; if a diagonal block is singular

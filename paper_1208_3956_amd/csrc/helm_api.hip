@@ -153,6 +153,7 @@ struct helm_problem {
     helm::RedPlan red;
     void *red_T = nullptr, *red_R = nullptr, *red_S = nullptr;
     long red_gen = 0;           // generation of the plan and its buffers
+    bool red_tried = false;     // built, or found impossible, since the last factorisation
     int red_m = 0;              // rows per fine chunk they were laid out for
     // per-strip tables of the batches of strips, J entries each (kinds of strip_batch)
     helm::StripIO* sio[5] = {};
@@ -866,10 +867,23 @@ void free_panels(helm_t H) {
     H->ws_epoch += 1;
 }
 
+// whether the caller records the handle's stream into a graph: nothing is allocated, built or
+// waited for then, and the call runs in the form that is there
+bool capturing(helm_t H) {
+    hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(H->st, &c) == hipSuccess) return c != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return true;
+}
+
+helm_status build_reduced(helm_t H);
+
 helm_status ensure_red_ws(helm_t H, int nrhs) {
     Work& w = H->wk;
     const auto& p = H->red;
     const int G = (nrhs + 15) / 16;
+    if (dense(H, nrhs) || (H->red_tried && !p.kappa) || capturing(H)) return HELM_OK;
+    if (!H->red_tried) CHK(build_reduced(H));
     if (!p.kappa || dense(H, nrhs)) return HELM_OK;
     free_panels(H);
     const size_t esz = H->prec == HELM_C128 ? sizeof(double2) : sizeof(float2);
@@ -989,13 +1003,18 @@ int batch_strips(helm_t H, int nrhs, size_t cap) {
     return (J + nsub - 1) / nsub;
 }
 
+// the batches have the workspace they want
+bool batched_in_full(helm_t H, int nrhs) {
+    return batched(H, nrhs) && H->wk.bcap >= (size_t)batch_strips(H, nrhs, H->g.J) * nrhs;
+}
+
 // Workspaces of the dense operators and of the batches of strips for nrhs right-hand sides, where
 // they can be had: called before a solve's Krylov basis takes most of what is free, and nowhere
 // where a graph may be captured.  Of the strips' workspace at most an eighth of the free memory,
 // so that the basis keeps its length, and half as much again and again until it fits.
 helm_status prepare_dense(helm_t H, int nrhs) {
     CHK(ensure_red_ws(H, nrhs));
-    if (!dense(H, nrhs) || H->batch_fuse) return HELM_OK;
+    if (!dense(H, nrhs) || H->batch_fuse || batched_in_full(H, nrhs) || capturing(H)) return HELM_OK;
     Work& w = H->wk;
     const size_t per = batch_strip_bytes(H, nrhs), want = (size_t)batch_strips(H, nrhs, H->g.J);
     if (w.bcap < want * nrhs) {
@@ -1491,16 +1510,20 @@ bool release_dense(helm_t H) {
     }
     w.bcap = 0;
     free_reduced(H);
+    H->red_tried = true;
     return true;
 }
 
-// The dense strip operators of the reduced sweeps, after the factorisation (2-D, double sweep
-// with PML transmission).  Their memory is kept for the handle's life, the build's workspace (2 GB
+// The dense strip operators of the reduced sweeps (2-D, double sweep with PML transmission), by the
+// first call after a factorisation that can use them: a program that only solves strips does not
+// pay for them (factorisation of 16 strips of 532 rows, complex128: 12.5 ms with set-up, 15.6 with
+// the operators).  Their memory is kept for the handle's life, the build's workspace (2 GB
 // where there are many strips) goes back to the pool, which has it for the next factorisation of
 // any handle; where they would take more than half of what is free, or cannot be had, the sweeps keep
 // the block substitutions.
 helm_status build_reduced(helm_t H) {
     const auto& g = H->g;
+    H->red_tried = true;
     // a full-form handle uses them for the sweeps of P (see batched)
     if (g.dim != 2 || (H->mode != HELM_REDUCED && H->batch_fuse) || H->sweep != 0 || H->trans != 0 || g.J < 2)
         return HELM_OK;
@@ -1541,6 +1564,12 @@ helm_status build_reduced(helm_t H) {
                      helm::launch_red_build<float>(p, bs, H->tf, H->gf, H->ch, H->nfac, H->F64, ws, H->d_err + 1,
                                                    static_cast<float2*>(H->red_T), static_cast<float2*>(H->red_R),
                                                    static_cast<float2*>(H->red_S), H->st)));
+    int herr = 0;
+    HIPCHK(hipMemcpyAsync(&herr, H->d_err + 1, sizeof(int), hipMemcpyDeviceToHost, H->st));
+    HIPCHK(hipStreamSynchronize(H->st));
+    // the strip operators stay with the block substitutions where a joined block is too
+    // ill-conditioned to be applied as an explicit inverse
+    if (herr) H->red.kappa = 0;
     return HELM_OK;
 }
 
@@ -2733,6 +2762,8 @@ helm_status helm_factor(helm_t H) {
     CHK(drop_graph(H));
     HIPCHK(hipStreamSynchronize(H->st));    // no queued work may still read the old factors
     H->factored = false;
+    H->red = helm::RedPlan();
+    H->red_tried = false;
     if (g.dim == 3) return factor3(H);
     // The factor buffers keep their size for the handle's life: they are allocated (and
     // cleared: slots no factorisation writes must read as zero) once, and every later
@@ -2791,15 +2822,11 @@ helm_status helm_factor(helm_t H) {
     else
         HIPCHK(TIMED(H, helm::K_OTHER, helm::launch_extract_targets<double2>(F64, static_cast<double2*>(H->Fc),
                                                                             H->tf.tcol, gf, H->ch, H->st)));
-    CHK(build_reduced(H));
-    int herr[2] = {0, 0};
-    HIPCHK(hipMemcpyAsync(herr, H->d_err, 2 * sizeof(int), hipMemcpyDeviceToHost, H->st));
+    int herr = 0;
+    HIPCHK(hipMemcpyAsync(&herr, H->d_err, sizeof(int), hipMemcpyDeviceToHost, H->st));
     HIPCHK(hipStreamSynchronize(H->st));
-    // the strip operators stay with the block substitutions where a joined block is too
-    // ill-conditioned to be applied as an explicit inverse
-    if (herr[1]) H->red.kappa = 0;
-    if (herr[0] & 1) return fail(H, HELM_ESINGULAR, "zero or non-finite pivot in a strip factorisation");
-    if (herr[0] & 2)
+    if (herr & 1) return fail(H, HELM_ESINGULAR, "zero or non-finite pivot in a strip factorisation");
+    if (herr & 2)
         return fail(H, HELM_ESINGULAR, "a strip block is numerically singular (1-norm condition estimate "
                                        "above 1e13): the strip operator is at or near a resonance");
     H->factored = true;

@@ -29,7 +29,7 @@ std::string log_text;
 bool logging = false;
 size_t handles = 0x1000;
 thread_local int cur = 0;
-bool capturing = false;
+void* captured_stream = nullptr;
 
 void note(const char* what, const void* p, size_t n = 0) {
     if (!logging) return;
@@ -61,6 +61,7 @@ size_t rec_live(int dev) {
     return n;
 }
 void rec_kill_stream(void* s) { LOCK; dead_streams.insert(s); }
+void rec_capture(void* s) { LOCK; captured_stream = s; }
 void rec_fail_launch(long n) { LOCK; fail_launch = n; }
 void rec_fail_malloc(long n) { LOCK; fail_malloc = n; }
 void rec_log(int on) { LOCK; logging = on != 0; if (on) log_text.clear(); }
@@ -127,8 +128,9 @@ int hipEventDestroy(void*) { return 0; }
 int hipEventRecord(void* e, void* s) { LOCK; note("record", s, (size_t)e); return 0; }
 int hipEventSynchronize(void*) { return 0; }
 int hipEventElapsedTime(float* t, void*, void*) { *t = 1.0f; return 0; }
-int hipStreamBeginCapture(void*, int) { capturing = true; return 0; }
-int hipStreamEndCapture(void*, void** g) { capturing = false; *g = fresh(); return 0; }
+int hipStreamBeginCapture(void*, int) { return 0; }
+int hipStreamEndCapture(void*, void** g) { *g = fresh(); return 0; }
+int hipStreamIsCapturing(void* s, int* c) { LOCK; *c = s && s == captured_stream; return 0; }
 int hipGraphInstantiate(void** x, void*, void**, char*, size_t) { *x = fresh(); return 0; }
 int hipGraphLaunch(void*, void* s) { LOCK; note("launch", s); return 0; }
 int hipGraphDestroy(void*) { return 0; }

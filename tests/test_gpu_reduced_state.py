@@ -59,3 +59,30 @@ def test_narrower_panel_after_infinities(prec, chunk):
             assert torch.equal(a(x[:nrhs]), b(x[:nrhs])), (a.__name__, nrhs)
     A.close()
     B.close()
+
+
+@pytest.mark.parametrize("prec", ["c128", "mixed"])
+@pytest.mark.parametrize("warm", [True, False])
+def test_P_recorded_into_a_graph(prec, warm):
+    """P under capture, on a handle that has swept before and on one that was factored again and has
+    not (nothing is built while the stream is recorded): replays with other work between them."""
+    st = torch.cuda.Stream(DEV)
+    H = _handle(prec, "full", stream=st)
+    f = _field(H, 3)
+    want = H.apply_P(f)
+    if not warm:
+        H.factor()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=st):
+        out = H.apply_P(f)
+    tol = 1e-12 if prec == "c128" else 5e-5           # the block substitutions' rounding where not warm
+    for k in range(3):
+        out.zero_()
+        other = H.apply_P(2.0 * f)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert (out - want).abs().max() <= tol * want.abs().max(), k
+        assert (other - 2.0 * want).abs().max() <= 2 * tol * want.abs().max(), k
+    H.close()

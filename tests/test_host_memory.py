@@ -17,7 +17,7 @@ R = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
 sz, vp = ctypes.c_size_t, ctypes.c_void_p
 R.rec_budget.argtypes = [ctypes.c_int, sz]
 R.rec_room.restype = R.rec_live.restype = R.rec_log_size.restype = sz
-R.rec_kill_stream.argtypes = [vp]
+R.rec_kill_stream.argtypes = R.rec_capture.argtypes = [vp]
 R.rec_fail_launch.argtypes = R.rec_fail_malloc.argtypes = R.rec_fail_new.argtypes = [ctypes.c_long]
 R.rec_log_text.argtypes = [ctypes.c_char_p, sz]
 from paper_1208_3956_amd import _lib as L
@@ -255,16 +255,22 @@ for k in range(blocks, blocks + 6):
     if st != [0, 0, 0, 0]:
         bad.append((k, st))
 empty_cache()
+f = np.zeros((216 * 216), np.complex128)
+P = lambda H: status(L.helm_apply_P, H, 1, f.ctypes.data, f.copy().ctypes.data)
 H = setup(prec={prec}, mode={mode}, n=200, J=8)
 L.helm_factor(H)
 own = R.rec_live(0)
+assert P(H) == 0
+empty_cache()
+added = R.rec_live(0) - own
 L.helm_destroy(H)
 empty_cache()
-R.rec_budget(0, own * 2 // 3)                         # they would take more than half of what is free
+R.rec_budget(0, own + added // 2)                     # no room for them
 H = setup(prec={prec}, mode={mode}, n=200, J=8)
-print(json.dumps({{"bad": bad, "blocks": blocks, "every": every, "tight": status(L.helm_factor, H)}}))
+tight = [status(L.helm_factor, H), P(H)]
+print(json.dumps({{"bad": bad, "blocks": blocks, "every": every, "tight": tight}}))
 """)
-    assert got["bad"] == [] and got["tight"] == 0 and got["every"] > got["blocks"] > 0, got
+    assert got["bad"] == [] and got["tight"] == [0, 0] and got["every"] > got["blocks"] > 0, got
 
 
 def test_build_workspace_is_shared(recorder):
@@ -277,8 +283,11 @@ def mallocs(f):
     f()
     return sorted(n for w, p, n, d in log() if w == "malloc")
 A, B = setup(n=200, J=8), setup(n=200, J=8)
-a, b = mallocs(lambda: L.helm_factor(A)), mallocs(lambda: L.helm_factor(B))
-again = mallocs(lambda: L.helm_factor(A))
+def use(H):
+    f = field(H, 1)
+    L.helm_factor(H)
+    L.helm_apply_P(H, 1, f.ctypes.data, f.copy().ctypes.data)
+a, b, again = mallocs(lambda: use(A)), mallocs(lambda: use(B)), mallocs(lambda: use(A))
 R.rec_log(1)
 empty_cache()
 freed = [n for w, p, n, d in log() if w == "free"]
@@ -320,20 +329,21 @@ print(json.dumps({{"least": plain[0], "lost": [r for r in plain if r not in both
 @pytest.mark.parametrize("prec", ["C128", "MIXED"])
 @pytest.mark.parametrize("call", ["solve", "P", "rhs", "AP"])
 def test_any_one_allocation_of_a_call_may_fail(recorder, prec, call):
-    """Whichever allocation of a first call fails, the dense operators, panels or batches make room
-    and the call runs."""
+    """Whichever allocation of a call with more right-hand sides than before fails, the dense
+    operators, panels or batches make room and the call runs."""
     got = run(recorder, f"""
 from paper_1208_3956_amd import empty_cache
-def go(H):
-    f, psi = field(H, 3), np.zeros((3, 56 * 4), np.complex128)
-    return {{"solve": lambda: status(L.helm_solve, H, 3, f.ctypes.data, f.copy().ctypes.data, 1e-6),
-            "P": lambda: status(L.helm_apply_P, H, 3, f.ctypes.data, f.copy().ctypes.data),
-            "rhs": lambda: status(L.helm_restart_rhs_reduced, H, 3, f.ctypes.data, f.copy().ctypes.data),
-            "AP": lambda: status(L.helm_apply_AP_reduced, H, 3, psi.ctypes.data, psi.copy().ctypes.data)}}["{call}"]()
+def go(H, n=3):
+    f, psi = field(H, n), np.zeros((n, 56 * 4), np.complex128)
+    return {{"solve": lambda: status(L.helm_solve, H, n, f.ctypes.data, f.copy().ctypes.data, 1e-6),
+            "P": lambda: status(L.helm_apply_P, H, n, f.ctypes.data, f.copy().ctypes.data),
+            "rhs": lambda: status(L.helm_restart_rhs_reduced, H, n, f.ctypes.data, f.copy().ctypes.data),
+            "AP": lambda: status(L.helm_apply_AP_reduced, H, n, psi.ctypes.data, psi.copy().ctypes.data)}}["{call}"]()
 bad, n = [], 0
 for k in range(60):
     H = setup(prec={prec})
     L.helm_factor(H)
+    assert go(H, 1) == 0
     empty_cache()
     R.rec_fail_malloc(k)
     st = go(H)
@@ -345,3 +355,37 @@ for k in range(60):
 print(json.dumps({{"bad": bad}}))
 """)
     assert got["bad"] == [], got
+
+
+@pytest.mark.parametrize("mode", ["REDUCED", "FULL"])
+def test_factorisation_alone_builds_no_dense_operators(recorder, mode):
+    """They are built by the first call that uses them, once per factorisation: not for strip solves,
+    and not while the caller records the stream into a graph."""
+    got = run(recorder, f"""
+H = setup(mode={mode}, stream=0x10)
+x = np.zeros(1 << 18)
+f = field(H, 2)
+def launches(f):
+    R.rec_log(1)
+    f()
+    return [n for w, p, n, d in log() if w == "launch"], [w for w, *_ in log() if w in ("malloc", "sync")]
+P = lambda: L.helm_apply_P(H, 2, f.ctypes.data, f.copy().ctypes.data)
+A = setup(mode=FULL, stream=0x10, batch_fuse=1)                 # never has them
+plain, _ = launches(lambda: L.helm_factor(A))
+first, _ = launches(lambda: L.helm_factor(H))
+strip, _ = launches(lambda: [L.helm_strip_solve(H, s, 2, x.ctypes.data, x.ctypes.data) for s in range(3)])
+p1, _ = launches(P)
+p2, w2 = launches(P)
+again, _ = launches(lambda: L.helm_factor(H))
+R.rec_capture(vp(0x10))
+p3, w3 = launches(P)
+R.rec_capture(None)
+p4, _ = launches(P)
+p5, w5 = launches(P)
+print(json.dumps({{"plain": len(plain), "first": len(first), "again": len(again), "same": first == plain,
+                  "built": [len(set(p) - set(p2)) > 0 for p in (p1, p3, p4)], "calls": [p1[-len(p2):] == p2, p4[-len(p2):] == p2, p5 == p2],
+                  "quiet": [w2, w3, w5], "captured": len(p3)}}))
+""")
+    assert got["same"] and got["plain"] == got["first"] == got["again"], got
+    assert got["built"] == [True, True, True] and got["calls"] == [True, True, True], got
+    assert got["quiet"] == [[], [], []] and got["captured"] > 0, got
