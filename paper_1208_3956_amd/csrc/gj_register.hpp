@@ -36,9 +36,6 @@ struct GJShared {
 // A block whose 1-norm condition estimate ||S||_1 ||S^-1||_1 exceeds this is numerically
 // singular in FP64 (its inverse has no correct digit): the factorisation reports it
 constexpr double GJ_COND_MAX = 1e13;
-// The dense operators of the reduced form (kernels_reduced.hip) are built only from blocks
-// below this: above it the block substitutions, which never form them, stay in use
-constexpr double RED_COND_MAX = 1e9;
 
 // sum over the 64 lanes of a wavefront (butterfly, every lane gets the sum)
 __device__ inline double wave_sum(double v) {

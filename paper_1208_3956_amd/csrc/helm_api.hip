@@ -1567,8 +1567,8 @@ helm_status build_reduced(helm_t H) {
     int herr = 0;
     HIPCHK(hipMemcpyAsync(&herr, H->d_err + 1, sizeof(int), hipMemcpyDeviceToHost, H->st));
     HIPCHK(hipStreamSynchronize(H->st));
-    // the strip operators stay with the block substitutions where a joined block is too
-    // ill-conditioned to be applied as an explicit inverse
+    // the strips stay with the block substitutions where a separator eliminated in a join is too
+    // ill-conditioned (kernels_reduced.hip, RedCond)
     if (herr) H->red.kappa = 0;
     return HELM_OK;
 }

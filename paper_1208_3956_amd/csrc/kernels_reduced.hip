@@ -288,6 +288,7 @@ struct RedBuild {
     const double2* sax; const double2* saxh; const int* scol; const int* sW; const int* tcol;   // from that slot on
     const double* k2;
     int* err;
+    double cond_max;         // of the separators eliminated in a join
     int Nx, Ny, m, P;        // fine chunks
     double ih2;
     __device__ const double2* slot(int u, int l, int sl) const { return F + (((size_t)u * Ny + l) * NSLOT + sl) * BLK; }
@@ -299,6 +300,18 @@ struct RedBuild {
         return q < 0 ? -1 : i < 3 ? q - 1 + i : q + 1 + (i - 3);
     }
 };
+
+// Largest 1-norm condition estimate of a separator's Schur complement in a join; above it the strips
+// stay with the block substitutions, which do not eliminate separators node by node.  Measured
+// against extended precision on strips without PML near a resonance (162 rows): from chunks of 8
+// rows, three levels of joins, the error of the reduced operator is 1.6 to 10 times the
+// substitutions' at 3e3, 5 at 4e5, 25 at 4e7; from chunks of 48 (no join) it is theirs at any
+// condition, so that leaves and the factorisation's own separators need no limit of their own.
+// With PML the estimate stays below 4e4 (178 problems of 48 to 2000 points a side) and P below
+// 1.03 times their error.  In complex64 the joins are in FP64 all the same, and the dense operator
+// is the more accurate one at any condition at which either has a digit.
+template <typename T> struct RedCond { static constexpr double max = 1e5; };
+template <> struct RedCond<float> { static constexpr double max = 1e9; };
 
 // 64 x 64 by 64 x 16 products of a chain: the block's A operands of this lane in registers
 struct Chain {
@@ -454,7 +467,7 @@ __global__ void __launch_bounds__(NT) k_red_schur(RedBuild b, const double2* __r
         }
         M[r] = v;
     }
-    gj_invert_store(M, W, sh, gout + ((size_t)u * gridDim.x + j2) * BLK, nullptr, b.err, RED_COND_MAX);
+    gj_invert_store(M, W, sh, gout + ((size_t)u * gridDim.x + j2) * BLK, nullptr, b.err, b.cond_max);
 }
 
 // Products of 64 x 64 tiles from LDS (leading dimension LDT, element (r, k) of X at k LDT + r,
@@ -904,6 +917,7 @@ hipError_t launch_red_build(const RedPlan& p, const RedBuildSize& sz, const DevT
         b.sax = t.sax + (size_t)u0 * WP; b.saxh = t.saxh + (size_t)u0 * (WP + 1);
         b.scol = t.scol + (size_t)u0 * WP; b.sW = t.sW + u0; b.tcol = t.tcol + (size_t)u0 * 8;
         b.err = err;
+        b.cond_max = RedCond<T>::max;
         b.Nx = g.Nx; b.Ny = g.Ny; b.m = ch.m; b.P = ch.P; b.ih2 = 1.0 / (g.h * g.h);
         double2* K = ws;
         double2* K2 = K + sz.K * sz.batch;
