@@ -2628,8 +2628,8 @@ helm_status factor3(helm_t H) {
         return HELM_OK;
     };
     const size_t nb = helm::factor3_panel_width();
-    double2 *S[2], *G64[2], *Tm[2], *Cm[2];
-    int *perm[2], *pi[2];
+    double2 *S[2] = {}, *G64[2] = {}, *Tm[2] = {}, *Cm[2] = {};
+    int *perm[2] = {}, *pi[2] = {};
     void* work32 = nullptr;
     helm_status st;
     helm::Fac3Args a;
@@ -2651,8 +2651,10 @@ helm_status factor3(helm_t H) {
         return TIMED(H, helm::K_OTHER, run());
     };
     // the eliminations from both ends of the slabs meet at plane p.  plane(l, end, stream): the
-    // lower end on the handle's stream, the upper on a second one (default priority), then the
-    // middle plane on both (end says whose workspace it uses)
+    // lower end on the handle's stream, the upper on a second one (default priority; the handle's
+    // too where the ends share their work arrays), then the middle plane on both (end says whose
+    // workspace it uses)
+    bool shared = false;
     const int p = helm::slab_mid(g.Ny);
     if (!H->st_fac) HIPCHK(hipStreamCreateWithFlags(&H->st_fac, hipStreamNonBlocking));
     hipEvent_t evs[2] = {};
@@ -2662,8 +2664,9 @@ helm_status factor3(helm_t H) {
     } evguard{evs};
     for (hipEvent_t& v : evs) HIPCHK(hipEventCreateWithFlags(&v, hipEventDisableTiming));
     auto two_ends = [&](auto plane) -> hipError_t {
-        hipStream_t q[2] = {H->st, H->st_fac};
+        hipStream_t q[2] = {H->st, shared ? H->st : H->st_fac};
         auto after = [&](int from, int to) {             // stream `to` waits for `from`
+            if (shared) return hipSuccess;
             const hipError_t r = hipEventRecord(evs[from], q[from]);
             return r == hipSuccess ? hipStreamWaitEvent(q[to], evs[from], 0) : r;
         };
@@ -2719,24 +2722,37 @@ helm_status factor3(helm_t H) {
         }
     }
     H->factor_path = 0;
-    // one set of work arrays per end
-    for (int end = 0; end < 2; ++end)
-        if ((st = alloc((void**)&S[end], nf * BB * sizeof(double2))) != HELM_OK ||
-            (st = alloc((void**)&G64[end], nf * BB * sizeof(double2))) != HELM_OK ||
-            (st = alloc((void**)&Tm[end], (size_t)nf * g.Bp * nb * sizeof(double2))) != HELM_OK ||
-            (st = alloc((void**)&Cm[end], (size_t)nf * g.Bp * nb * sizeof(double2))) != HELM_OK ||
-            (st = alloc((void**)&perm[end], (size_t)nf * g.Bp * sizeof(int))) != HELM_OK ||
-            (st = alloc((void**)&pi[end], (size_t)nf * g.Bp * sizeof(int))) != HELM_OK)
-            return st;
+    for (void* q : bufs.p) dfree(H, q);                  // the complex64 attempt's
+    bufs.p.clear();
+    // work arrays per end; where the second set cannot be had the ends take turns on the first.  The
+    // planes next to the one in work are read back from the stored inverses in complex128, from a
+    // copy in FP64 per end where those are complex64.
+    const size_t mat = nf * BB * sizeof(double2), pan = (size_t)nf * g.Bp * nb * sizeof(double2),
+                 idx = (size_t)nf * g.Bp * sizeof(int);
+    struct Part { void** p; size_t bytes; };
+    auto set = [&](int e) {
+        return std::vector<Part>{{(void**)&S[e], mat}, {(void**)&Tm[e], pan}, {(void**)&Cm[e], pan},
+                                 {(void**)&perm[e], idx}, {(void**)&pi[e], idx}};
+    };
+    for (const Part& q : set(0)) CHK(alloc(q.p, q.bytes));
+    for (int e = 0; single && e < 2; ++e) CHK(alloc((void**)&G64[e], mat));
+    for (const Part& q : set(1)) {
+        shared = shared || !try_alloc(q.p, q.bytes);
+        if (*q.p) bufs.p.push_back(*q.p);
+    }
+    if (shared) { S[1] = S[0]; Tm[1] = Tm[0]; Cm[1] = Cm[0]; perm[1] = perm[0]; pi[1] = pi[0]; }
     HIPCHK(hipMemsetAsync(H->d_err, 0, sizeof(int), H->st));
     // timed as one unit, like the complex64 route
     hipError_t e = TIMED(H, helm::K_FACTOR_CHUNKS, two_ends([&](int l, int end, hipStream_t q) {
         if (l == p && end == 1) return hipSuccess;
-        const double2* low = end == 0 && l > 0 ? G64[0] : nullptr;
-        const double2* up = l == p || (end == 1 && l < g.Ny - 1) ? G64[1] : nullptr;
+        const size_t stride = (size_t)g.Ny * BB;
+        const double2* Fd = static_cast<const double2*>(F) + (single ? 0 : l * BB);    // plane l, complex128
+        const bool below = end == 0 && l > 0, above = l == p || (end == 1 && l < g.Ny - 1);
+        const double2* low = !below ? nullptr : single ? G64[0] : Fd - BB;
+        const double2* up = !above ? nullptr : single ? G64[1] : Fd + BB;
         void* out = static_cast<char*>(F) + (size_t)l * BB * esz;
-        return helm::launch_factor3_plane(a, l, low, up, S[end], Tm[end], Cm[end], perm[end], pi[end], H->d_err,
-                                          l == p ? nullptr : G64[end], out, single, (size_t)g.Ny * BB, q);
+        return helm::launch_factor3_plane(a, l, low, up, single ? BB : stride, S[end], Tm[end], Cm[end], perm[end],
+                                          pi[end], H->d_err, l == p ? nullptr : G64[end], out, single, stride, q);
     }));
     HIPCHK(e);
     herr = 0;

@@ -325,10 +325,11 @@ hipError_t launch_sum_diff(const double2* x, const double2* y, const double2* z,
 int dots_blocks(long n);
 
 // one plane l of the 3-D slab factorisation for every slab: S = T_l - c_l b_{l-1} Glow
-// - b_l c_{l+1} Gup (null: no such term), inverted in place by blocked Gauss-Jordan; the inverse goes to G64 (FP64, may be null)
-// and to out + s * out_stride (complex64 if out_single, else complex128)
-hipError_t launch_factor3_plane(const Fac3Args& a, int l, const double2* Glow, const double2* Gup, double2* S,
-                                double2* Tm, double2* Cm, int* perm, int* pi, int* err,
+// - b_l c_{l+1} Gup (null: no such term; slabs gstride entries apart), inverted in place by blocked
+// Gauss-Jordan; the inverse goes to G64 (FP64, may be null) and to out + s * out_stride (complex64 if
+// out_single, else complex128)
+hipError_t launch_factor3_plane(const Fac3Args& a, int l, const double2* Glow, const double2* Gup, size_t gstride,
+                                double2* S, double2* Tm, double2* Cm, int* perm, int* pi, int* err,
                                 double2* G64, void* out, bool out_single, size_t out_stride,
                                 hipStream_t st);
 size_t factor3_panel_width();

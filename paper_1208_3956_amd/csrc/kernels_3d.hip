@@ -44,10 +44,11 @@ __device__ inline double2 cdiv(double2 a, double2 b) {
     return make_double2((a.x * b.x + a.y * b.y) / d, (a.y * b.x - a.x * b.y) / d);
 }
 
-// S = T_l - c_l b_{l-1} Glow - b_l c_{l+1} Gup (null: no such term) on every slab, identity on
-// the padding
+// S = T_l - c_l b_{l-1} Glow - b_l c_{l+1} Gup (null: no such term; slabs gstride entries apart) on
+// every slab, identity on the padding
 __global__ void __launch_bounds__(256) k3_build_S(Fac3Args a, int l, const double2* __restrict__ Glow,
-                                                  const double2* __restrict__ Gup, double2* __restrict__ S) {
+                                                  const double2* __restrict__ Gup, size_t gstride,
+                                                  double2* __restrict__ S) {
     const int s = blockIdx.y;
     const size_t BB = (size_t)a.Bp * a.Bp;
     const int W = a.sW[s], B = W * a.Nz;
@@ -60,8 +61,8 @@ __global__ void __launch_bounds__(256) k3_build_S(Fac3Args a, int l, const doubl
         const int col = (int)(e / a.Bp), row = (int)(e % a.Bp);
         double2 v = make_double2(0.0, 0.0);
         if (row < B && col < B) {
-            if (Glow) v = csub(v, cmul(cb, Glow[(size_t)s * BB + e]));
-            if (Gup) v = csub(v, cmul(bc, Gup[(size_t)s * BB + e]));
+            if (Glow) v = csub(v, cmul(cb, Glow[s * gstride + e]));
+            if (Gup) v = csub(v, cmul(bc, Gup[s * gstride + e]));
             const int xr = row % W, zr = row / W, xc = col % W, zc = col / W;
             const double2* sax = a.sax + (size_t)s * WP;
             const double2* saxh = a.saxh + (size_t)s * (WP + 1);
@@ -657,13 +658,13 @@ hipError_t launch_factor3_panelize(float2* F, size_t stride, int J, int Ny, int 
     return hipGetLastError();
 }
 
-hipError_t launch_factor3_plane(const Fac3Args& a, int l, const double2* Glow, const double2* Gup, double2* S,
-                                double2* Tm, double2* Cm, int* perm, int* pi, int* err,
+hipError_t launch_factor3_plane(const Fac3Args& a, int l, const double2* Glow, const double2* Gup, size_t gstride,
+                                double2* S, double2* Tm, double2* Cm, int* perm, int* pi, int* err,
                                 double2* G64, void* out, bool out_single, size_t out_stride,
                                 hipStream_t st) {
     const size_t BB = (size_t)a.Bp * a.Bp;
     unsigned nb = (unsigned)std::min<size_t>((BB + 255) / 256, 4096);
-    hipLaunchKernelGGL(k3_build_S, dim3(nb, a.J), dim3(256), 0, st, a, l, Glow, Gup, S);
+    hipLaunchKernelGGL(k3_build_S, dim3(nb, a.J), dim3(256), 0, st, a, l, Glow, Gup, gstride, S);
     for (int k0 = 0; k0 < a.Bp; k0 += NB) {
         if (a.Bp <= BPI_MAX)
             hipLaunchKernelGGL(k3_gj_panel_lds, dim3(a.J), dim3(NTI), 0, st, S, a.Bp, k0, perm, err);

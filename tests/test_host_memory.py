@@ -389,3 +389,37 @@ print(json.dumps({{"plain": len(plain), "first": len(first), "again": len(again)
     assert got["same"] and got["plain"] == got["first"] == got["again"], got
     assert got["built"] == [True, True, True] and got["calls"] == [True, True, True], got
     assert got["quiet"] == [[], [], []] and got["captured"] > 0, got
+
+
+@pytest.mark.parametrize("prec", ["C128", "MIXED"])
+def test_slab_factorisation_takes_no_second_set_of_matrices_it_cannot_have(recorder, prec):
+    """FP64 slab inverses: beside the stored factor two work matrices a slab in complex128, as an
+    elimination from one end needs; the second end's set may be missing."""
+    got = run(recorder, f"""
+import os
+os.environ["HELM_FACTOR3_FP64"] = "1"
+from paper_1208_3956_amd import empty_cache
+def go(fail=-1):
+    empty_cache()
+    H = setup(n=10, dim=3, prec={prec}, mode=FULL, stream=0x10)
+    R.rec_log(1)
+    R.rec_fail_malloc(fail)
+    st = status(L.helm_factor, H)
+    R.rec_fail_malloc(-1)
+    sizes = [n for w, p, n, d in log() if w == "malloc"]
+    again = status(L.helm_factor, H)
+    mat = max(L.helm_get_partition(H, 3)[2]) * L.helm_get_dims3(H)[2]
+    mat = 16 * ((mat + 63) // 64 * 64) ** 2 * L.helm_get_factor_slots(H, 3)[0]
+    L.helm_destroy(H)
+    return st, again, sizes, mat
+st, again, sizes, mat = go()
+assert st == 0 and again == 0
+out = [go(k)[:2] for k in range(len(sizes))]
+print(json.dumps({{"work": sum(n >= mat for n in sizes) - 1, "out": out, "n": len(sizes)}}))
+""")
+    if prec == "C128":
+        assert got["work"] == 2, got
+    assert all(again == 0 for _, again in got["out"]), got
+    # the factor, one end's five arrays and (complex64) the FP64 copies have to be had, the rest not
+    need = 6 if prec == "C128" else 8
+    assert [st for st, _ in got["out"]] == [2] * need + [0] * (got["n"] - need) and got["n"] == need + 5, got
