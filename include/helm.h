@@ -172,14 +172,15 @@ helm_status helm_factor(helm_t H);
 /*
  * Autotuner of the strip solver's y-partition (2-D): for each candidate number of rows
  * per chunk, refactor and time `reps` applications of the operator one GMRES iteration
- * applies (Algorithm 3 on the reduced columns of `rhs` and P on `rhs` in REDUCED mode, A P
- * on `rhs` in FULL mode) with HIP events on the handle's stream; the handle is left factored with
- * the fastest candidate.  The chunk size changes only the order of the substitutions
+ * applies (REDUCED: Algorithm 3 on the reduced columns of `rhs`, and an eighth of P on `rhs`, of
+ * which a solve applies one to 6 to 10 iterations; FULL: A P on `rhs`) with HIP events on the
+ * handle's stream; the handle is left factored with the fastest candidate.  The chunk size changes only the order of the substitutions
  * (the strip inverse is the same in exact arithmetic), so any candidate is correct.
  *   rhs     device, nrhs * N_y * N_x complex128 (padded grid): the panel to time on
  *   cand    host, ncand ints >= 2: candidate rows per chunk
  *   best    host, one int (may be NULL): the chosen rows per chunk
- *   ms      host, ncand doubles (may be NULL): milliseconds per application
+ *   ms      host, ncand doubles (may be NULL): milliseconds per application (REDUCED: with the
+ *           eighth of P)
  * 3-D handles have one chunk per slab: nothing is timed, best = N_y, ms = 0 (factored if
  * it was not).  HELM_EINVAL for nrhs, ncand or reps < 1, a candidate below 2 or a null
  * rhs / cand; errors of helm_factor are passed on.

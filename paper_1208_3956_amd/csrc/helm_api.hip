@@ -2887,8 +2887,10 @@ helm_status helm_autotune(helm_t H, int nrhs, const void* rhs, const int* cand, 
     CHK(ensure_sweep_ws(H, nrhs));
     // the operator one GMRES iteration applies: Algorithm 3 on the right-hand sides'
     // reduced columns (REDUCED), or P followed by A (FULL).  The dense strip operators of the
-    // reduced form hardly depend on the chunk size, so REDUCED times one application of P
-    // as well (Algorithms 2 and 4 and the restarts run it, and there the chunk size counts)
+    // reduced form hardly depend on the chunk size, so REDUCED times applications of P as well
+    // (Algorithms 2 and 4 and the restarts run it, and there the chunk size counts), and weighs
+    // them as a solve does: one to 6 to 10 iterations
+    constexpr double FIELDS_PER_ITERATION = 1.0 / 8;
     const size_t in_bytes = reduced ? (size_t)nrhs * g.Nrow() * nred * sizeof(double2) : field_bytes(H, nrhs);
     double2 *xin = nullptr, *xout = nullptr;
     struct Bufs { helm_t H; double2** a; double2** b; ~Bufs() { dfree(H, *a); dfree(H, *b); } } bufs{H, &xin, &xout};
@@ -2899,15 +2901,14 @@ helm_status helm_autotune(helm_t H, int nrhs, const void* rhs, const int* cand, 
                                         g.Nx, xin, H->st));
     else
         HIPCHK(hipMemcpyAsync(xin, rhs, in_bytes, hipMemcpyDeviceToDevice, H->st));
-    hipEvent_t e0, e1;
-    HIPCHK(hipEventCreate(&e0));
-    HIPCHK(hipEventCreate(&e1));
-    struct Ev { hipEvent_t a, b; ~Ev() { (void)hipEventDestroy(a); (void)hipEventDestroy(b); } } ev{e0, e1};
+    struct Ev {
+        hipEvent_t e[3] = {};
+        ~Ev() { for (hipEvent_t v : e) if (v) (void)hipEventDestroy(v); }
+    } ev;
+    for (hipEvent_t& v : ev.e) HIPCHK(hipEventCreate(&v));
+    auto field = [&]() { return apply_P_any(H, nrhs, static_cast<const double2*>(rhs), H->wk.PF); };
     auto apply = [&]() -> helm_status {
-        if (reduced) {
-            CHK(apply_AP_red(H, nrhs, xin, xout));
-            return apply_P_any(H, nrhs, static_cast<const double2*>(rhs), H->wk.PF);
-        }
+        if (reduced) return apply_AP_red(H, nrhs, xin, xout);
         CHK(apply_P_any(H, nrhs, xin, H->wk.PF));
         HIPCHK(helm::launch_apply_A(H->t, g, nrhs, H->wk.PF, nullptr, xout, H->st));
         return HELM_OK;
@@ -2919,13 +2920,17 @@ helm_status helm_autotune(helm_t H, int nrhs, const void* rhs, const int* cand, 
         CHK(helm_factor(H));
         CHK(prepare_dense(H, nrhs));
         CHK(apply());                      // warm-up (first touch of the layout)
-        HIPCHK(hipEventRecord(e0, H->st));
+        if (reduced) CHK(field());
+        HIPCHK(hipEventRecord(ev.e[0], H->st));
         for (int r = 0; r < reps; ++r) CHK(apply());
-        HIPCHK(hipEventRecord(e1, H->st));
-        HIPCHK(hipEventSynchronize(e1));
-        float t = 0.0f;
-        HIPCHK(hipEventElapsedTime(&t, e0, e1));
-        const double per = (double)t / reps;
+        HIPCHK(hipEventRecord(ev.e[1], H->st));
+        for (int r = 0; reduced && r < reps; ++r) CHK(field());
+        HIPCHK(hipEventRecord(ev.e[2], H->st));
+        HIPCHK(hipEventSynchronize(ev.e[2]));
+        float t = 0.0f, tf = 0.0f;
+        HIPCHK(hipEventElapsedTime(&t, ev.e[0], ev.e[1]));
+        if (reduced) HIPCHK(hipEventElapsedTime(&tf, ev.e[1], ev.e[2]));
+        const double per = (t + FIELDS_PER_ITERATION * tf) / reps;
         if (ms) ms[c] = per;
         if (bi < 0 || per < bms) { bi = c; bms = per; }
     }

@@ -28,6 +28,8 @@ int last_error = 0;
 std::string log_text;
 bool logging = false;
 size_t handles = 0x1000;
+long launches = 0;
+std::map<void*, long> at_launch;   // kernels launched before an event was recorded
 thread_local int cur = 0;
 void* captured_stream = nullptr;
 
@@ -125,9 +127,13 @@ int hipStreamWaitEvent(void* s, void* e, unsigned) { LOCK; note("wait", s, (size
 int hipEventCreate(void** e) { LOCK; *e = fresh(); return 0; }
 int hipEventCreateWithFlags(void** e, unsigned) { LOCK; *e = fresh(); return 0; }
 int hipEventDestroy(void*) { return 0; }
-int hipEventRecord(void* e, void* s) { LOCK; note("record", s, (size_t)e); return 0; }
+int hipEventRecord(void* e, void* s) { LOCK; note("record", s, (size_t)e); at_launch[e] = launches; return 0; }
 int hipEventSynchronize(void*) { return 0; }
-int hipEventElapsedTime(float* t, void*, void*) { *t = 1.0f; return 0; }
+int hipEventElapsedTime(float* t, void* a, void* b) {    // a millisecond a kernel
+    LOCK;
+    *t = (float)(at_launch[b] - at_launch[a]);
+    return 0;
+}
 int hipStreamBeginCapture(void*, int) { return 0; }
 int hipStreamEndCapture(void*, void** g) { *g = fresh(); return 0; }
 int hipStreamIsCapturing(void* s, int* c) { LOCK; *c = s && s == captured_stream; return 0; }
@@ -150,6 +156,7 @@ int __hipPopCallConfiguration(Dim* g, Dim* b, size_t* n, void** s) {
 int hipLaunchKernel(const void* f, Dim, Dim, void**, size_t, void* s) {
     LOCK;
     note("launch", s, (size_t)f);
+    ++launches;
     if (fail_launch == 0) { last_error = BAD; fail_launch = -1; return BAD; }
     if (fail_launch > 0) --fail_launch;
     return 0;

@@ -423,3 +423,26 @@ print(json.dumps({{"work": sum(n >= mat for n in sizes) - 1, "out": out, "n": le
     # the factor, one end's five arrays and (complex64) the FP64 copies have to be had, the rest not
     need = 6 if prec == "C128" else 8
     assert [st for st, _ in got["out"]] == [2] * need + [0] * (got["n"] - need) and got["n"] == need + 5, got
+
+
+def test_autotune_weighs_the_operators_as_a_solve_does(recorder):
+    """An iteration applies the reduced operator, a solve of 6 to 10 iterations P once (a kernel
+    takes a millisecond here)."""
+    got = run(recorder, """
+H = setup(n=60, J=4, stream=0x10, graph=0)
+L.helm_factor(H)
+f, psi = field(H, 2), np.zeros((2, 76 * 6), np.complex128)
+def launches(f):
+    R.rec_log(1)
+    f()
+    return sum(w == "launch" for w, *_ in log())
+P = lambda: L.helm_apply_P(H, 2, f.ctypes.data, f.copy().ctypes.data)
+AP = lambda: L.helm_apply_AP_reduced(H, 2, psi.ctypes.data, psi.copy().ctypes.data)
+P(), AP()
+ap, p = launches(AP), launches(P)
+F = setup(n=60, J=4, stream=0x10, mode=FULL)
+_, ms = L.helm_autotune(H, 2, f.ctypes.data, [9], 3)
+_, full = L.helm_autotune(F, 2, f.ctypes.data, [9], 3)
+print(json.dumps({"ms": ms, "want": ap + p / 8, "full": full, "p": p}))
+""")
+    assert got["ms"] == [got["want"]] and got["full"] == [got["p"] + 1], got
