@@ -10,8 +10,12 @@ import os
 from typing import Optional, Sequence
 
 
+# what the cached choices were timed on: entries of another operator are not looked up
+OPERATOR = "dense AP + P/8"
+
+
 def key(device: str, prec: str, mode: str, dims: Sequence[int], widths: Sequence[int], nrhs: int) -> str:
-    return "|".join([device, prec, mode, "x".join(map(str, dims)),
+    return "|".join([OPERATOR, device, prec, mode, "x".join(map(str, dims)),
                      ",".join(map(str, widths)), str(int(nrhs))])
 
 

@@ -446,3 +446,15 @@ _, full = L.helm_autotune(F, 2, f.ctypes.data, [9], 3)
 print(json.dumps({"ms": ms, "want": ap + p / 8, "full": full, "p": p}))
 """)
     assert got["ms"] == [got["want"]] and got["full"] == [got["p"] + 1], got
+
+
+def test_cached_choices_of_another_operator_are_not_used(tmp_path):
+    """Chunk sizes cached when the operator's block substitutions were timed mean nothing for the
+    dense operators."""
+    from paper_1208_3956_amd import tune
+    p = str(tmp_path / "tune.json")
+    tune.store(p, "|".join(["MI355X", "mixed", "reduced", "2032x2032x1", "62,61", "64"]), 16, {})
+    k = tune.key("MI355X", "mixed", "reduced", (2032, 2032, 1), [62, 61], 64)
+    assert tune.lookup(p, k) is None
+    tune.store(p, k, 32, {})
+    assert tune.lookup(p, k) == 32
