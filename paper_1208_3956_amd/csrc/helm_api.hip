@@ -1154,7 +1154,9 @@ helm_status apply_P_full(helm_t H, int nrhs, const double2* f, double2* out) {
     const auto& g = H->g;
     Work& w = H->wk;
     // complex64 solves three batches instead of 2 J - 1 single strips: worth it while a
-    // single strip fills at most half of the 256 CUs
+    // single strip (chunks x groups of 16 right-hand sides) fills at most half of the 256 CUs.
+    // Strip by strip against batches, 282 to 2032 rows, 8 to 32 strips: 1.7 to 4 times the time up to
+    // 65 workgroups a strip, 1.02 to 1.24 times at 99 to 136, 0.85 to 0.97 times from 192 on
     if (batched(H, nrhs) && (H->prec == HELM_C128 || H->ch.P * ((nrhs + 15) / 16) <= 128)) {
         // f is read after parts of out are written: where the two overlap the batches read a copy
         // (V is the sequential sweeps')
@@ -2053,10 +2055,11 @@ helm_status build_aug(helm_t H, int nrhs, long n, double2* b, const std::vector<
 }
 
 // first-cycle stop of the complex64 path, relative to the rounding noise Algorithm 2 leaves
-// off the reduced columns.  The true residual after a first cycle run to tol stalls at 4 to
-// 7 times that noise (2000^2 layers: noise 9.1e-6, stall 6.4e-5; 1000^2 lens: 6.0e-6 and
-// 2.2e-5 of ||f||), so the cycle stops at 3 times it: iterating further gains nothing, the
-// restart starts from the stall anyway
+// off the reduced columns.  The true residual after a first cycle run to tol stalls at 2 to
+// 25 times that noise (2000^2 layers: noise 8.5e-5, stall 4.6e-4; 1000^2 lens: 6.9e-6 and 1.7e-4;
+// 250^2 layers: 5.6e-6 and 1.3e-5 of ||f||), so the cycle stops at 3 times it: iterating further
+// gains nothing, the restart starts from the stall anyway.  Solves of these to 1e-6 and 1e-10 take
+// the same time with 1.5 to 6 (within 5%), and up to 30% more where the cycle runs to tol
 #ifndef FLOOR_PER_NOISE
 #define FLOOR_PER_NOISE 3.0
 #endif
