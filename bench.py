@@ -26,7 +26,7 @@ sys.path.insert(0, ROOT)
 
 METRIC = "RHS·gridpts/s to 1e-6 residual, 2000² 2-D, c64-mixed vs c128 on 1 GPU"
 PEAK = {"c64": 157.3, "c128": 78.6}          # dense MFMA TFLOP/s, FP32 / FP64
-PHASES = ("phase_a", "phase_b", "phase_c", "factor_chunks", "factor_separators")
+PHASES = ("phase_a", "phase_b", "phase_c", "factor_chunks", "factor_separators", "dense")
 
 
 def parse():
@@ -93,7 +93,7 @@ def phase_flops(H, wl, nrhs):
         B = [w * H.N_z for w in H.strip_width]
         B2 = sum(b * b for b in B) / len(B)
         return {"phase_a": 8.0 * B2 * nrhs * (2 * Ny - 1), "phase_b": 0.0, "phase_c": 0.0,
-                "factor_chunks": 8.0 * sum(B[r] ** 3 for r in reps) * Ny, "factor_separators": 0.0}
+                "factor_chunks": 8.0 * sum(B[r] ** 3 for r in reps) * Ny, "factor_separators": 0.0, "dense": 0.0}
     m = H.chunk_rows
     P = -(-Ny // m)
     n_int = Ny - (P - 1)                    # interior rows over all chunks
@@ -109,8 +109,33 @@ def phase_flops(H, wl, nrhs):
         # inverse (Gauss-Jordan, W^3) + top spike (2 W^3) + bottom spike (W^3) per interior row
         "factor_chunks": 8.0 * W3 * n_int * 4.0,
         "factor_separators": 8.0 * W3 * (P - 1) * 3.0,
+        "dense": 8.0 * dense_values(H) * nrhs,
     }
     return fl
+
+
+def dense_values(H):
+    """Matrix values of one dense strip solve, averaged over a sweep's strips: chunks of M rows (kappa
+    factorised ones joined, ns separators between them; kappa as the library chooses it, the fewest
+    values) with Rm 64 x 6 M and Tm (outputs M) x (3 M + 128) a chunk and Sm (64 ns)^2; five outputs a
+    strip, two at the sweep's last."""
+    m, Ny, J = H.chunk_rows, H.N_y, H.J
+    fine = -(-Ny // m)
+    best = None
+    for lev in range(8):
+        M, P = m << lev, -(-fine // (1 << lev))
+        if J < 2 or M > 128:
+            break
+        ns, rows = P - 1, min(M, Ny) if P == 1 else M
+        Mp = -(-rows // 16) * 16
+        K = 3 * Mp + (128 if ns else 0)
+        cost = 5 * P * Mp * K + ns * 64 * 6 * Mp + (64 * ns) ** 2 + (3e6 if ns else 0)
+        if best is None or cost < best[0]:
+            outs = (5.0 * (J - 2) + 2.0) / (J - 1)
+            best = (cost, outs * Ny * (3 * rows + (128 if ns else 0)) + ns * 64 * 6 * rows + (64 * ns) ** 2)
+        if P == 1:
+            break
+    return best[1] if best else 0.0
 
 
 def _oracle_solve_one(k):
@@ -691,11 +716,15 @@ def main():
     # roofline of the costliest hot kernel class
     fl = phase_flops(H, wl, nrhs)
     cnt, ms = kt[dom]
+    if dom == "dense" and cnt:
+        # the operator's panels drop converged right-hand sides, the fields' keep them all
+        solves, ops = 2 * (H.J - 1) * args.roofline_steps, res.panel_rhs_full / nrhs
+        fl["dense"] *= 1.0 - solves * (ops - res.panel_rhs / nrhs) / cnt
     avg_s = ms / 1e3 / max(cnt, 1)
     ach = fl[dom] / avg_s / 1e12 if avg_s > 0 else 0.0
     # the strip solves run in the working precision; the 2-D factor computes in FP64; the
     # 3-D mixed factor in FP32 unless it fell back to the FP64 route
-    if dom.startswith("phase"):
+    if dom.startswith("phase") or dom == "dense":
         arith = dtype
     else:
         arith = "c64" if (wl.dim == 3 and args.prec == "mixed" and H.factor_path == 1) else "c128"

@@ -379,16 +379,17 @@ helm_status helm_get_fusion_stats(helm_t H, long long* fused, long long* unfused
  * bracketed by a pair of HIP events on the handle's stream (events are recorded
  * asynchronously; no synchronisation is added).  helm_get_kernel_times synchronises the
  * stream and returns, per kernel class, the number of launches and their summed
- * duration in milliseconds since timing was last enabled.  Classes (nclass <= 8):
+ * duration in milliseconds since timing was last enabled.  Classes (nclass <= 9):
  *   0 strip solve phase A (chunk substitutions)   1 phase B (separators)
  *   2 phase C (spike correction + scatter)        3 factor, chunks
  *   4 factor, separators                          5 FP64 stencil
  *   6 GMRES vector kernels                        7 other
- * A launch over a batch of strips counts once per strip; the dense products of the reduced
- * form and their build are in class 7 (a reduced iteration then has none in 0 to 2).
+ *   8 dense products of the reduced form, a strip solve each (part of class 7 for nclass <= 8)
+ * A launch over a batch of strips counts once per strip; a reduced iteration on the dense
+ * products has none in 0 to 2.  Their build is in class 7.
  * launches, total_ms: host arrays of nclass entries.  At most 65536 launches are
  * recorded per enable; later ones are counted but not timed (ms stays a lower bound).
- * enable is a bit mask of the classes to time (bit c = class c, 0xFF = all); launches of
+ * enable is a bit mask of the classes to time (bit c = class c, 0xFF and 0x1FF = all); launches of
  * the other classes are still counted.  0 disables timing.  Every timed launch costs two
  * event records on the stream, so timing only the classes of interest disturbs less.
  * While timing is enabled the reduced operator is launched kernel by kernel, not replayed

@@ -26,7 +26,7 @@ EXPORTS = ["helm_default_opts", "helm_setup", "helm_factor", "helm_solve", "helm
            "helm_get_factor_slots", "helm_strip_solve_noalloc", "helm_get_panel_stats",
            "helm_get_fusion_stats", "helm_empty_cache"]
 KERNEL_CLASSES = ["phase_a", "phase_b", "phase_c", "factor_chunks", "factor_separators",
-                  "stencil", "gmres_vectors", "other"]
+                  "stencil", "gmres_vectors", "other", "dense"]
 
 
 class HelmOpts(ctypes.Structure):
@@ -278,7 +278,7 @@ def helm_get_fusion_stats(hdl):
 
 def helm_set_kernel_timing(hdl, mask: int) -> None:
     """mask: bit c times kernel class KERNEL_CLASSES[c]; 0 disables timing."""
-    check(lib().helm_set_kernel_timing(hdl, int(mask) & 0xFF), hdl)
+    check(lib().helm_set_kernel_timing(hdl, int(mask) & 0x1FF), hdl)
 
 
 def helm_get_kernel_times(hdl) -> dict:

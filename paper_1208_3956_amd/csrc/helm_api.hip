@@ -87,13 +87,14 @@ struct Work {
 // Event-pair timing of kernel launches (helm_set_kernel_timing).
 struct EventTimer : helm::KTimer {
     static constexpr int kMax = 65536;
+    static constexpr unsigned ALL = (1u << helm::K_NCLASS) - 1;
     std::vector<hipEvent_t> pool;
     std::vector<int> cls;        // class of pair k (events 2k, 2k+1)
     int used = 0;
     long counts[helm::K_NCLASS] = {0};
     double ms[helm::K_NCLASS] = {0};
     int pending_cls = -1;
-    unsigned mask = 0xFFu;       // classes whose launches are timed (all are counted)
+    unsigned mask = ALL;         // classes whose launches are timed (all are counted)
     hipEvent_t get(int idx) {
         while ((int)pool.size() <= idx) {
             hipEvent_t e;
@@ -957,7 +958,7 @@ helm_status red_sweep(helm_t H, int nrhs, bool up, const double2* psi, bool base
         const V* Tm = static_cast<const V*>(H->red_T) + (fs * 2 + (up ? 0 : 1)) * p.tsz;
         const V* Rm = static_cast<const V*>(H->red_R) + (fs * 2 + (up ? 0 : 1)) * p.rsz;
         const V* Sm = static_cast<const V*>(H->red_S) + fs * p.ssz;
-        HIPCHK(TIMED(H, helm::K_OTHER, helm::launch_red_strip<T>(a, Tm, Rm, Sm, H->st)));
+        HIPCHK(TIMED(H, helm::K_DENSE, helm::launch_red_strip<T>(a, Tm, Rm, Sm, H->st)));
     }
     return HELM_OK;
 }
@@ -3229,7 +3230,8 @@ helm_status helm_set_kernel_timing(helm_t H, int enable) {
         if (!H->timer) H->timer = new EventTimer();
         HIPCHK(quiesce(H));
         H->timer->reset();
-        H->timer->mask = (unsigned)enable & 0xFFu;
+        // all of the first eight classes stood for all there are
+        H->timer->mask = ((unsigned)enable & 0xFFu) == 0xFFu ? EventTimer::ALL : (unsigned)enable & EventTimer::ALL;
     } else if (H->timer) {
         HIPCHK(quiesce(H));
         delete H->timer;
@@ -3245,8 +3247,10 @@ helm_status helm_get_kernel_times(helm_t H, int nclass, int* launches, double* t
     H->timer->collect();
     for (int c = 0; c < nclass; ++c) {
         const bool ok = c < helm::K_NCLASS;
-        if (launches) launches[c] = ok ? (int)H->timer->counts[c] : 0;
-        if (total_ms) total_ms[c] = ok ? H->timer->ms[c] : 0.0;
+        // a caller that does not ask for the dense products' class has them in `other`
+        const bool add = c == helm::K_OTHER && nclass <= helm::K_DENSE;
+        if (launches) launches[c] = ok ? (int)(H->timer->counts[c] + (add ? H->timer->counts[helm::K_DENSE] : 0)) : 0;
+        if (total_ms) total_ms[c] = ok ? H->timer->ms[c] + (add ? H->timer->ms[helm::K_DENSE] : 0.0) : 0.0;
     }
     return HELM_OK;
 }

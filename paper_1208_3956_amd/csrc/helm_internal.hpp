@@ -231,7 +231,7 @@ struct KTimer {
     virtual ~KTimer() = default;
 };
 enum KClass { K_PHASE_A = 0, K_PHASE_B, K_PHASE_C, K_FACTOR_CHUNKS, K_FACTOR_SEPS, K_STENCIL,
-              K_GMRES, K_OTHER, K_NCLASS };
+              K_GMRES, K_OTHER, K_DENSE, K_NCLASS };
 
 // ---------------------------------------------------------------- kernels (launchers)
 // F32 (complex64 path) receives every stored block rounded to complex64, null otherwise

@@ -294,7 +294,7 @@ class Helmholtz:
         classes, or only those named in `classes` (names as in kernel_times())."""
         mask = 0
         if enable:
-            mask = 0xFF if classes is None else sum(1 << L.KERNEL_CLASSES.index(c) for c in classes)
+            mask = 0x1FF if classes is None else sum(1 << L.KERNEL_CLASSES.index(c) for c in classes)
         L.helm_set_kernel_timing(self.h, mask)
 
     def kernel_times(self) -> dict:

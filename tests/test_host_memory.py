@@ -458,3 +458,28 @@ def test_cached_choices_of_another_operator_are_not_used(tmp_path):
     assert tune.lookup(p, k) is None
     tune.store(p, k, 32, {})
     assert tune.lookup(p, k) == 32
+
+
+def test_dense_products_have_a_kernel_class(recorder):
+    """The launches of the reduced operator's dense strip solves, one each; callers of the eight classes
+    there were find them in the last of these, as before."""
+    got = run(recorder, """
+H = setup(n=60, J=4, stream=0x10)
+L.helm_factor(H)
+psi = np.zeros((2, 76 * 6), np.complex128)
+AP = lambda: L.helm_apply_AP_reduced(H, 2, psi.ctypes.data, psi.copy().ctypes.data)
+AP()
+out = []
+for mask in (0x1FF, 0xFF, 0x100, 0x80):
+    L.helm_set_kernel_timing(H, mask)
+    AP()
+    kt = L.helm_get_kernel_times(H)
+    cnt, ms = (ctypes.c_int * 8)(), (ctypes.c_double * 8)()
+    L.lib().helm_get_kernel_times(H, 8, cnt, ms)
+    out.append([kt["dense"], kt["other"], (cnt[7], ms[7])])
+print(json.dumps(out))
+""")
+    for (dn, dms), (on, oms), (n8, ms8) in got:
+        assert dn == 2 * 3 and n8 == dn + on and ms8 == dms + oms, got
+    timed = [(d[1] > 0, o[1] > 0) for d, o, _ in got]
+    assert timed == [(True, True), (True, True), (True, False), (False, True)], got
