@@ -1018,13 +1018,14 @@ helm_status prepare_dense(helm_t H, int nrhs) {
     if (!dense(H, nrhs) || H->batch_fuse || batched_in_full(H, nrhs) || capturing(H)) return HELM_OK;
     Work& w = H->wk;
     const size_t per = batch_strip_bytes(H, nrhs), want = (size_t)batch_strips(H, nrhs, H->g.J);
-    if (w.bcap < want * nrhs) {
+    size_t freeb = 0;
+    HIPCHK(free_bytes(&freeb));
+    const size_t held = w.bcap * (per / nrhs), fit = std::min(want, std::max<size_t>(1, (freeb + held) / 8 / per));
+    if (w.bcap < fit * nrhs) {
         dfree(H, w.Yb);
         w.Yb = nullptr;
         w.bcap = 0;
-        size_t freeb = 0;
-        HIPCHK(free_bytes(&freeb));
-        for (size_t nb = std::min(want, std::max<size_t>(1, freeb / 8 / per)); nb >= 1; nb /= 2)
+        for (size_t nb = fit; nb >= 1; nb /= 2)
             if (try_alloc(&w.Yb, per * nb)) {
                 w.bcap = nb * nrhs;
                 break;

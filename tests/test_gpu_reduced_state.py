@@ -86,3 +86,16 @@ def test_P_recorded_into_a_graph(prec, warm):
         assert (out - want).abs().max() <= tol * want.abs().max(), k
         assert (other - 2.0 * want).abs().max() <= 2 * tol * want.abs().max(), k
     H.close()
+
+
+@pytest.mark.parametrize("prec", ["c128", "mixed"])
+@pytest.mark.parametrize("n,J,chunk", [(30, 2, 9), (150, 5, 2), (150, 5, 9)])
+def test_reduced_operator_has_one_order_of_sums(prec, n, J, chunk):
+    """Bit for bit the same for every width of the panel: tiles of four and of 16 right-hand sides, one
+    group and several."""
+    H = _handle(prec, "reduced", n, J, chunk)
+    psi = _field(H, 49, chunk, 2 * (H.J - 1))
+    wide = H.apply_AP_reduced(psi)
+    for nrhs in (1, 2, 3, 4, 5, 8, 9, 13, 16, 17, 32):
+        assert torch.equal(H.apply_AP_reduced(psi[:nrhs]), wide[:nrhs]), nrhs
+    H.close()

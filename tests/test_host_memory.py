@@ -483,3 +483,57 @@ print(json.dumps(out))
         assert dn == 2 * 3 and n8 == dn + on and ms8 == dms + oms, got
     timed = [(d[1] > 0, o[1] > 0) for d, o, _ in got]
     assert timed == [(True, True), (True, True), (True, False), (False, True)], got
+
+
+def test_batches_in_little_memory_keep_their_workspace(recorder):
+    """Batches of fewer strips than wanted, for want of memory: the next call neither frees nor allocates."""
+    got = run(recorder, """
+from paper_1208_3956_amd import empty_cache
+out = []
+for room in (600, 500, 400, 300, 200):
+    A = setup(n=100, J=6, mode=FULL, stream=0x10)
+    L.helm_factor(A)
+    g = field(A, 64)
+    L.helm_apply_P(A, 1, g.ctypes.data, g.copy().ctypes.data)      # builds the dense operators
+    empty_cache()
+    R.rec_budget(0, room << 20)
+    go = lambda: status(L.helm_apply_P, A, 64, g.ctypes.data, g.copy().ctypes.data)
+    st = go()
+    room_left = R.rec_room(0)
+    R.rec_log(1)
+    st2 = go()
+    quiet = [w for w, *_ in log() if w in ("malloc", "free", "sync", "nomem")]
+    R.rec_log(0)
+    R.rec_budget(0, 64 << 30)
+    L.helm_destroy(A)
+    out.append((room, st, st2, quiet))
+print(json.dumps(out))
+""")
+    assert all(st == st2 == 0 and not quiet for _, st, st2, quiet in got if st == 0) and got[0][1] == 0, got
+
+
+def test_pool_with_several_threads(recorder):
+    """Handles made, used and closed by several threads at a time: every block is one handle's, and
+    all of it can be given back."""
+    got = run(recorder, """
+import threading
+bad = []
+def work(seed):
+    try:
+        for k in range(6):
+            H = setup(n=30 + 4 * ((seed + k) % 5), J=2, stream=0x10 + 16 * seed)
+            L.helm_factor(H)
+            f = field(H, 1 + seed % 3)
+            L.helm_apply_P(H, 1 + seed % 3, f.ctypes.data, f.copy().ctypes.data)
+            L.helm_destroy(H)
+            if k % 3 == 2:
+                L.helm_empty_cache()
+    except Exception as e:
+        bad.append(repr(e))
+ts = [threading.Thread(target=work, args=(i,)) for i in range(6)]
+[t.start() for t in ts]
+[t.join() for t in ts]
+L.helm_empty_cache()
+print(json.dumps({"bad": bad, "live": R.rec_live(0)}))
+""")
+    assert got == {"bad": [], "live": 0}, got
