@@ -11,8 +11,8 @@
 //     S_p = T_p - c_p b_{p-1} G_{p-1} - b_p c_{p+1} G_{p+1},
 //     x_p = G_p (r_p - c_p y_{p-1} - b_p y_{p+1})
 //     below  x_l = y_l - b_l G_l x_{l+1},       above  x_l = y_l - c_l G_l x_{l-1}
-// The two ends advance together: one launch per pair of planes, N_y + 1 dependent steps
-// instead of 2 N_y - 1, each with twice the tiles (a single plane's leave two thirds of the
+// The two ends advance together: one launch per pair of planes, 2 p + 1 dependent steps (N_y + 1, or
+// N_y + 2 for odd N_y) instead of 2 N_y - 1, each with twice the tiles (a single plane's leave two thirds of the
 // chip idle), for the same operations.
 // The blocks are dense (B = W N_z up to ~2000), so the explicit inverses are computed in
 // FP64 by blocked Gauss-Jordan elimination with partial pivoting over the whole column:
