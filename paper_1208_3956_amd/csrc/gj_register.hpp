@@ -22,7 +22,7 @@ namespace gjr {
 // and products (about 750 clocks for 64 + 64 instructions), the search (270) and a barrier
 // with its round through LDS (280).  The wave that owns column k + 1 finds the pivot and forms
 // the multipliers for all waves after its update of step k, so there is one such round a step.
-// 53 -> 47 us for a 64 x 64 block (before: every wave's own multipliers with two divisions from a
+// 53 -> 49 us for a 64 x 64 block (before: every wave's own multipliers with two divisions from a
 // second read of LDS, a 64-bit search, products waiting for the lane reads).  Deferring the
 // owner's update past the barrier took 56: the waves wait for it one step later.
 struct GJShared {
