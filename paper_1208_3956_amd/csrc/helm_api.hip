@@ -486,9 +486,13 @@ helm_status dmalloc(helm_t H, P** p, size_t bytes) {
 // (and collected) from code that has another device current
 struct OnDevice {
     int prev = -1;
+    hipError_t err = hipSuccess;
     explicit OnDevice(helm_t H) {
         int cur = H->dev;
-        if (hipGetDevice(&cur) == hipSuccess && cur != H->dev && hipSetDevice(H->dev) == hipSuccess) prev = cur;
+        err = hipGetDevice(&cur);
+        if (err != hipSuccess || cur == H->dev) return;
+        err = hipSetDevice(H->dev);
+        if (err == hipSuccess) prev = cur;
     }
     ~OnDevice() { if (prev >= 0) (void)hipSetDevice(prev); }
     OnDevice(const OnDevice&) = delete;
@@ -503,7 +507,7 @@ bool try_alloc(void** p, size_t bytes) { return Pool::get().alloc(p, std::max<si
 // which a call that failed half way has not joined
 hipError_t quiesce(helm_t H) {
     OnDevice on(H);
-    hipError_t r = H->st ? hipStreamSynchronize(H->st) : hipDeviceSynchronize();
+    hipError_t r = on.err != hipSuccess ? on.err : H->st ? hipStreamSynchronize(H->st) : hipDeviceSynchronize();
     for (hipStream_t q : {H->st_c[0], H->st_c[1], H->st_fac}) {
         if (!q) continue;
         const hipError_t e = hipStreamSynchronize(q);
