@@ -356,8 +356,8 @@ helm_status fail(helm_t H, helm_status code, const std::string& msg) {
 // model (a misfit and its gradient) allocated and freed 3.5 GB per call; the frees alone took
 // 6 to 170 ms (the driver clears what it takes back, at about 35 GB/s when it has a backlog)
 // against 28 ms of work.  At most POOL_BYTES per device stay cached, the oldest block goes
-// first, and all of them when an allocation fails.  A block enters only after the stream that
-// used it has been synchronised, so that any thread may take it for any stream.
+// first, and all of them when an allocation fails.  A block enters only after the streams that
+// used it have been synchronised (dfree), so that any thread may take it for any stream.
 struct Pool {
     static constexpr size_t POOL_BYTES = (size_t)8 << 30;
     static constexpr int MAX_DEV = 64;
